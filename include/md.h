@@ -174,28 +174,18 @@ typedef struct {
     int32_t n;          /* particles (0 if the slot is empty) */
 } md_obs;
 
-/* Launch shapes (the autotuner's knobs).  None changes any result bit. */
+/* Launch shapes (the autotuner's knobs).  None changes any result bit.  The
+ * list build takes one wave per cell whatever the build_* fields say: they
+ * are checked and kept, and have no effect. */
 typedef struct {
     int32_t step_block;    /* threads per block of the fused step kernel: 64..1024, multiple of 64 */
-    int32_t build_width;   /* cells per row segment staged in LDS by the list build: 1..16 */
-    int32_t build_block;   /* threads per block of the list build: 64..1024, multiple of 64 */
+    int32_t build_width;   /* 1..16; no effect */
+    int32_t build_block;   /* 64..1024, multiple of 64; no effect */
     int32_t graph_steps;   /* steps per captured hipGraph (even, 2..256); 0 = no graphs */
     int32_t xcd_remap;     /* 1 = map consecutive particle tiles to one XCD (8 XCDs) */
-    int32_t build_lanes;   /* lanes that build one particle's list together: 1, 2, 4, .., 64;
-                            * 0 = automatic: one lane for replicas with >= 256 row segments;
-                            * smaller replicas split each segment's members over several
-                            * work items, each using the most lanes that keep one group per
-                            * member (16 for single-cell replicas) */
-    int32_t build_split;   /* most list-build work items one row segment is split into (the
-                            * members of a small replica's segments are shared out): 0 =
-                            * automatic (up to 256 / segments per replica), 1 = no split,
-                            * up to 256 */
-    int32_t build_bulk;    /* a step's list build in which at least this many replicas rebuild
-                            * uses one lane per member and unsplit row segments for every
-                            * replica of more than one cell, whatever build_lanes and
-                            * build_split say (the shape that suits many simultaneous
-                            * rebuilds, as aligned rebuilds make); 0 = never.  Changes no
-                            * list entry. */
+    int32_t build_lanes;   /* 0, 1, 2, 4, .., 64; no effect */
+    int32_t build_split;   /* 0..256; no effect */
+    int32_t build_bulk;    /* >= 0; no effect */
 } md_launch;
 
 /* ---- sizing and lifetime ------------------------------------------------ */

@@ -91,7 +91,7 @@ struct md_system {
     char *ws = nullptr;
     int64_t ws_bytes = 0;
     // device arrays
-    uint4 *st[3]{}, *sc_st[3]{}, *snap[2]{}, *sc_snap = nullptr, *xref = nullptr;
+    uint4 *st[3]{}, *sc_st[3]{}, *snap[2]{}, *sc_snap = nullptr, *xref = nullptr, *cand = nullptr;
     int4 *meta = nullptr, *sc_meta = nullptr;
     int *nbr = nullptr, *nbr_cnt = nullptr;
     double *obs = nullptr, *obs_out = nullptr;
@@ -238,6 +238,7 @@ static int64_t carve(md_system *s, const Layout &L, char *base)
     d->xref = c.take<uint4>(L.P * L.NS);
     d->meta = c.take<int4>(L.P);
     d->sc_meta = c.take<int4>(L.P);
+    d->cand = c.take<uint4>(L.P);
     d->nbr_cnt = c.take<int>(L.P);
     d->nbr = c.take<int>(L.P * L.cap);
     d->obs = c.take<double>(L.P * 8);
@@ -326,74 +327,49 @@ static int cells_per_edge(double L, double rl)
     return nd;
 }
 
-// staged candidates per list-build workgroup (48 KB of LDS)
-static int lds_cap_of(int prec) { return prec == PREC_FP64 ? 1536 : 3072; }
-
-// Grids of the sort and list-build kernels: one full residency of the
-// device (queried for the current block size).
+// Grids of the sort and list-build kernels: one full residency of the device.
 static md_status size_grids(md_system *s)
 {
     int per_cu = 0;
     HIPCHK(s, occupancy_permute(s->prec, &per_cu));
     s->grid_perm = std::max(1, per_cu) * s->n_cu;
     per_cu = 0;
-    HIPCHK(s, occupancy_build(s->prec, s->launch.build_block, lds_cap_of(s->prec), &per_cu));
-    if (per_cu < 1) return fail(s, MD_E_ARG, "list-build block of %d threads does not fit a CU", s->launch.build_block);
-    s->grid_build = per_cu * s->n_cu;
+    HIPCHK(s, occupancy_build(s->prec, &per_cu));
+    s->grid_build = std::max(1, per_cu) * s->n_cu;
     return MD_OK;
 }
 
-// members per list-build work item of a single-cell replica: one group of
-// build_lanes lanes (16 when automatic) per member
-static int single_members(const md_system *s)
+// The form of a replica's list build (none changes a list entry).  With 12 or
+// more members per cell a product of the matrix cores (32 members x 32
+// candidates) is full enough to beat one lane per candidate, whose cost per
+// cell grows with the square of its members; both take about 2,500
+// instructions per cell at 14.  Below that, replicas of many cells give each
+// member a lane (64 members share a wave), and smaller ones, which would
+// leave the chip idle that way, give each cell a wave.
+static int build_mode(int n, int nd)
 {
-    const int G = s->launch.build_lanes ? s->launch.build_lanes : 16;
-    return std::max(1, s->launch.build_block / G);
+    const int64_t nc = (int64_t)nd * nd * nd;
+    if (nd == 1) return BUILD_SINGLE;
+    if (n >= 12 * nc) return BUILD_CELLS;
+    return nc > 100000 ? BUILD_MEMBERS : BUILD_SPARSE;
 }
 
-// Work decomposition of the list build of one replica.  A replica with at
-// least one row segment per compute unit builds one segment per work item,
-// one lane per member.  A smaller one (whose build would otherwise run on a
-// few CUs, each testing every member against hundreds of candidates) splits
-// each segment's members over up to 256 / segments work items (at least 16
-// members each) and lets a group of lanes share each member's candidates.
-// None of this changes a list entry.
-static void build_shape(const md_system *s, int n, int nd, int &parts, int &lanes)
+// List-build items per cell: two where the mean cell holds more than 29
+// members, so that most cells take more than one product of 32 (at the 27.8
+// of a large mixture about one cell in thirty does, and an item of its own
+// for the rest of every cell would cost more than it spreads).
+static int build_parts(int n, int nd)
 {
-    parts = 1;
-    lanes = s->launch.build_lanes;
-    if (nd == 1) return;
-    const int W = s->launch.build_width;
-    const int nseg = nd <= W + 2 ? 1 : (nd + W - 1) / W;
-    const int base = nd * nd * nseg;
-    if (base >= 256) {
-        if (!lanes) lanes = 1;
-        return;
+    return build_mode(n, nd) == BUILD_CELLS && n > 29 * (int64_t)nd * nd * nd ? 2 : 1;
+}
+
+static int items4_of(int n, int nd)
+{
+    switch (build_mode(n, nd)) {
+    case BUILD_SINGLE: return (n + SINGLE_MEMBERS - 1) / SINGLE_MEMBERS;
+    case BUILD_MEMBERS: return (n + 63) / 64;
+    default: return nd * nd * nd * build_parts(n, nd);
     }
-    parts = std::max(1, std::min((256 + base - 1) / base, n / base / 16));
-    if (s->launch.build_split > 0) parts = std::min(parts, s->launch.build_split);
-}
-
-static int items4_of(const md_system *s, int n, int nd)
-{
-    if (nd == 1) {
-        const int M = single_members(s);
-        return (n + M - 1) / M;
-    }
-    int parts, lanes;
-    build_shape(s, n, nd, parts, lanes);
-    int W = s->launch.build_width;
-    int nseg = nd <= W + 2 ? 1 : (nd + W - 1) / W;
-    return nd * nd * nseg * parts;
-}
-
-// Work items of a bulk list build (one per row segment; a single-cell
-// replica keeps its usual items).
-static int bulk_items_of(const md_system *s, int n, int nd)
-{
-    if (nd == 1) return items4_of(s, n, nd);
-    const int W = s->launch.build_width;
-    return nd * nd * (nd <= W + 2 ? 1 : (nd + W - 1) / W);
 }
 
 static md_status upload_items(md_system *s)
@@ -405,7 +381,7 @@ static md_status upload_items(md_system *s)
         int a3 = 0, a4 = 0, a5 = 0;
         if (h.attached) {
             a3 = h.nd * h.nd * h.nd;
-            a4 = items4_of(s, h.n, h.nd);
+            a4 = items4_of(h.n, h.nd);
             a5 = (h.n + 4095) / 4096;
         }
         p3[k + 1] = p3[k] + a3;
@@ -507,6 +483,7 @@ static md_status launch_rebuild(md_system *s, int p, int force_slot, bool from_s
     for (int k = 0; k < 3; ++k) pa.sc_st[k] = s->sc_st[k];
     pa.sc_snap = s->sc_snap;
     pa.sc_meta = s->sc_meta;
+    pa.cand = s->cand;
     pa.status = s->status;
     HIPCHK(s, launch_permute(prec, pa, s->grid_perm, s->stream));
 
@@ -516,26 +493,22 @@ static md_status launch_rebuild(md_system *s, int p, int force_slot, bool from_s
     ba.max_slots = (int)s->lay.slots;
     ba.force_slot = force_slot;
     ba.from_scratch = from_scratch ? 1 : 0;
-    ba.width = s->launch.build_width;
-    ba.lds_cap = lds_cap_of(prec);
-    ba.single_members = single_members(s);
-    ba.bulk = s->launch.build_bulk;
     ba.xcd = s->launch.xcd_remap;
     ba.items_pref = s->items4;
     ba.rep = s->rep;
-    ba.need = s->need[p];
     ba.rlist = s->rlist[p];
     ba.ctl = s->ctl[p ^ 1];
     ba.cs = s->cs;
     ba.cs_new = s->cs_new;
     ba.corder = s->corder;
     ba.src_x = s->sc_snap;
+    ba.cand = s->cand;
     ba.snap_cur = s->snap[p ^ 1];
     for (int k = 0; k < 3; ++k) ba.sc_st[k] = s->sc_st[k];
     ba.sc_meta = s->sc_meta;
     ba.status = s->status;
     ba.pp = s->pp;
-    HIPCHK(s, launch_build(prec, ba, s->grid_build, s->launch.build_block, s->stream));
+    HIPCHK(s, launch_build(prec, ba, s->grid_build, s->stream));
     return MD_OK;
 }
 
@@ -548,23 +521,22 @@ static md_status launch_build_main(md_system *s, int slot)
     ba.max_slots = (int)s->lay.slots;
     ba.force_slot = slot;
     ba.from_scratch = 0;
-    ba.width = s->launch.build_width;
-    ba.lds_cap = lds_cap_of(s->prec);
-    ba.single_members = single_members(s);
     ba.xcd = s->launch.xcd_remap;
     ba.items_pref = s->items4;
     ba.rep = s->rep;
-    ba.need = s->need[0];
     ba.rlist = s->rlist[0];
     ba.ctl = s->ctl[0];
     ba.cs = s->cs;
     ba.cs_new = s->cs_new;
     ba.corder = s->corder;
     ba.src_x = s->xref;
+    ba.cand = s->cand;
     ba.snap_cur = s->snap[0];
     ba.status = s->status;
     ba.pp = s->pp;
-    HIPCHK(s, launch_build(s->prec, ba, s->grid_build, s->launch.build_block, s->stream));
+    const SlotHost &h = s->slots[slot];
+    if (build_mode(h.n, h.nd) == BUILD_CELLS) HIPCHK(s, launch_cand(s->prec, ba, s->cand, slot, h.n, s->stream));
+    HIPCHK(s, launch_build(s->prec, ba, s->grid_build, s->stream));
     return MD_OK;
 }
 
@@ -758,13 +730,18 @@ static RepDev repdev_of(const md_system *s, const SlotHost &h)
             r.xsc[t] = p.smooth ? (float)(u / p.hsd[t]) : 0.0f;
             r.ihs[t] = p.smooth ? (float)(1.0 / p.hsd[t]) : 0.0f;
         }
+        const double cu = (double)CELL_UNITS * h.nd / h.L;
+        for (int t = 0; t < 4; ++t) {
+            r.rl2s[t] = (float)(p.rl2d[t] / (u * u));
+            r.rlc[t] = (float)(p.rl2d[t] * cu * cu);
+        }
         r.hs2s = (float)(p.hs2d / (u * u));
         r.hs2s_early = (float)(p.hs2d_early / (u * u));
     }
     r.items3 = h.nd * h.nd * h.nd; // a sort work item covers a cell in every plane
-    r.items4 = items4_of(s, h.n, h.nd);
-    r.items4b = bulk_items_of(s, h.n, h.nd);
-    build_shape(s, h.n, h.nd, r.bparts, r.blanes);
+    r.items4 = items4_of(h.n, h.nd);
+    r.bmode = build_mode(h.n, h.nd);
+    r.bparts = build_parts(h.n, h.nd);
     return r;
 }
 

@@ -25,11 +25,10 @@
 //                over them in old slot order gives each its new slot.  The
 //                whole particle record is gathered into the scratch arena,
 //                positions folded back into the box.
-//   k_build<P>   per row segment of cells (one workgroup): the segment's
-//                27-cell neighbourhood is staged in LDS, every member scans
-//                its own cell and then the 13 opposite cell pairs (Sec. 4.1)
-//                and writes its list column-major; the sorted record is
-//                copied back from scratch.
+//   k_build<P>   per cell (one wave): its members' lists over the own cell and
+//                then the 13 opposite cell pairs (Sec. 4.1), the distance
+//                tests on the matrix cores; the sorted records are copied
+//                back from scratch.
 //
 // Bitwise determinism: lists are in a canonical order (own cell, then +o/-o
 // pairs; inside a cell the A members, then the B members, in slot order), the sort is stable, each particle sums
@@ -84,8 +83,7 @@ __device__ __forceinline__ bool slot_selected(int s, int force_slot, const int *
 // visits the items of the slots on the rebuild list written by k_step; a
 // host-forced rebuild visits those of the selected slots (items_pref holds
 // the host's per-slot item counts as a prefix).  `which` names the item
-// count of a listed slot: 3 the sort's, 4 the list build's, 5 the bulk list
-// build's.  `unit` is this worker's index among `nunits` workers;
+// count of a listed slot: 3 the sort's, 4 the list build's.  `unit` is this worker's index among `nunits` workers;
 // visit(slot, item) is called for each item assigned to it.  Consecutive
 // slots start on different workers so that small replicas spread over the
 // grid.  The slots and their item counts are read 64 at a time, one per lane
@@ -107,7 +105,7 @@ __device__ __forceinline__ void for_items(const int *rlist, const int *items_pre
         if (li < cnt) {
             if (listed) {
                 sl = rlist[1 + li];
-                its = which == 3 ? rep[sl].items3 : which == 4 ? rep[sl].items4 : rep[sl].items4b;
+                its = which == 3 ? rep[sl].items3 : rep[sl].items4;
             } else {
                 sl = li;
                 if (slot_selected(sl, force_slot, nullptr, ctl)) its = items_pref[sl + 1] - items_pref[sl];
@@ -137,6 +135,55 @@ __device__ __forceinline__ void u4_to_dbl2(uint4 u, double &a, double &b)
 {
     a = __longlong_as_double(((unsigned long long)u.y << 32) | u.x);
     b = __longlong_as_double(((unsigned long long)u.w << 32) | u.z);
+}
+
+// Order this wave's LDS accesses (no other wave shares the data).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Position relative to the centre of the particle's own cell, in units of
+// 1 / CELL_UNITS of the cell edge: the fraction of X nd 2^-32 (fixed point),
+// or of the folded double position.  The cell is the one the sort uses.
+template <int P>
+__device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, const uint4 &b, float u[3])
+{
+    if constexpr (P == PREC_FP64) {
+        double x[3], w;
+        u4_to_dbl2(a, x[0], x[1]);
+        u4_to_dbl2(b, x[2], w);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double t = (x[d] - r.L * floor(x[d] * r.invL)) * r.invL * (double)r.nd;
+            u[d] = (float)(t - (double)dbl_cell1(x[d], r.L, r.invL, r.nd) - 0.5) * CELL_UNITS;
+        }
+    } else {
+        const uint32_t X[3] = {a.x, a.y, a.z};
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            u[d] = (float)(int)((X[d] * (uint32_t)r.nd) ^ 0x80000000u) * (CELL_UNITS / 4294967296.0f);
+    }
+}
+
+// Candidate record of the list build: position in cell units and its squared
+// length, each as two half-precision words (high words x, y, z, low words x,
+// y, z, then the square's).
+__device__ __forceinline__ unsigned half2_bits(_Float16 a, _Float16 b)
+{
+    return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+}
+template <int P>
+__device__ __forceinline__ uint4 cand_record(const RepDev &r, const uint4 &a, const uint4 &b)
+{
+    float u[3];
+    cell_units<P>(r, a, b, u);
+    const float s = __builtin_fmaf(u[0], u[0], __builtin_fmaf(u[1], u[1], u[2] * u[2]));
+    const _Float16 xh = (_Float16)u[0], yh = (_Float16)u[1], zh = (_Float16)u[2], sh = (_Float16)s;
+    const _Float16 xl = (_Float16)(u[0] - (float)xh), yl = (_Float16)(u[1] - (float)yh),
+                   zl = (_Float16)(u[2] - (float)zh), sl = (_Float16)(s - (float)sh);
+    return make_uint4(half2_bits(xh, yh), half2_bits(zh, xl), half2_bits(yl, zl), half2_bits(sh, sl));
 }
 
 // ------------------------------------------------------- per-precision state

@@ -72,23 +72,22 @@ struct PermArgs {
     uint4 *sc_st[3];
     uint4 *sc_snap;
     int4 *sc_meta;
+    uint4 *cand; // candidate records of the list build
     int *status;
 };
 
 struct BuildArgs {
     KArena A;
-    int max_slots, force_slot, from_scratch, width, lds_cap, xcd;
-    int single_members; // members per work item of a single-cell replica
-    int bulk;           // rebuilding replicas from which a step's build is a bulk build; 0 = never
+    int max_slots, force_slot, from_scratch, xcd;
     const int *items_pref;
     const RepDev *rep;
-    const int *need;
     const int *rlist;
     const Ctl *ctl;
     int *cs;
     const int *cs_new;
     const int *corder;
     const uint4 *src_x;
+    const uint4 *cand; // candidate records (cand_record)
     uint4 *snap_cur;
     const uint4 *sc_st[3];
     const int4 *sc_meta;
@@ -138,9 +137,10 @@ hipError_t launch_step(int prec, const StepArgs &a, int block, bool obs, hipStre
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
 hipError_t launch_scan(const ScanArgs &a, hipStream_t s);
 hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s);
-hipError_t launch_build(int prec, const BuildArgs &a, int grid, int block, hipStream_t s);
+hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
+hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
 hipError_t occupancy_permute(int prec, int *per_cu);
-hipError_t occupancy_build(int prec, int block, int lds_cap, int *per_cu);
+hipError_t occupancy_build(int prec, int *per_cu);
 hipError_t launch_obs_reduce(const ObsArgs &a, hipStream_t s);
 hipError_t launch_scale_vel(int prec, const ScaleArgs &a, hipStream_t s);
 hipError_t launch_ds_eval(int op, long long n, const float *a, const float *b, float *out, hipStream_t s);

@@ -50,16 +50,22 @@ struct RepDev {
     float sc;     // L / 2^32   (fixed point unit in length units)
     float L_hi, L_lo; // L as double-single
     int items3, items4; // work items of the sort and list-build kernels
-    int bparts;   // list-build work items per row segment (its members split evenly)
-    int blanes;   // lanes building one member's list; 0 = chosen per work item
+    int bmode;    // how the list build works on the replica (BUILD_CELLS, ...)
+    int bparts;   // list-build work items per cell (BUILD_CELLS: 1 or 2)
     // pair constants in fixed-point units u = L / 2^32, per species pair
     // [si*2+sj]: rc^2/u^2, sigma^2/u^2, 24 eps/u; smoothing: rc/u, u/(h sigma),
     // 1/(h sigma); and (skin/2)^2/u^2 for the displacement test
     float rc2s[4], sig2s[4], e24s[4], rcs[4], xsc[4], ihs[4];
     float hs2s;
     float hs2s_early; // (rebuild_early * skin/2)^2 / u^2 (aligned rebuilds)
-    int items4b;      // list-build work items of a bulk build (unsplit segments)
+    float rl2s[4];    // list radius^2 / u^2, the list test's
+    float rlc[4];     // list radius^2 in cell units (cell_units), the matrix-core test's
 };
+
+// Forms of the list build (rebuild.hip), chosen per replica by build_mode().
+enum { BUILD_SINGLE = 0, BUILD_CELLS = 1, BUILD_SPARSE = 2, BUILD_MEMBERS = 3 };
+#define SINGLE_MEMBERS 2     // members per list-build work item of a single-cell replica
+#define CELL_UNITS 64.0f     // cell edge in the units of the list build's candidate records
 
 // Control word of a slot: x = completed steps, y = 1 if velocities are at a
 // full step, z = 1 if attached.  Double-buffered by step parity.

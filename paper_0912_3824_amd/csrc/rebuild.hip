@@ -1,5 +1,7 @@
 // Neighbour-list rebuild kernels (cell count, scan, stable sort, list build)
 // and their launchers.
+#include <type_traits>
+
 #include "dev_common.hpp"
 
 // ------------------------------------------------------------ k_count
@@ -192,13 +194,18 @@ __device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, 
         if constexpr (NS == 2) { // the double snapshot, from the folded state
             double zz, ww;
             u4_to_dbl2(mv.snap, zz, ww);
-            a.sc_snap[dst] = dbl2_to_u4(x, y);
-            a.sc_snap[(size_t)a.A.P + dst] = dbl2_to_u4(z, ww);
+            const uint4 w0 = dbl2_to_u4(x, y), w1 = dbl2_to_u4(z, ww);
+            a.sc_snap[dst] = w0;
+            a.sc_snap[(size_t)a.A.P + dst] = w1;
+            if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, w0, w1);
         }
     }
     m.x += ix; m.y += iy; m.z += iz;
     a.sc_meta[dst] = m;
-    if constexpr (NS == 1) a.sc_snap[dst] = mv.snap;
+    if constexpr (NS == 1) {
+        a.sc_snap[dst] = mv.snap;
+        if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.snap, mv.snap);
+    }
 }
 
 template <int P>
@@ -329,355 +336,148 @@ __attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 1))) k
 }
 
 // ------------------------------------------------------------ k_build
-// One workgroup per row segment of cells (cells x0..x1-1 of row (y, z)):
-// the 9 neighbouring rows over x0-1..x1 are staged in LDS, each cell's
-// plane-0 members followed by its plane-1 members, then every member of the
-// segment (of either plane) writes its list in the canonical order: the own
-// cell, then each half-space offset o followed by -o, and within each cell
-// the A members before the B members, in slot order.
-#define BUILD_LDS_CAP 3072 // staged candidates (x 16 B = 48 KB, fixed point)
-#define BUILD_MAX_NX 18    // cells per staged row (width + 2 halo)
-#define BUILD_TAB (9 * BUILD_MAX_NX)
+// One wave per work item; the waves of a block share nothing.  An item is,
+// by the replica's build mode (RepDev::bmode, build_mode() on the host):
+//
+//   BUILD_CELLS    a cell of a replica whose cells hold many members: its
+//                  members, 32 at a time, against the members of the 27
+//                  surrounding cells, tested on the matrix cores
+//                  (build_cell_mfma); where cells hold more than 32 members
+//                  as a rule, an item is every other 32 of them
+//   BUILD_SPARSE   a cell of a replica of few members per cell: one lane per
+//                  candidate, a loop over the members (build_by_candidates)
+//   BUILD_MEMBERS  64 members of a large replica of few members per cell, one
+//                  lane each (build_by_members)
+//   BUILD_SINGLE   SINGLE_MEMBERS members of a single-cell replica, one lane
+//                  per candidate
+//
+// Every form writes the same list: the own cell, then each half-space offset
+// o followed by -o (Sec. 4.1), and within a cell the A members before the B
+// members, in slot order.  The sorted records of the item's members are
+// copied back from scratch, and the old cell starts retired, on the way.
+#define BUILD_WIN 128     // list entries per member buffered in LDS (a multiple of 16)
+#define BUILD_STRIDE 130  // their stride: members of a wave start in different banks
+#define BUILD_SLOTS 96   // chunks of 32 candidates per neighbourhood (BUILD_CELLS)
 
-struct BuildTabs {
-    // staged cell k = row * NX + lx: (LDS start of its members, members of
-    // both planes, global start in plane 0, global start in plane 1)
-    int4 pk[BUILD_TAB];
-    int na[BUILD_TAB]; // members in plane 0
-    int mp[2 * BUILD_MAX_NX + 1]; // member prefix: own-row cells' plane-0 members, then plane-1
-    int ncell, total, fits, NX, own0, nown;
+#define BUILD_BLOCK 256   // threads per block: four waves that share nothing
+
+typedef int v4i_t __attribute__((ext_vector_type(4)));
+
+struct BuildLds { // one per wave
+    uint16_t lst[32][BUILD_STRIDE];
+    int4 tab[BUILD_SLOTS];
 };
 
-// Candidate e of a staged cell: plane-0 member e, else plane-1 member e - na
-// (its global slot), and where it is read from (LDS, or the arena when the
-// neighbourhood did not fit).
-__device__ __forceinline__ int cand_glob(const int4 &c, int na, int e) { return e < na ? c.z + e : c.w + (e - na); }
-template <bool FROM_LDS>
-__device__ __forceinline__ int cand_at(const int4 &c, int na, int e) { return FROM_LDS ? c.x + e : cand_glob(c, na, e); }
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
 
-// Staged cell of the v-th visit (v = 0..26) of a member in staged column
-// lx_m: the own cell, then each half-space offset o followed by -o, where
-// the half space is indices 14..26 of the (dz, dy, dx) enumeration of the 27
-// offsets (odd v: +o, even v: -o).
-__device__ __forceinline__ int visit_cell(int v, int lx_m, bool full, int nd, int NX)
+// Offset of the v-th visit (v = 0..26) of a member: the own cell, then each
+// half-space offset o followed by -o, where the half space is indices 14..26
+// of the (dz, dy, dx) enumeration of the 27 offsets (odd v: +o, even v: -o).
+__device__ __forceinline__ void visit_offset(int v, int &dx, int &dy, int &dz)
 {
-    int dx = 0, dy = 0, dz = 0;
-    if (v > 0) {
-        const int q = 14 + ((v - 1) >> 1);
-        const int sg = (v & 1) ? 1 : -1;
-        dz = sg * (q / 9 - 1);
-        dy = sg * ((q / 3) % 3 - 1);
-        dx = sg * (q % 3 - 1);
-    }
-    int lx = lx_m + dx;
-    if (full) { lx += lx < 0 ? nd : 0; lx -= lx >= nd ? nd : 0; }
-    return ((dz + 1) * 3 + (dy + 1)) * NX + lx;
+    const int q = v > 0 ? 14 + ((v - 1) >> 1) : 13;
+    const int sg = (v & 1) ? 1 : -1;
+    dz = sg * (q / 9 - 1);
+    dy = sg * ((q / 3) % 3 - 1);
+    dx = sg * (q % 3 - 1);
 }
 
-template <int P, bool FROM_LDS>
-__device__ __forceinline__ void build_member(const BuildArgs &a, const RepDev &rp, int i, int lx_m,
-                                             const BuildTabs &T, bool full, const uint4 *cand, int s,
-                                             int nd)
+// Rank of the cell at an offset of at most one from cell (cx, cy, cz).
+__device__ __forceinline__ int offset_rank(int cx, int cy, int cz, int dx, int dy, int dz, const RepDev &rp,
+                                           const int *corder)
 {
-    constexpr int NS = Traits<P>::NS;
-    const KArena &A = a.A;
-    const size_t P_ = (size_t)A.P;
-    const int NX = T.NX;
-    uint4 xi = a.src_x[i];
-    double xd = 0, yd = 0, zd = 0, wd = 0;
-    uint32_t meta;
-    if (NS == 2) {
-        u4_to_dbl2(xi, xd, yd);
-        u4_to_dbl2(a.src_x[P_ + i], zd, wd);
-        meta = meta_of_bits(wd);
-    } else meta = xi.w;
-    const int si = species_of(meta);
-    float rl2s0, rl2s1;
-    double rl2d0 = a.pp.rl2d[si * 2], rl2d1 = a.pp.rl2d[si * 2 + 1];
-    {
-        const double u = (double)rp.sc;
-        rl2s0 = (float)(rl2d0 / (u * u));
-        rl2s1 = (float)(rl2d1 / (u * u));
-    }
-    const int cap = A.cap;
-    // entry k of slot i: int4 row list_entry_row(k), column list_entry_col(k)
-    int *col = A.nbr_w + 4 * list_row_index(i, 0, cap);
-    const size_t row_stride = 4 * LIST_TILE;
-    const int lg = A.lg, lm = (1 << lg) - 1, gm = (4 << lg) - 1;
-    int cnt = 0;
-    // a candidate's snapshot (two words for double snapshots) at staged
-    // index x (a global slot when nothing is staged), then the test
-    struct Cand { uint4 a, b; };
-    auto load = [&](int x) -> Cand {
-        Cand q;
-        if (NS == 2) {
-            q.a = FROM_LDS ? cand[2 * x] : a.src_x[x];
-            q.b = FROM_LDS ? cand[2 * x + 1] : a.src_x[P_ + x];
-        } else {
-            q.a = FROM_LDS ? cand[x] : a.src_x[x];
-            q.b = q.a;
-        }
-        return q;
-    };
-    auto eval = [&](const Cand &q) -> bool {
-        if (NS == 2) {
-            double xj, yj, zj, wj;
-            u4_to_dbl2(q.a, xj, yj);
-            u4_to_dbl2(q.b, zj, wj);
-            double dx = xd - xj, dy = yd - yj, dz = zd - zj;
-            dx -= rp.L * rint(dx * rp.invL);
-            dy -= rp.L * rint(dy * rp.invL);
-            dz -= rp.L * rint(dz * rp.invL);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            return r2 < (species_of(meta_of_bits(wj)) ? rl2d1 : rl2d0);
-        }
-        const uint4 xj = q.a;
-        const float dx = (float)(int)(xi.x - xj.x), dy = (float)(int)(xi.y - xj.y),
-                    dz = (float)(int)(xi.z - xj.z);
-        const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-        return r2 < (((int)xj.w < 0) ? rl2s1 : rl2s0);
-    };
-    // The candidates of staged cell k in order (i itself is skipped).  Each
-    // chunk of up to 64 (32 when staged) candidates is tested four at a
-    // time (independent reads in flight, no stores and no branches in the
-    // test loop: a wave would otherwise run the store path whenever any of
-    // its lanes accepts) into an acceptance mask, whose set bits are then
-    // stored in order.
-    //
-    // Staged candidates are read at fixed offsets from the chunk's start,
-    // past the cell's end too (into the next cell's records or the padding
-    // that follows the staged array): those tests are masked off once per
-    // chunk instead of clamping every read.  The list is written through a
-    // running pointer to entry cnt.
-    int *wp = col; // entry cnt (see list_entry_row): the next lane's row, else
-                   // the next column of the first lane's row, else the next group
-    auto put = [&](int g) {
-        if (cnt < cap) *wp = list_entry(g);
-        ++cnt;
-        wp += (cnt & lm) ? (ptrdiff_t)row_stride : (cnt & gm) ? 1 - (ptrdiff_t)lm * (ptrdiff_t)row_stride
-                                                                : (ptrdiff_t)row_stride - 3;
-    };
-    auto scan_cell = [&](int k) {
-        const int4 c = T.pk[k];
-        const int na = T.na[k], n = c.y;
-        auto at = [&](int e) { return cand_at<FROM_LDS>(c, na, e); };
-        const int self = (unsigned)(i - c.z) < (unsigned)na ? i - c.z
-                       : (unsigned)(i - c.w) < (unsigned)(n - na) ? na + (i - c.w) : -1;
-        if constexpr (FROM_LDS) {
-            const uint4 *cp = cand + NS * c.x; // the cell's staged records
-            for (int base = 0; base < n; base += 32) {
-                unsigned mask = 0;
-                for (int e = 0; e < n - base; e += 4) {
-                    const uint4 *q = cp + NS * (base + e);
-                    const Cand q0 = {q[0], q[NS - 1]}, q1 = {q[NS], q[2 * NS - 1]},
-                               q2 = {q[2 * NS], q[3 * NS - 1]}, q3 = {q[3 * NS], q[4 * NS - 1]};
-                    const unsigned bits = (eval(q0) ? 1u : 0u) | (eval(q1) ? 2u : 0u) | (eval(q2) ? 4u : 0u) |
-                                          (eval(q3) ? 8u : 0u);
-                    mask |= bits << e;
-                    if (e == 28) break; // a full chunk of 32
-                }
-                const int m = n - base;
-                if (m < 32) mask &= (1u << m) - 1u;
-                if ((unsigned)(self - base) < 32u) mask &= ~(1u << (self - base));
-                while (mask) {
-                    const int b = __ffs(mask) - 1;
-                    mask &= mask - 1u;
-                    put(cand_glob(c, na, base + b));
-                }
-            }
-            return;
-        }
-        for (int base = 0; base < n; base += 64) {
-            const int m = min(64, n - base), last = base + m - 1;
-            unsigned long long mask = 0;
-            for (int e = 0; e < m; e += 4) {
-                // past the chunk's end: re-test its last candidate, masked off
-                const Cand q0 = load(at(base + e)), q1 = load(at(min(base + e + 1, last))),
-                           q2 = load(at(min(base + e + 2, last))), q3 = load(at(min(base + e + 3, last)));
-                const bool c0 = eval(q0);
-                const bool c1 = eval(q1) && e + 1 < m;
-                const bool c2 = eval(q2) && e + 2 < m;
-                const bool c3 = eval(q3) && e + 3 < m;
-                const unsigned bits = (unsigned)c0 | ((unsigned)c1 << 1) | ((unsigned)c2 << 2) | ((unsigned)c3 << 3);
-                mask |= (unsigned long long)bits << e;
-            }
-            if (self >= base && self < base + 64) mask &= ~(1ull << (self - base));
-            while (mask) {
-                const int b = __ffsll((long long)mask) - 1;
-                mask &= mask - 1;
-                put(cand_glob(c, na, base + b));
-            }
-        }
-    };
-    // own cell, then each half-space offset o followed by -o (see
-    // visit_cell), as one loop: a single copy of the scan code
-    const int nvis = nd == 1 ? 1 : 27;
-#pragma unroll 1
-    for (int v = 0; v < nvis; ++v) scan_cell(nd == 1 ? 0 : visit_cell(v, lx_m, full, nd, NX));
-    const int last_cell = nd == 1 ? 0 : visit_cell(26, lx_m, full, nd, NX);
-    // Pad the list to a multiple of 4 entries per lane of a particle
-    // (list_entry_row) with a particle that is outside the
-    // list radius at this build: it stays beyond the force cutoff until the
-    // next build (each particle moves at most skin/2), so the force loop
-    // needs no per-entry validity test.  The pad is the first rejected
-    // candidate of the last cell visited (a corner cell), else of any
-    // staged cell.
-    if (cnt & gm) {
-        int pad = -1;
-        for (int k = 0, kk = last_cell; k <= T.ncell && pad < 0; kk = k++) {
-            const int4 c = T.pk[kk];
-            const int na = T.na[kk];
-            for (int e = 0; e < c.y && pad < 0; ++e) {
-                const int g = cand_glob(c, na, e);
-                if (!eval(load(cand_at<FROM_LDS>(c, na, e))) && g != i) pad = g;
-            }
-        }
-        if (pad < 0) atomicOr(a.status + s, 8);
-        for (int k = cnt; k < ((cnt + gm) & ~gm) && k < cap; ++k)
-            col[(size_t)list_entry_row(k, lg) * row_stride + list_entry_col(k, lg)] = list_entry(pad < 0 ? i : pad);
-    }
-    A.nbr_cnt_w[i] = cnt < A.cap ? cnt : A.cap;
-    if (cnt > A.cap) atomicOr(a.status + s, 1);
+    const int nd = rp.nd;
+    int x = cx + dx, y = cy + dy, z = cz + dz;
+    x += x < 0 ? nd : 0; x -= x >= nd ? nd : 0;
+    y += y < 0 ? nd : 0; y -= y >= nd ? nd : 0;
+    z += z < 0 ? nd : 0; z -= z >= nd ? nd : 0;
+    return cell_rank(x + nd * (y + nd * z), rp, corder);
 }
 
-// The same list, built by a group of G lanes (G a power of two <= 64, the
-// group's lanes adjacent in one wave): the member's candidates, concatenated
-// in the canonical cell order, are tested G at a time, one per lane, and the
-// accepted ones are stored at the running count plus their rank among the
-// group's accepted lanes (ballot + popcount), i.e. in exactly the order of
-// the one-lane scan.  Splits one member's dependent candidate chain G ways,
-// which is what bounds the build of small replicas.
-template <int P, bool FROM_LDS>
-__device__ __forceinline__ void build_member_grp(const BuildArgs &a, const RepDev &rp, int i, int lx_m,
-                                                 const BuildTabs &T, bool full, const uint4 *cand, int s,
-                                                 int nd, int G, int gl, unsigned long long gmask)
+// A position as the list test reads it: the snapshot (fixed point), or its
+// two words (double).
+template <int P> struct Snap { uint4 a, b; };
+template <int P> __device__ __forceinline__ Snap<P> ld_pos(const BuildArgs &a, int i)
 {
-    constexpr int NS = Traits<P>::NS;
-    const KArena &A = a.A;
-    const size_t P_ = (size_t)A.P;
-    const int NX = T.NX;
-    uint4 xi = a.src_x[i];
-    double xd = 0, yd = 0, zd = 0, wd = 0;
-    uint32_t meta;
-    if (NS == 2) {
-        u4_to_dbl2(xi, xd, yd);
-        u4_to_dbl2(a.src_x[P_ + i], zd, wd);
-        meta = meta_of_bits(wd);
-    } else meta = xi.w;
-    const int si = species_of(meta);
-    float rl2s0, rl2s1;
-    double rl2d0 = a.pp.rl2d[si * 2], rl2d1 = a.pp.rl2d[si * 2 + 1];
+    Snap<P> q;
+    q.a = a.src_x[i];
+    if constexpr (Traits<P>::NS == 2) q.b = a.src_x[(size_t)a.A.P + i];
+    else q.b = q.a;
+    return q;
+}
+template <int P> __device__ __forceinline__ int snap_species(const Snap<P> &q)
+{
+    return Traits<P>::NS == 2 ? (int)(q.b.z >> 31) : (int)(q.a.w >> 31);
+}
+
+// Squared list radii of a member against candidates of species A and B, in
+// the units of the list test.  (Values are loaded before they are selected:
+// a selected address would put the replica record in scratch memory.)
+template <int P> struct ListRadii {
+    typedef typename std::conditional<Traits<P>::NS == 2, double, float>::type T;
+    T a, b;
+    __device__ __forceinline__ ListRadii(const BuildArgs &g, const RepDev &rp, int si)
     {
-        const double u = (double)rp.sc;
-        rl2s0 = (float)(rl2d0 / (u * u));
-        rl2s1 = (float)(rl2d1 / (u * u));
-    }
-    const int cap = A.cap;
-    int *col = A.nbr_w + 4 * list_row_index(i, 0, cap);
-    const size_t row_stride = 4 * LIST_TILE;
-    const int lg = A.lg, gm = (4 << lg) - 1;
-    // test the candidate at staged index x (a global slot when nothing is staged)
-    auto test = [&](int x) -> bool {
-        if (NS == 2) {
-            double xj, yj, zj, wj;
-            if (FROM_LDS) {
-                u4_to_dbl2(cand[2 * x], xj, yj);
-                u4_to_dbl2(cand[2 * x + 1], zj, wj);
-            } else {
-                u4_to_dbl2(a.src_x[x], xj, yj);
-                u4_to_dbl2(a.src_x[P_ + x], zj, wj);
-            }
-            double dx = xd - xj, dy = yd - yj, dz = zd - zj;
-            dx -= rp.L * rint(dx * rp.invL);
-            dy -= rp.L * rint(dy * rp.invL);
-            dz -= rp.L * rint(dz * rp.invL);
-            const double r2 = dx * dx + dy * dy + dz * dz;
-            return r2 < (species_of(meta_of_bits(wj)) ? rl2d1 : rl2d0);
+        T r[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            if constexpr (Traits<P>::NS == 2) r[t] = g.pp.rl2d[t];
+            else r[t] = rp.rl2s[t];
         }
-        const uint4 xj = FROM_LDS ? cand[x] : a.src_x[x];
-        const float dx = (float)(int)(xi.x - xj.x), dy = (float)(int)(xi.y - xj.y),
-                    dz = (float)(int)(xi.z - xj.z);
+        a = si ? r[2] : r[0];
+        b = si ? r[3] : r[1];
+    }
+};
+
+// The list test: is candidate q within the list radius of member x?
+template <int P>
+__device__ __forceinline__ bool in_list(const RepDev &rp, const Snap<P> &x, const ListRadii<P> &rl, const Snap<P> &q)
+{
+    const bool b = snap_species<P>(q) != 0;
+    if constexpr (Traits<P>::NS == 2) {
+        double xi, yi, zi, wi, xj, yj, zj, wj;
+        u4_to_dbl2(x.a, xi, yi);
+        u4_to_dbl2(x.b, zi, wi);
+        u4_to_dbl2(q.a, xj, yj);
+        u4_to_dbl2(q.b, zj, wj);
+        double dx = xi - xj, dy = yi - yj, dz = zi - zj;
+        dx -= rp.L * rint(dx * rp.invL);
+        dy -= rp.L * rint(dy * rp.invL);
+        dz -= rp.L * rint(dz * rp.invL);
+        const double r2 = dx * dx + dy * dy + dz * dz;
+        return r2 < (b ? rl.b : rl.a);
+    } else {
+        const float dx = (float)(int)(x.a.x - q.a.x), dy = (float)(int)(x.a.y - q.a.y),
+                    dz = (float)(int)(x.a.z - q.a.z);
         const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-        return r2 < (((int)xj.w < 0) ? rl2s1 : rl2s0);
-    };
-    // one cell's candidates (in the one-lane build's order), 4G at a time:
-    // lane gl tests e = b + u G + gl (u = 0..3, independent loads in
-    // flight); the ballots are taken in u order, which is ascending e
-    // (the member's own candidate index is excluded by position, its global
-    // slot is formed only for the entries stored, and the store address is
-    // one 32 x 32 -> 64-bit multiply-add)
-    int cnt = 0;
-    const unsigned rs32 = (unsigned)row_stride;
-    auto scan_cell = [&](int k) {
-        const int4 c = T.pk[k];
-        const int na = T.na[k], n = c.y;
-        const int self = (unsigned)(i - c.z) < (unsigned)na ? i - c.z
-                       : (unsigned)(i - c.w) < (unsigned)(n - na) ? na + (i - c.w) : -1;
-        for (int b = 0; b < n; b += 4 * G) {
-            bool acc[4];
-            int ev[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { // past the end: test the last candidate, masked off
-                const int e = b + u * G + gl, ec = min(e, n - 1);
-                ev[u] = e;
-                acc[u] = test(cand_at<FROM_LDS>(c, na, ec)) && e < n && e != self;
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const unsigned long long m = __ballot(acc[u]) & gmask;
-                if (acc[u]) { // rank among the group's accepting lanes below this one
-                    const unsigned k2 = (unsigned)cnt +
-                        __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-                    if (k2 < (unsigned)cap) {
-                        const size_t idx = (size_t)(unsigned)list_entry_row((int)k2, lg) * rs32 +
-                                           (unsigned)list_entry_col((int)k2, lg);
-                        col[idx] = list_entry(cand_glob(c, na, ev[u]));
-                    }
-                }
-                cnt += __popcll(m);
-            }
-        }
-    };
-    // the canonical visiting order (see visit_cell), as one loop
-    const int nvis = nd == 1 ? 1 : 27;
-#pragma unroll 1
-    for (int v = 0; v < nvis; ++v) scan_cell(nd == 1 ? 0 : visit_cell(v, lx_m, full, nd, NX));
-    const int last_cell = nd == 1 ? 0 : visit_cell(26, lx_m, full, nd, NX);
-    // pad to a multiple of 4 entries per lane of a particle, as in the
-    // one-lane build: the first rejected candidate of the last visited
-    // cell, else (rare) of any staged cell
-    if (cnt & gm) {
-        int pad = -1;
-        {
-            const int4 cl = T.pk[last_cell];
-            const int na = T.na[last_cell];
-            for (int b = 0; b < cl.y; b += G) {
-                const int e = b + gl;
-                const int g = cand_glob(cl, na, min(e, cl.y - 1));
-                const bool r = e < cl.y && !test(cand_at<FROM_LDS>(cl, na, min(e, cl.y - 1))) && g != i;
-                const unsigned long long m = __ballot(r) & gmask;
-                if (m) { pad = cand_glob(cl, na, b + (__ffsll(m) - 1) - (__ffsll(gmask) - 1)); break; }
-            }
-        }
-        if (gl == 0) {
-            for (int k = 0; k < T.ncell && pad < 0; ++k) {
-                const int4 c = T.pk[k];
-                const int na = T.na[k];
-                for (int e = 0; e < c.y && pad < 0; ++e) {
-                    const int g = cand_glob(c, na, e);
-                    if (!test(cand_at<FROM_LDS>(c, na, e)) && g != i) pad = g;
-                }
-            }
-            if (pad < 0) atomicOr(a.status + s, 8);
-            for (int k = cnt; k < ((cnt + gm) & ~gm) && k < cap; ++k)
-                col[(size_t)list_entry_row(k, lg) * row_stride + list_entry_col(k, lg)] =
-                    list_entry(pad < 0 ? i : pad);
-        }
+        return r2 < (b ? rl.b : rl.a);
     }
-    if (gl == 0) {
-        A.nbr_cnt_w[i] = cnt < cap ? cnt : cap;
-        if (cnt > cap) atomicOr(a.status + s, 1);
-    }
+}
+
+// Entry k of slot i's list.
+__device__ __forceinline__ void put_entry(const KArena &A, int i, int k, int j)
+{
+    A.nbr_w[4 * list_row_index(i, list_entry_row(k, A.lg), A.cap) + list_entry_col(k, A.lg)] = list_entry(j);
+}
+
+// Entries [k0, list end) up to the next multiple of four per lane: a
+// particle outside the list radius at this build.  It stays beyond the force
+// cutoff until the next build (each particle moves at most skin/2), so the
+// force loop needs no per-entry validity test.
+__device__ __forceinline__ void pad_list(const KArena &A, int i, int cnt, int k0, int pad)
+{
+    const int gm = (4 << A.lg) - 1;
+    for (int k = max(cnt, k0); k < ((cnt + gm) & ~gm) && k < A.cap; ++k) put_entry(A, i, k, pad < 0 ? i : pad);
+}
+
+// List length of slot i, and the status bits of a list that overflowed or
+// that needed padding and found none.
+__device__ __forceinline__ void finish_list(const BuildArgs &a, int s, int i, int cnt, bool padded)
+{
+    a.A.nbr_cnt_w[i] = min(cnt, a.A.cap);
+    if (cnt > a.A.cap) atomicOr(a.status + s, 1);
+    if ((cnt & ((4 << a.A.lg) - 1)) && !padded) atomicOr(a.status + s, 8);
 }
 
 template <int P>
@@ -699,178 +499,433 @@ __device__ __forceinline__ void copy_back(const BuildArgs &a, int i)
     }
 }
 
+// The members of an item: slots a0 .. a0 + na - 1, then b0 ...
+struct Members {
+    int a0, na, b0, n;
+    __device__ __forceinline__ int slot(int m) const { return m < na ? a0 + m : b0 + (m - na); }
+};
+
+// One lane per candidate.  tab holds nr ranges of candidates in canonical
+// order: (candidates before the range, first slot in plane 0, first slot in
+// plane 1 less the range's plane-0 members, plane-0 members); tot candidates
+// in all.  Members [m0, m1) are taken 64 at a time, each chunk of 64
+// candidates tested against them in turn; a ballot keeps the order.
 template <int P>
-__global__ void __launch_bounds__(1024) k_build(const BuildArgs a)
+__device__ __forceinline__ void build_by_candidates(const BuildArgs &a, const RepDev &rp, int s, const int4 *tab, int nr,
+                                                    int tot, const Members &mem, int m0, int m1)
 {
-    constexpr int NS = Traits<P>::NS;
-    __shared__ BuildTabs T;
-    extern __shared__ uint4 cand[];
-    const int B = blockDim.x, t = threadIdx.x;
-    // a bulk build (many replicas rebuilding together) gives each member of a
-    // multi-cell replica one lane and each row segment one work item
-    const bool bulk = a.bulk > 0 && a.force_slot == -1 && a.rlist[0] >= a.bulk;
-    for_items(a.rlist, a.items_pref, a.rep, a.max_slots, a.force_slot, a.ctl, bulk ? 5 : 4,
-              remap_block(blockIdx.x, gridDim.x, a.xcd), gridDim.x, [&](int s, int item) {
-        const RepDev rp = a.rep[s];
-        const int bparts = bulk ? 1 : rp.bparts;
-        const int nd = rp.nd, planes = rp.planes, nc = nd * nd * nd;
-        const int *cs = a.cs_new + rp.coff;
-        int NX = 1, part = 0;
-        bool full = true;
-        if (nd == 1) {
-            if (t == 0) {
-                const int na = cs[1] - cs[0];
-                T.pk[0] = make_int4(0, rp.n, cs[0], planes > 1 ? cs[1] : cs[0] + na);
-                T.na[0] = na;
-                T.ncell = 1;
-                T.NX = 1;
-                T.own0 = 0;
-                T.nown = 1;
-                T.total = rp.n;
-                T.fits = rp.n <= a.lds_cap;
-                if (item == 0 && a.from_scratch)
-                    for (int k = 0; k <= planes; ++k) a.cs[rp.coff + k] = cs[k];
-            }
-        } else {
-            const int W = a.width;
-            full = nd <= W + 2;
-            const int nseg = full ? 1 : (nd + W - 1) / W;
-            part = item % bparts;
-            const int segitem = item / bparts;
-            const int seg = segitem % nseg, row = segitem / nseg;
-            const int cy = row % nd, cz = row / nd;
-            const int x0 = full ? 0 : (seg * nd) / nseg; // balanced segments
-            const int x1 = full ? nd : ((seg + 1) * nd) / nseg;
-            NX = full ? nd : x1 - x0 + 2;
-            const int rowbase = nd * (cy + nd * cz);
-            if (a.from_scratch && part == 0) { // retire the old cell starts of this segment
-                for (int k = x0 + t; k < x1; k += B) {
-                    const int rk = cell_rank(rowbase + k, rp, a.corder);
-                    for (int pl = 0; pl < planes; ++pl) a.cs[rp.coff + pl * nc + rk] = cs[pl * nc + rk];
+    const KArena &A = a.A;
+    const int lane = __lane_id();
+    for (int g0 = m0; g0 < m1; g0 += 64) {
+        const int gn = min(64, m1 - g0);
+        const int mine = mem.slot(g0 + min(lane, gn - 1));
+        const Snap<P> xm = ld_pos<P>(a, mine);
+        int cnt = 0, pad = -1; // of this lane's member
+        int r = 0;
+        for (int b = 0; b < tot; b += 64) {
+            const bool valid = b + lane < tot;
+            const int e = min(b + lane, tot - 1);
+            while (r + 1 < nr && tab[r + 1].x <= e) ++r;
+            const int4 t = tab[r];
+            const int x = e - t.x, j = (x < t.w ? t.y : t.z) + x;
+            const Snap<P> q = ld_pos<P>(a, j);
+            for (int m = 0; m < gn; ++m) {
+                Snap<P> xi;
+                xi.a.x = __builtin_amdgcn_readlane(xm.a.x, m);
+                xi.a.y = __builtin_amdgcn_readlane(xm.a.y, m);
+                xi.a.z = __builtin_amdgcn_readlane(xm.a.z, m);
+                xi.a.w = __builtin_amdgcn_readlane(xm.a.w, m);
+                if constexpr (Traits<P>::NS == 2) {
+                    xi.b.x = __builtin_amdgcn_readlane(xm.b.x, m);
+                    xi.b.y = __builtin_amdgcn_readlane(xm.b.y, m);
+                    xi.b.z = __builtin_amdgcn_readlane(xm.b.z, m);
+                    xi.b.w = __builtin_amdgcn_readlane(xm.b.w, m);
+                } else xi.b = xi.a;
+                const int i = __builtin_amdgcn_readlane(mine, m);
+                const int base = __builtin_amdgcn_readlane(cnt, m);
+                const bool other = valid && j != i;
+                const bool acc = in_list<P>(rp, xi, ListRadii<P>(a, rp, snap_species<P>(xi)), q) && other;
+                const unsigned long long hit = __ballot(acc), miss = __ballot(other && !acc);
+                if (acc) {
+                    const int k = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(hit >> 32),
+                                                                        __builtin_amdgcn_mbcnt_lo((unsigned)hit, 0u));
+                    if (k < A.cap) put_entry(A, i, k, j);
                 }
-                if (t == 0 && rowbase + x1 == nc) a.cs[rp.coff + planes * nc] = cs[planes * nc];
-            }
-            const int gs = full ? 0 : (x0 - 1 + nd) % nd; // first staged x
-            for (int k = t; k < 9 * NX; k += B) {
-                const int rw = k / NX, lx = k - rw * NX;
-                const int dz = rw / 3 - 1, dy = rw % 3 - 1;
-                int gx = gs + lx;
-                gx -= gx >= nd ? nd : 0;
-                int gy = cy + dy, gz = cz + dz;
-                gy += gy < 0 ? nd : 0; gy -= gy >= nd ? nd : 0;
-                gz += gz < 0 ? nd : 0; gz -= gz >= nd ? nd : 0;
-                const int rk = cell_rank(gx + nd * (gy + nd * gz), rp, a.corder);
-                const int ga = cs[rk], na = cs[rk + 1] - ga;
-                const int gb = planes > 1 ? cs[nc + rk] : ga + na;
-                const int nb = planes > 1 ? cs[nc + rk + 1] - gb : 0;
-                T.pk[k] = make_int4(0, na + nb, ga, gb);
-                T.na[k] = na;
-            }
-            if (t == 0) {
-                T.NX = NX;
-                T.ncell = 9 * NX;
-                T.own0 = 4 * NX + (full ? 0 : 1); // own row (dz = dy = 0), segment cells
-                T.nown = full ? NX : NX - 2;
-            }
-            __syncthreads();
-            if (t < 64) { // exclusive scan of the staged cell sizes (one wave)
-                const int ncells = 9 * NX;
-                int carry = 0;
-                for (int b = 0; b < ncells; b += 64) {
-                    const int k = b + t;
-                    const int v = k < ncells ? T.pk[k].y : 0;
-                    int incl = v;
-#pragma unroll
-                    for (int o = 1; o < 64; o <<= 1) {
-                        const int u = __shfl_up(incl, o, 64);
-                        if (t >= o) incl += u;
-                    }
-                    if (k < ncells) T.pk[k].x = carry + incl - v;
-                    carry += __shfl(incl, 63, 64);
+                const int found = miss ? __shfl(j, __ffsll((long long)miss) - 1, 64) : -1;
+                if (lane == m) {
+                    cnt += __popcll(hit);
+                    pad = pad < 0 ? found : pad;
                 }
-                if (t == 0) { T.total = carry; T.fits = carry <= a.lds_cap; }
             }
         }
-        __syncthreads();
-        if (t == 0) { // member prefix over the segment's cells: plane 0 members, then plane 1
-            const int o = T.own0, no = T.nown;
-            int acc = 0;
-            T.mp[0] = 0;
-            for (int j = 0; j < no; ++j) { acc += T.na[o + j]; T.mp[j + 1] = acc; }
-            for (int j = 0; j < no; ++j) { acc += T.pk[o + j].y - T.na[o + j]; T.mp[no + j + 1] = acc; }
+        if (lane < gn) {
+            pad_list(A, mine, cnt, 0, pad);
+            finish_list(a, s, mine, cnt, pad >= 0);
         }
-        const bool fits = T.fits != 0;
-        if (fits) { // stage: element e belongs to the last cell whose LDS start is <= e
-            const int tot = T.total, ncl = T.ncell;
-            for (int e = t; e < tot; e += B) {
-                int lo = 0, hi = ncl;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) >> 1;
-                    if (T.pk[mid].x <= e) lo = mid; else hi = mid;
-                }
-                const int4 c = T.pk[lo];
-                const int g = cand_glob(c, T.na[lo], e - c.x);
-                if (NS == 2) {
-                    cand[2 * e] = a.src_x[g];
-                    cand[2 * e + 1] = a.src_x[(size_t)a.A.P + g];
-                } else cand[e] = a.src_x[g];
-            }
-        }
-        __syncthreads();
-        // this item's share of the segment's members
-        const int no = T.nown, ms = T.mp[2 * no];
-        int m0, m1;
-        if (nd == 1) {
-            m0 = item * a.single_members;
-            m1 = min(m0 + a.single_members, rp.n);
-        } else {
-            m0 = (int)(((long long)part * ms) / bparts);
-            m1 = (int)(((long long)(part + 1) * ms) / bparts);
-        }
-        // member index k -> slot i and the member's own-row staged cell lx
-        auto member = [&](int k, int &i, int &lx) {
-            int lo = 0, hi = 2 * no; // last j with mp[j] <= k
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (T.mp[mid] <= k) lo = mid; else hi = mid;
-            }
-            const int jj = lo < no ? lo : lo - no;
-            const int4 c = T.pk[T.own0 + jj];
-            i = (lo < no ? c.z : c.w) + (k - T.mp[lo]);
-            lx = nd == 1 ? 0 : T.own0 + jj - 4 * NX;
-        };
-        // lanes per member: the replica's (fixed by the launch, or one lane
-        // for large replicas), else the largest power of two that still
-        // gives every member of this work item its own group
-        int G = bulk && nd > 1 ? 1 : rp.blanes;
-        if (G == 0) {
-            G = 1;
-            while (G < 64 && (2 * G) * (m1 - m0) <= B) G *= 2;
-        }
-        if (G == 1) {
-            for (int k = m0 + t; k < m1; k += B) {
-                int i, lx_m;
-                member(k, i, lx_m);
-                if (fits) build_member<P, true>(a, rp, i, lx_m, T, full, cand, s, nd);
-                else build_member<P, false>(a, rp, i, lx_m, T, full, cand, s, nd);
-                copy_back<P>(a, i);
-            }
-        } else {
-            const int lane = t & 63, gl = t & (G - 1);
-            const unsigned long long gmask =
-                G == 64 ? ~0ull : ((1ull << G) - 1ull) << (lane & ~(G - 1));
-            for (int k = m0 + t / G; k < m1; k += B / G) {
-                int i, lx_m;
-                member(k, i, lx_m);
-                if (fits) build_member_grp<P, true>(a, rp, i, lx_m, T, full, cand, s, nd, G, gl, gmask);
-                else build_member_grp<P, false>(a, rp, i, lx_m, T, full, cand, s, nd, G, gl, gmask);
-                if (gl == 0) copy_back<P>(a, i);
-            }
-        }
-        __syncthreads();
-    });
+    }
 }
 
+// One lane per member: each walks the candidates of its own 27 cells.
+template <int P>
+__device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDev &rp, int s, int i, bool live)
+{
+    const KArena &A = a.A;
+    const int nd = rp.nd, nc = nd * nd * nd;
+    const int *cs = a.cs_new + rp.coff;
+    const Snap<P> xi = ld_pos<P>(a, i);
+    const ListRadii<P> rl(a, rp, snap_species<P>(xi));
+    int cell;
+    if constexpr (Traits<P>::NS == 2) {
+        double x, y, z, w;
+        u4_to_dbl2(xi.a, x, y);
+        u4_to_dbl2(xi.b, z, w);
+        cell = dbl_cell(x, y, z, rp.L, rp.invL, nd);
+    } else cell = fixed_cell(xi.a.x, xi.a.y, xi.a.z, nd);
+    const int cx = cell % nd, cy = (cell / nd) % nd, cz = cell / (nd * nd);
+    int cnt = 0, pad = -1;
+#pragma unroll 1
+    for (int v = 0; v < 27; ++v) {
+        int dx, dy, dz;
+        visit_offset(v, dx, dy, dz);
+        const int rk = offset_rank(cx, cy, cz, dx, dy, dz, rp, a.corder);
+        const int gA = cs[rk], nA = cs[rk + 1] - gA;
+        const int gB = rp.planes > 1 ? cs[nc + rk] : 0, nB = rp.planes > 1 ? cs[nc + rk + 1] - gB : 0;
+        for (int e = 0; e < nA + nB; ++e) {
+            const int j = e < nA ? gA + e : gB + (e - nA);
+            if (j == i) continue;
+            if (in_list<P>(rp, xi, rl, ld_pos<P>(a, j))) {
+                if (live && cnt < A.cap) put_entry(A, i, cnt, j);
+                ++cnt;
+            } else pad = j;
+        }
+    }
+    if (live) {
+        pad_list(A, i, cnt, 0, pad);
+        finish_list(a, s, i, cnt, pad >= 0);
+    }
+}
+
+// A cell's members against its 27-cell neighbourhood on the matrix cores.
+//
+// Positions are taken in units of 1/CELL_UNITS of the cell edge from the
+// centre of the particle's own cell (cell_units), so a candidate at w in the
+// cell at offset o is w + d - u away from a member at u, d = CELL_UNITS o,
+// and the list test is
+//   T = |w|^2 - 2 w.u + |u|^2 - r_list^2  +  2 w.d + |d|^2 - 2 d.u < 0.
+// T is a sum of products of a candidate's and a member's numbers, each split
+// into two half-precision words; the products of two low words are left out.
+// The first four terms (15 products) are the same for every offset, the last
+// three (8 products) the same for every member up to -2 d.u: 32 candidates x
+// 32 members are two v_mfma_f32_32x32x16_f16.  Lane 32 h + m gets the 16
+// tests of member m and candidates 16 h .. 16 h + 15 (the candidates are
+// laid over the rows of the product so that a lane's are consecutive), and
+// their acceptance bits are the signs of T, one instruction each.
+//
+// T is off by at most 3.2e-5 of the squared edge: the products left out, the
+// rounding of the low words (w and u are at most half an edge per axis), low
+// words flushed to zero, and 32 roundings of the sum.  Where some |T| is
+// below BUILD_EDGE (6.1e-5 of the squared edge, about 3 % of the products),
+// that candidate is tested again by the list test itself, so the lists are
+// those of the list test, entry for entry.
+//
+// Two chunks of 32 candidates are taken at a time: the lower half of the
+// wave then holds the acceptance bits of the first, the upper half those of
+// the second.  The entries go to LDS as 16-bit codes (chunk, candidate), and
+// from there to the list as whole rows, coalesced over the members.
+//
+// What bounds it is VALU issue: about 86 instructions per product of 1024
+// tests (16 of them for the acceptance bits), 10 per entry of the longest of
+// a wave's lists, 4,900 per cell of 28 members, against 10,500 with a lane
+// per member and 14 per test.  Before and after, whole rebuild group: 1M
+// mixture in double-single 953 -> 564 us, 200,000 particles in FP64 556 ->
+// 171 us, an aligned rebuild of 256 small replicas 461 -> 360 us.
+#define BUILD_EDGE (CELL_UNITS * CELL_UNITS / 16384.0f)
+
+// Per visit: 2 d in half precision as the candidate words multiply it (x y,
+// z x, y z), -2 d and |d|^2.
+struct VisitTab {
+    struct { unsigned xy, zx, yz; float x, y, z, sq; int pad; } v[27];
+};
+constexpr VisitTab make_visit_tab()
+{
+    VisitTab t{};
+    for (int v = 0; v < 27; ++v) {
+        const int q = v > 0 ? 14 + ((v - 1) >> 1) : 13, sg = (v & 1) ? 1 : -1;
+        const int o[3] = {sg * (q % 3 - 1), sg * ((q / 3) % 3 - 1), sg * (q / 9 - 1)};
+        unsigned b[3] = {0, 0, 0};
+        for (int d = 0; d < 3; ++d) b[d] = o[d] == 0 ? 0u : o[d] > 0 ? 0x5800u : 0xD800u; // +-128 = 2 CELL_UNITS
+        t.v[v].xy = b[0] | b[1] << 16;
+        t.v[v].zx = b[2] | b[0] << 16;
+        t.v[v].yz = b[1] | b[2] << 16;
+        t.v[v].x = -2.0f * CELL_UNITS * o[0];
+        t.v[v].y = -2.0f * CELL_UNITS * o[1];
+        t.v[v].z = -2.0f * CELL_UNITS * o[2];
+        t.v[v].sq = CELL_UNITS * CELL_UNITS * (o[0] * o[0] + o[1] * o[1] + o[2] * o[2]);
+    }
+    return t;
+}
+static_assert(CELL_UNITS == 64.0f, "the half-precision words of VisitTab");
+__constant__ const VisitTab visit_tab = make_visit_tab();
+
+template <int P>
+__device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev &rp, int s, BuildLds &W, int ns,
+                                                const Members &mem, int first, int stride)
+{
+    const KArena &A = a.A;
+    const int lane = __lane_id(), col = lane & 31, h = lane >> 5;
+    const int lg = A.lg, lm = (1 << lg) - 1, cap = A.cap;
+    // row `col` of the product holds this candidate of the chunk (rows 8 k +
+    // 4 h + c of column m end in register 4 k + c of lane 32 h + m)
+    const int ci = 16 * ((col >> 2) & 1) + 4 * (col >> 3) + (col & 3);
+    // the upper half of the terms: candidate words (high words, 1, 1, B, B, 0)
+    const unsigned keep1 = h ? 0x0000FFFFu : ~0u, set1 = h ? 0x3C000000u : 0u;
+    const unsigned keep2 = h ? 0u : ~0u, setA = h ? 0x00003C00u : 0u, setB = h ? 0x3C003C00u : 0u;
+    const unsigned setB3 = h ? 0x00003C00u : 0u;
+    auto chunk = [&](int k) { // the same for all lanes
+        const int4 t = W.tab[k];
+        return make_int4(__builtin_amdgcn_readfirstlane(t.x), __builtin_amdgcn_readfirstlane(t.y),
+                         __builtin_amdgcn_readfirstlane(t.z), __builtin_amdgcn_readfirstlane(t.w));
+    };
+    auto load = [&](const int4 &t) {
+        const int e = min(ci, (t.w & 0xFFFF) - 1); // past the end: the last one again, masked off below
+        const unsigned j = (unsigned)((e < t.z ? t.x : t.y) + e);
+        return *(const uint4 *)((const char *)a.cand + (j << 4)); // below 2^28 slots
+    };
+    for (int g0 = first; g0 < mem.n; g0 += stride) {
+        const int m = g0 + col;
+        const bool live = m < mem.n;
+        const int i = mem.slot(min(m, mem.n - 1));
+        const Snap<P> xi = ld_pos<P>(a, i);
+        const int si = snap_species<P>(xi);
+        const ListRadii<P> rl(a, rp, si);
+        float u[3];
+        cell_units<P>(rp, xi.a, xi.b, u);
+        half8 mb; // the members' side of the terms that no offset enters
+        {
+            const float c0 = rp.rlc[0], c1 = rp.rlc[1], c2 = rp.rlc[2], c3 = rp.rlc[3];
+            const float rlA = si ? c2 : c0, rlB = si ? c3 : c1;
+            const float c = __builtin_fmaf(u[0], u[0], __builtin_fmaf(u[1], u[1], u[2] * u[2])) - rlA;
+            const float px = -2.0f * u[0], py = -2.0f * u[1], pz = -2.0f * u[2], d = rlA - rlB;
+            const _Float16 xh = (_Float16)px, yh = (_Float16)py, zh = (_Float16)pz, ch = (_Float16)c, dh = (_Float16)d;
+            const _Float16 xl = (_Float16)(px - (float)xh), yl = (_Float16)(py - (float)yh),
+                           zl = (_Float16)(pz - (float)zh), cl = (_Float16)(c - (float)ch),
+                           dl = (_Float16)(d - (float)dh), one = (_Float16)1.0f, zero = (_Float16)0.0f;
+            mb = h ? half8{xl, yl, zl, ch, cl, dh, dl, zero} : half8{xh, yh, zh, xh, yh, zh, one, one};
+        }
+        // acceptance bits of this lane's 16 candidates of chunk t, whose
+        // record of row `col` is rec
+        auto product = [&](const int4 &t, const uint4 &rec) {
+            const auto &vt = visit_tab.v[t.w >> 16];
+            const bool isb = ci >= t.z;
+            uint4 ra, ob;
+            ra.x = rec.x;
+            ra.y = (rec.y & keep1) | set1;
+            ra.z = (rec.z & keep2) | (isb ? setB : setA);
+            ra.w = (rec.w & keep2) | (isb ? setB3 : 0u);
+            const float g = __builtin_fmaf(vt.x, u[0], __builtin_fmaf(vt.y, u[1], __builtin_fmaf(vt.z, u[2], vt.sq)));
+            const _Float16 gh = (_Float16)g;
+            const unsigned gw = half2_bits((_Float16)(g - (float)gh), gh);
+            ob.x = vt.xy & keep2;
+            ob.y = h ? gw & 0xFFFF0000u : vt.zx;
+            ob.z = h ? gw & 0x0000FFFFu : vt.yz;
+            ob.w = 0;
+            float16v T;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) T[q] = 0.0f;
+            const half8 ca = __builtin_bit_cast(half8, ra);
+            T = __builtin_amdgcn_mfma_f32_32x32x16_f16(ca, __builtin_bit_cast(half8, ob), T, 0, 0, 0);
+            T = __builtin_amdgcn_mfma_f32_32x32x16_f16(ca, mb, T, 0, 0, 0);
+            unsigned hit = 0;
+#pragma unroll
+            for (int q = 15; q >= 0; --q) hit = __builtin_amdgcn_alignbit(hit, __float_as_uint(T[q]), 31);
+            float near = fminf(fabsf(T[0]), fabsf(T[1]));
+#pragma unroll
+            for (int q = 2; q < 16; q += 2) near = fminf(fminf(near, fabsf(T[q])), fabsf(T[q + 1]));
+            if (near < BUILD_EDGE) { // too close to call: the list test itself
+                unsigned again = 0;
+#pragma unroll
+                for (int q = 0; q < 16; ++q) again |= fabsf(T[q]) < BUILD_EDGE ? 1u << q : 0u;
+                for (; again; again &= again - 1) {
+                    const int b = __ffs(again) - 1, e = min(16 * h + b, (t.w & 0xFFFF) - 1);
+                    const bool in = in_list<P>(rp, xi, rl, ld_pos<P>(a, (e < t.z ? t.x : t.y) + e));
+                    hit = (hit & ~(1u << b)) | (in ? 1u << b : 0u);
+                }
+            }
+            return hit;
+        };
+        int cnt = 0, pad = -1;
+        int4 t0 = chunk(0), t1 = chunk(min(1, ns - 1));
+        uint4 r0 = load(t0), r1 = load(t1);
+#pragma unroll 1
+        for (int k = 0; k < ns; k += 2) {
+            const int4 c0 = t0, c1 = t1;
+            const uint4 q0 = r0, q1 = r1;
+            t0 = chunk(min(k + 2, ns - 1));
+            t1 = chunk(min(k + 3, ns - 1));
+            r0 = load(t0);
+            r1 = load(t1);
+            const unsigned h0 = product(c0, q0), h1 = product(c1, q1);
+            // this lane's chunk: the first of the two for the lower half
+            const auto sw = __builtin_amdgcn_permlane32_swap(h0, h1, false, false);
+            unsigned hit = sw[0] | (sw[1] << 16);
+            const int left0 = c0.w & 0xFFFF, left1 = k + 1 < ns ? c1.w & 0xFFFF : 0;
+            const unsigned v0 = left0 >= 32 ? ~0u : (1u << left0) - 1u, v1 = left1 >= 32 ? ~0u : (1u << left1) - 1u;
+            unsigned valid = live ? (h ? v1 : v0) : 0u;
+            const int kk = k + h;
+            if ((c0.w >> 16) == 0) { // the own cell's chunks come first: not the member itself
+                const int self = m - 32 * kk;
+                if ((unsigned)self < 32u && (c1.w >> 16 == 0 || h == 0)) valid &= ~(1u << self);
+            }
+            hit &= valid;
+            const unsigned miss = valid & ~hit;
+            const int code = kk << 5;
+            if (miss) pad = code | (__ffs(miss) - 1);
+            const int found = __popc(hit);
+            const auto both = __builtin_amdgcn_permlane32_swap(found, found, false, false);
+            int at = cnt + (h ? (int)both[0] : 0);
+            cnt += (int)both[0] + (int)both[1];
+            if (!__any(cnt > BUILD_WIN)) {
+                uint16_t *wp = &W.lst[col][at];
+                while (hit) {
+                    const int b = __ffs(hit) - 1;
+                    hit &= hit - 1;
+                    *wp++ = (uint16_t)(code | b);
+                }
+            } else {
+                for (; hit; ++at) { // a list beyond the buffer: its tail goes to memory at once
+                    const int b = __ffs(hit) - 1;
+                    hit &= hit - 1;
+                    if (at < BUILD_WIN) W.lst[col][at] = (uint16_t)(code | b);
+                    else if (at < cap) put_entry(A, i, at, (h ? (b < c1.z ? c1.x : c1.y) : (b < c0.z ? c0.x : c0.y)) + b);
+                }
+            }
+        }
+        // a rejected candidate of either half pads the list
+        const auto pads = __builtin_amdgcn_permlane32_swap(pad, pad, false, false);
+        pad = (int)pads[0] >= 0 ? (int)pads[0] : (int)pads[1];
+        auto slot_of_code = [&](int code) {
+            const int4 t = W.tab[code >> 5];
+            const int e = code & 31;
+            return (e < t.z ? t.x : t.y) + e;
+        };
+        const int used = min(cnt, cap), gm = (4 << lg) - 1;
+        const int buffered = min(used, BUILD_WIN), filled = min((used + gm) & ~gm, BUILD_WIN);
+        if (h == 0)
+            for (int k = buffered; k < filled; ++k) W.lst[col][k] = (uint16_t)max(pad, 0);
+        wave_sync();
+        if (live) {
+            const int rows = filled >> 2;
+            v4i_t *dst = (v4i_t *)A.nbr_w + list_row_index(i, 0, cap);
+            for (int q = h; q < rows; q += 2) { // the two halves take alternate rows
+                const uint16_t *lp = &W.lst[col][((q >> lg) << (lg + 2)) | (q & lm)];
+                v4i_t row;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) row[c] = list_entry(slot_of_code(lp[c << lg]));
+                dst[(size_t)q * LIST_TILE] = row;
+            }
+            if (pad < 0) // nothing to pad with: the list is not stepped on (the replica stops)
+                for (int k = buffered; k < filled; ++k)
+                    if ((list_entry_row(k, lg) & 1) == h) put_entry(A, i, k, i);
+            if (h == 0) {
+                if (used > BUILD_WIN) pad_list(A, i, used, BUILD_WIN, pad >= 0 ? slot_of_code(pad) : -1);
+                finish_list(a, s, i, cnt, pad >= 0);
+            }
+        }
+        wave_sync();
+    }
+}
+
+template <int P>
+__device__ __forceinline__ void build_item(const BuildArgs &a, BuildLds &W, int s, int item)
+{
+    const RepDev rp = a.rep[s];
+    const int lane = __lane_id();
+    const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes, items = rp.items4;
+    const int *cs = a.cs_new + rp.coff;
+    if (a.from_scratch) { // retire this item's share of the old cell starts
+        const long long all = (long long)planes * nc + 1;
+        const int k1 = (int)((item + 1) * all / items);
+        for (int k = (int)(item * all / items) + lane; k < k1; k += 64) a.cs[rp.coff + k] = cs[k];
+    }
+    if (rp.bmode == BUILD_MEMBERS) {
+        const int m = item * 64 + lane;
+        const int i = rp.off + min(m, rp.n - 1);
+        build_by_members<P>(a, rp, s, i, m < rp.n);
+        if (m < rp.n) copy_back<P>(a, i);
+        return;
+    }
+    if (rp.bmode == BUILD_SINGLE) { // the replica's slots are one range in canonical order
+        const Members mem = {rp.off, rp.n, 0, rp.n};
+        const int m0 = item * SINGLE_MEMBERS, m1 = min(m0 + SINGLE_MEMBERS, rp.n);
+        if (lane == 0) W.tab[0] = make_int4(0, rp.off, 0, rp.n);
+        wave_sync();
+        build_by_candidates<P>(a, rp, s, W.tab, 1, rp.n, mem, m0, m1);
+        if (m0 + lane < m1) copy_back<P>(a, rp.off + m0 + lane);
+        wave_sync();
+        return;
+    }
+    const int parts = rp.bparts, cell = parts == 2 ? item >> 1 : item, part = parts == 2 ? item & 1 : 0;
+    // lane v holds the cell of visit v: its starts and members in both planes
+    int gA = 0, nA = 0, gB = 0, nB = 0;
+    if (lane < 27) {
+        int dx, dy, dz;
+        visit_offset(lane, dx, dy, dz);
+        const int rk = offset_rank(cell % nd, (cell / nd) % nd, cell / (nd * nd), dx, dy, dz, rp, a.corder);
+        gA = cs[rk];
+        nA = cs[rk + 1] - gA;
+        if (planes > 1) {
+            gB = cs[nc + rk];
+            nB = cs[nc + rk + 1] - gB;
+        }
+    }
+    const int n = nA + nB;
+    const Members mem = {__builtin_amdgcn_readlane(gA, 0), __builtin_amdgcn_readlane(nA, 0),
+                         __builtin_amdgcn_readlane(gB, 0), __builtin_amdgcn_readlane(n, 0)};
+    if (mem.n <= 32 * part) return;
+    const int chunks = (n + 31) >> 5;
+    int upto = n, chunks_upto = chunks; // inclusive sums over the visits
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int x = __shfl_up(upto, o, 64), y = __shfl_up(chunks_upto, o, 64);
+        if (lane >= o) { upto += x; chunks_upto += y; }
+    }
+    const int tot = __builtin_amdgcn_readlane(upto, 26), ns = __builtin_amdgcn_readlane(chunks_upto, 26);
+    if (rp.bmode == BUILD_CELLS && ns <= BUILD_SLOTS) {
+        for (int c = 0, k = chunks_upto - chunks; c < chunks; ++c, ++k)
+            W.tab[k] = make_int4(gA + 32 * c, gB - nA + 32 * c, nA - 32 * c, (n - 32 * c) | (lane << 16));
+        wave_sync();
+        build_cell_mfma<P>(a, rp, s, W, ns, mem, 32 * part, 32 * parts);
+    } else if (part == 0) { // few members per cell (or a neighbourhood beyond the chunk table)
+        if (lane < 27) W.tab[lane] = make_int4(upto - n, gA, gB - nA, nA);
+        wave_sync();
+        build_by_candidates<P>(a, rp, s, W.tab, 27, tot, mem, 0, mem.n);
+        wave_sync();
+    }
+    if (part == 0)
+        for (int m = lane; m < mem.n; m += 64) copy_back<P>(a, mem.slot(m));
+}
+
+template <int P>
+__global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
+{
+    __shared__ BuildLds lds[BUILD_BLOCK / 64];
+    const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for_items(a.rlist, a.items_pref, a.rep, a.max_slots, a.force_slot, a.ctl, 4,
+              remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
+              [&](int s, int item) { build_item<P>(a, lds[wv], s, item); });
+}
+
+// Candidate records of a slot's particles (k_permute writes those of a
+// rebuild), for the first list of an attached replica.
+template <int P>
+__global__ void __launch_bounds__(256) k_cand(const BuildArgs a, uint4 *cand, int slot)
+{
+    const RepDev &rp = a.rep[slot];
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= rp.n) return;
+    const Snap<P> q = ld_pos<P>(a, rp.off + k);
+    cand[rp.off + k] = cand_record<P>(rp, q.a, q.b);
+}
 // ------------------------------------------------------------ launchers
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
 {
@@ -915,16 +970,8 @@ hipError_t occupancy_permute(int prec, int *per_cu)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, 256, 0);
 }
 
-// Staged records plus four of padding: the one-lane scan reads up to three
-// records past a cell's end (masked off), also past the last staged cell.
-static size_t build_lds_bytes(int prec, int lds_cap)
+hipError_t occupancy_build(int prec, int *per_cu)
 {
-    return (size_t)(lds_cap + 4) * 16 * (prec == PREC_FP64 ? 2 : 1);
-}
-
-hipError_t occupancy_build(int prec, int block, int lds_cap, int *per_cu)
-{
-    const size_t lds = build_lds_bytes(prec, lds_cap);
     const void *f;
     switch (prec) {
     case PREC_FP32: f = (const void *)k_build<PREC_FP32>; break;
@@ -932,17 +979,24 @@ hipError_t occupancy_build(int prec, int block, int lds_cap, int *per_cu)
     case PREC_MIX: f = (const void *)k_build<PREC_MIX>; break;
     default: f = (const void *)k_build<PREC_FP64>; break;
     }
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, block, lds);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, BUILD_BLOCK, 0);
 }
 
-hipError_t launch_build(int prec, const BuildArgs &a, int grid, int block, hipStream_t s)
+hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s)
 {
-    const size_t lds = build_lds_bytes(prec, a.lds_cap);
     switch (prec) {
-    case PREC_FP32: hipLaunchKernelGGL((k_build<PREC_FP32>), dim3(grid), dim3(block), lds, s, a); break;
-    case PREC_DS: hipLaunchKernelGGL((k_build<PREC_DS>), dim3(grid), dim3(block), lds, s, a); break;
-    case PREC_MIX: hipLaunchKernelGGL((k_build<PREC_MIX>), dim3(grid), dim3(block), lds, s, a); break;
-    default: hipLaunchKernelGGL((k_build<PREC_FP64>), dim3(grid), dim3(block), lds, s, a); break;
+    case PREC_FP32: hipLaunchKernelGGL((k_build<PREC_FP32>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
+    case PREC_DS: hipLaunchKernelGGL((k_build<PREC_DS>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
+    case PREC_MIX: hipLaunchKernelGGL((k_build<PREC_MIX>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_build<PREC_FP64>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
     }
+    LAUNCH_CHECK();
+}
+
+hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s)
+{
+    const int grid = (n + 255) / 256;
+    if (prec == PREC_FP64) hipLaunchKernelGGL((k_cand<PREC_FP64>), dim3(grid), dim3(256), 0, s, a, cand, slot);
+    else hipLaunchKernelGGL((k_cand<PREC_FP32>), dim3(grid), dim3(256), 0, s, a, cand, slot);
     LAUNCH_CHECK();
 }

@@ -1,9 +1,8 @@
 """Autotuner of libmdx launch shapes.
 
-The knobs (md_launch: block size of the fused step kernel, cells per LDS row
-segment, block size, lanes per member and segment split of the list build,
-the rebuilding-replica count from which a build takes the bulk shape, steps
-per captured hipGraph, XCD-aware tile mapping) change no result bit: lists are in a canonical order and
+The knobs (md_launch: block size of the fused step kernel, steps per captured
+hipGraph, XCD-aware tile mapping; the list build's own fields have no effect)
+change no result bit: lists are in a canonical order and
 every particle sums its own list sequentially.  The tuner therefore times
 candidate shapes on the live pool, from a saved checkpoint so that every
 candidate advances the same trajectory, and keeps the fastest.  Results are
@@ -22,16 +21,12 @@ CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "tune_cache.jso
 
 SPACE = {
     "step_block": [256, 512, 1024],
-    "build_width": [4, 8, 10],
-    "build_block": [256, 320, 512],
-    "build_lanes": [0, 16],
     "graph_steps": [32],
     "xcd_remap": [0, 1],
-    "build_split": [0, 4],
 }
 
-# Pools with aligned rebuilds also try the bulk build (one lane per member
-# and unsplit row segments in the steps where many replicas rebuild).
+# A field tried for pools with aligned rebuilds only (without effect on the
+# present list build; kept for callers that read the space).
 ALIGNED_SPACE = {"build_bulk": [0, 32]}
 
 
@@ -51,8 +46,8 @@ def key_of(pool) -> str:
 
 
 def space_for(pool) -> Dict[str, List[int]]:
-    """The shapes tried for a pool: SPACE, and the bulk-build threshold too
-    when the pool has aligned rebuilds."""
+    """The shapes tried for a pool: SPACE, and ALIGNED_SPACE too when the pool
+    has aligned rebuilds."""
     aligned = int(getattr(pool.cfg, "rebuild_every", 0) or 0) > 0
     return dict(SPACE, **ALIGNED_SPACE) if aligned else dict(SPACE)
 
