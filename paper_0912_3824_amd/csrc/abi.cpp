@@ -96,11 +96,11 @@ struct md_system {
     int *nbr = nullptr, *nbr_cnt = nullptr;
     double *obs = nullptr, *obs_out = nullptr;
     int *count[2]{}, *cs = nullptr, *cs_new = nullptr;
-    int *corder = nullptr; // per-replica cell rank tables (cell arena offsets)
+    int *corder = nullptr, *corder_inv = nullptr; // per-replica cell rank tables and their inverses (cell arena offsets)
     RepDev *rep = nullptr;
     Ctl *ctl[2]{};
     int *target = nullptr, *need[2]{}, *rlist[2]{}, *status = nullptr, *nreb = nullptr;
-    int *items3 = nullptr, *items4 = nullptr, *chunks = nullptr;
+    int *chunks = nullptr;
     double *partial = nullptr;
     // host state
     PairDev pp{};
@@ -247,6 +247,7 @@ static int64_t carve(md_system *s, const Layout &L, char *base)
     d->cs = c.take<int>(L.cells);
     d->cs_new = c.take<int>(L.cells);
     d->corder = c.take<int>(L.cells);
+    d->corder_inv = c.take<int>(L.cells);
     d->rep = c.take<RepDev>(L.slots);
     d->ctl[0] = c.take<Ctl>(L.slots);
     d->ctl[1] = c.take<Ctl>(L.slots);
@@ -257,8 +258,6 @@ static int64_t carve(md_system *s, const Layout &L, char *base)
     d->rlist[1] = c.take<int>(L.slots + 1);
     d->status = c.take<int>(L.slots);
     d->nreb = c.take<int>(L.slots);
-    d->items3 = c.take<int>(L.slots + 1);
-    d->items4 = c.take<int>(L.slots + 1);
     d->chunks = c.take<int>(L.slots + 1);
     d->partial = c.take<double>((L.P / 4096 + L.slots + 1) * 8);
     d->obs_out = c.take<double>(L.slots * 8);
@@ -372,25 +371,16 @@ static int items4_of(int n, int nd)
     }
 }
 
+// Chunk prefix of the observables' reduction (4096 particles per chunk).
 static md_status upload_items(md_system *s)
 {
-    int S = (int)s->lay.slots;
-    std::vector<int> p3(S + 1, 0), p4(S + 1, 0), p5(S + 1, 0);
+    const int S = (int)s->lay.slots;
+    std::vector<int> pre(S + 1, 0);
     for (int k = 0; k < S; ++k) {
         const SlotHost &h = s->slots[k];
-        int a3 = 0, a4 = 0, a5 = 0;
-        if (h.attached) {
-            a3 = h.nd * h.nd * h.nd;
-            a4 = items4_of(h.n, h.nd);
-            a5 = (h.n + 4095) / 4096;
-        }
-        p3[k + 1] = p3[k] + a3;
-        p4[k + 1] = p4[k] + a4;
-        p5[k + 1] = p5[k] + a5;
+        pre[k + 1] = pre[k] + (h.attached ? (h.n + 4095) / 4096 : 0);
     }
-    HIPCHK(s, hipMemcpyAsync(s->chunks, p5.data(), sizeof(int) * (S + 1), hipMemcpyHostToDevice, s->stream));
-    HIPCHK(s, hipMemcpyAsync(s->items3, p3.data(), sizeof(int) * (S + 1), hipMemcpyHostToDevice, s->stream));
-    HIPCHK(s, hipMemcpyAsync(s->items4, p4.data(), sizeof(int) * (S + 1), hipMemcpyHostToDevice, s->stream));
+    HIPCHK(s, hipMemcpyAsync(s->chunks, pre.data(), sizeof(int) * (S + 1), hipMemcpyHostToDevice, s->stream));
     HIPCHK(s, hipStreamSynchronize(s->stream));
     return MD_OK;
 }
@@ -448,56 +438,37 @@ static StepArgs step_args(const md_system *s, int p)
     return a;
 }
 
-// The three rebuild launches that follow a step of parity p (force_slot -1:
-// flagged replicas; -2: all attached; >= 0: that slot).
-static md_status launch_rebuild(md_system *s, int p, int force_slot, bool from_scratch)
+// The two rebuild launches that follow a step of parity p: the replicas on
+// its rebuild list are sorted and their lists built.
+static md_status launch_rebuild(md_system *s, int p)
 {
     const int prec = s->prec;
-    ScanArgs sa;
-    sa.max_slots = (int)s->lay.slots;
-    sa.force_slot = force_slot;
-    sa.rep = s->rep;
-    sa.need = s->need[p];
-    sa.rlist = s->rlist[p];
-    sa.ctl = s->ctl[p ^ 1];
-    sa.count = s->count[p];
-    sa.cs_new = s->cs_new;
-    sa.status = s->status;
-    sa.nreb = s->nreb;
-    HIPCHK(s, launch_scan(sa, s->stream));
-
     PermArgs pa;
     memset(&pa, 0, sizeof pa);
     pa.A = arena_of(s);
-    pa.max_slots = (int)s->lay.slots;
-    pa.force_slot = force_slot;
-    pa.items_pref = s->items3;
     pa.rep = s->rep;
-    pa.need = s->need[p];
     pa.rlist = s->rlist[p];
-    pa.ctl = s->ctl[p ^ 1];
+    pa.count = s->count[p];
     pa.cs = s->cs;
     pa.cs_new = s->cs_new;
     pa.corder = s->corder;
+    pa.corder_inv = s->corder_inv;
     pa.snap = s->snap[p ^ 1];
     for (int k = 0; k < 3; ++k) pa.sc_st[k] = s->sc_st[k];
     pa.sc_snap = s->sc_snap;
     pa.sc_meta = s->sc_meta;
     pa.cand = s->cand;
     pa.status = s->status;
+    pa.nreb = s->nreb;
     HIPCHK(s, launch_permute(prec, pa, s->grid_perm, s->stream));
 
     BuildArgs ba;
     memset(&ba, 0, sizeof ba);
     ba.A = arena_of(s);
-    ba.max_slots = (int)s->lay.slots;
-    ba.force_slot = force_slot;
-    ba.from_scratch = from_scratch ? 1 : 0;
+    ba.from_scratch = 1;
     ba.xcd = s->launch.xcd_remap;
-    ba.items_pref = s->items4;
     ba.rep = s->rep;
     ba.rlist = s->rlist[p];
-    ba.ctl = s->ctl[p ^ 1];
     ba.cs = s->cs;
     ba.cs_new = s->cs_new;
     ba.corder = s->corder;
@@ -512,20 +483,19 @@ static md_status launch_rebuild(md_system *s, int p, int force_slot, bool from_s
     return MD_OK;
 }
 
-// List build only, from the main arrays (attach / restore).
+// List build only, from the main arrays (attach / restore).  The rebuild list
+// of the parity that the next step clears serves as this one's.
 static md_status launch_build_main(md_system *s, int slot)
 {
+    int *rlist = s->rlist[s->parity ^ 1];
+    HIPCHK(s, launch_enlist(rlist, s->ctl[0], (int)s->lay.slots, slot, s->stream));
     BuildArgs ba;
     memset(&ba, 0, sizeof ba);
     ba.A = arena_of(s);
-    ba.max_slots = (int)s->lay.slots;
-    ba.force_slot = slot;
     ba.from_scratch = 0;
     ba.xcd = s->launch.xcd_remap;
-    ba.items_pref = s->items4;
     ba.rep = s->rep;
-    ba.rlist = s->rlist[0];
-    ba.ctl = s->ctl[0];
+    ba.rlist = rlist;
     ba.cs = s->cs;
     ba.cs_new = s->cs_new;
     ba.corder = s->corder;
@@ -544,7 +514,7 @@ static md_status launch_one_step(md_system *s, int p)
 {
     StepArgs a = step_args(s, p);
     HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, false, s->stream));
-    return launch_rebuild(s, p, -1, true);
+    return launch_rebuild(s, p);
 }
 
 // The launches of `steps` consecutive steps starting at snapshot parity
@@ -837,7 +807,12 @@ static md_status upload_slot(md_system *s, int slot, const SlotHost &h, const Ho
     HIPCHK(s, hipMemcpyAsync(s->cs_new + h.coff, hr.cs.data(), 4 * hr.cs.size(), hipMemcpyHostToDevice, st));
     RepDev r = repdev_of(s, h);
     const std::vector<int> rk = ranks_of(s, h); // kept until the stream synchronises below
-    if (r.curve) HIPCHK(s, hipMemcpyAsync(s->corder + h.coff, rk.data(), 4 * rk.size(), hipMemcpyHostToDevice, st));
+    std::vector<int> inv(r.curve ? rk.size() : 0);
+    if (r.curve) {
+        for (size_t c = 0; c < rk.size(); ++c) inv[rk[c]] = (int)c;
+        HIPCHK(s, hipMemcpyAsync(s->corder + h.coff, rk.data(), 4 * rk.size(), hipMemcpyHostToDevice, st));
+        HIPCHK(s, hipMemcpyAsync(s->corder_inv + h.coff, inv.data(), 4 * inv.size(), hipMemcpyHostToDevice, st));
+    }
     HIPCHK(s, hipMemcpyAsync(s->rep + slot, &r, sizeof r, hipMemcpyHostToDevice, st));
     for (int p = 0; p < 2; ++p) {
         HIPCHK(s, hipMemcpyAsync(s->ctl[p] + slot, &c, sizeof c, hipMemcpyHostToDevice, st));
@@ -1198,15 +1173,15 @@ md_status md_rebuild_neighbours(md_system *s)
     memset(&ca, 0, sizeof ca);
     ca.P = (int)s->lay.P;
     ca.max_slots = (int)s->lay.slots;
-    ca.force_slot = -2;
     ca.snap = s->snap[p];
     ca.rep = s->rep;
     ca.ctl = s->ctl[p];
     ca.count = s->count[kp];
     ca.corder = s->corder;
     HIPCHK(s, launch_count(s->prec, ca, s->stream));
+    HIPCHK(s, launch_enlist(s->rlist[kp], s->ctl[p], (int)s->lay.slots, -1, s->stream));
     // the rebuild kernels of a step of parity kp read snap[kp ^ 1] == snap[p]
-    return launch_rebuild(s, kp, -2, true);
+    return launch_rebuild(s, kp);
 }
 
 md_status md_forces(md_system *s, int32_t slot, double *f_host, double *e_host)
@@ -1452,7 +1427,7 @@ md_status md_profile_steps(md_system *s, int64_t n_steps, double *out)
         chk(hipEventRecord(ev[3 * k], s->stream), "event");
         chk(launch_step(s->prec, a, s->launch.step_block, false, s->stream), "step launch");
         chk(hipEventRecord(ev[3 * k + 1], s->stream), "event");
-        if (st == MD_OK) st = launch_rebuild(s, p, -1, true);
+        if (st == MD_OK) st = launch_rebuild(s, p);
         chk(hipEventRecord(ev[3 * k + 2], s->stream), "event");
         chk(hipMemcpyAsync(hn + (k + 1) * S, s->nreb, 4 * S, hipMemcpyDeviceToHost, s->stream), "copy counters");
         s->parity ^= 1;
@@ -1780,7 +1755,7 @@ md_status md_set_launch(md_system *s, const md_launch *in)
         s->err = why;
         return gs;
     }
-    // refresh per-slot item counts (list-build items depend on the shapes)
+    // refresh the replica records
     for (int k = 0; k < (int)s->lay.slots; ++k)
         if (s->slots[k].attached) {
             RepDev r = repdev_of(s, s->slots[k]);

@@ -5,7 +5,7 @@
 // Overview of the kernels (step.hip, rebuild.hip, aux_kernels.hip):
 //
 // One MD step (Sec. 2.2, velocity Verlet with Verlet lists) is one fused
-// launch of k_step plus three rebuild kernels that exit at once unless the
+// launch of k_step plus two rebuild kernels that exit at once unless the
 // replica's maximum displacement since its last list build exceeded skin/2:
 //
 //   k_step<P>    per particle: force over its Verlet list (FP32 pair term,
@@ -17,9 +17,8 @@
 //                The sort key is the cell within the particle's species
 //                plane: a binary mixture is stored as all A particles by
 //                cell, then all B particles by cell.
-//   k_scan       per replica: exclusive scan of the cell counts -> cell starts.
-//   k_permute<P> per cell of a plane (one wave): stable counting-sort
-//                scatter.  Members of a new cell come from the 27
+//   k_permute<P> per cell (one wave): cell starts from the counts, then the
+//                stable counting-sort scatter.  Members of a new cell come from the 27
 //                surrounding old cells of the same plane (a
 //                particle moves less than one cell between builds); a ballot
 //                over them in old slot order gives each its new slot.  The
@@ -72,54 +71,36 @@ __device__ __forceinline__ int find_item_slot(const int *pref, int nslots, int i
     return lo;
 }
 
-__device__ __forceinline__ bool slot_selected(int s, int force_slot, const int *need, const Ctl *ctl)
+// Work-item walk of the rebuild kernels: the items of the slots on the
+// rebuild list, which k_step writes (k_enlist for a rebuild asked for by the
+// host).  items(slot) is a slot's item count, `unit` this worker's index
+// among `nunits` workers; visit(slot, item) is called for each item assigned
+// to it.  Consecutive slots start on different workers so that small replicas
+// spread over the grid.  The slots and their item counts are read 64 at a
+// time, one per lane (a few round trips to memory however many replicas
+// rebuild), then walked from registers; visit is called from one place only,
+// so that its code is emitted once.
+template <class N, class F>
+__device__ __forceinline__ void for_items(const int *rlist, N items, int unit, int nunits, F visit)
 {
-    if (force_slot == -1) return need && need[s] != 0;
-    if (force_slot == -2) return ctl[s].z != 0;
-    return s == force_slot;
-}
-
-// Work-item walk of the rebuild kernels.  A step's rebuild (force_slot -1)
-// visits the items of the slots on the rebuild list written by k_step; a
-// host-forced rebuild visits those of the selected slots (items_pref holds
-// the host's per-slot item counts as a prefix).  `which` names the item
-// count of a listed slot: 3 the sort's, 4 the list build's.  `unit` is this worker's index among `nunits` workers;
-// visit(slot, item) is called for each item assigned to it.  Consecutive
-// slots start on different workers so that small replicas spread over the
-// grid.  The slots and their item counts are read 64 at a time, one per lane
-// (a few round trips to memory however many replicas rebuild), then walked
-// from registers; visit is called from one place only, so that its code is
-// emitted once.
-template <class F>
-__device__ __forceinline__ void for_items(const int *rlist, const int *items_pref, const RepDev *rep,
-                                          int max_slots, int force_slot, const Ctl *ctl, int which,
-                                          int unit, int nunits, F visit)
-{
-    const bool listed = force_slot == -1;
-    const int cnt = listed ? rlist[0] : max_slots;
+    const int cnt = rlist[0];
     const int lane = __lane_id();
     int cum = 0;
     for (int base = 0; base < cnt; base += 64) {
         const int li = base + lane;
         int sl = 0, its = 0;
         if (li < cnt) {
-            if (listed) {
-                sl = rlist[1 + li];
-                its = which == 3 ? rep[sl].items3 : rep[sl].items4;
-            } else {
-                sl = li;
-                if (slot_selected(sl, force_slot, nullptr, ctl)) its = items_pref[sl + 1] - items_pref[sl];
-            }
+            sl = rlist[1 + li];
+            its = items(sl);
         }
         const int m = min(64, cnt - base);
         for (int k = 0; k < m; ++k) {
-            const int items = __builtin_amdgcn_readlane(its, k);
-            if (items == 0) continue;
+            const int n = __builtin_amdgcn_readlane(its, k);
             const int s = __builtin_amdgcn_readlane(sl, k);
             int first = unit - cum % nunits;
             first += first < 0 ? nunits : 0;
-            for (int it = first; it < items; it += nunits) visit(s, it);
-            cum += items;
+            for (int it = first; it < n; it += nunits) visit(s, it);
+            cum += n;
         }
     }
 }

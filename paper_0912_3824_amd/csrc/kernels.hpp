@@ -38,7 +38,7 @@ struct StepArgs {
 };
 
 struct CountArgs {
-    int P, max_slots, force_slot, pad0;
+    int P, max_slots;
     const uint4 *snap;
     const RepDev *rep;
     const Ctl *ctl;
@@ -46,43 +46,27 @@ struct CountArgs {
     const int *corder;
 };
 
-struct ScanArgs {
-    int max_slots, force_slot;
-    const RepDev *rep;
-    const int *need;
-    const int *rlist;
-    const Ctl *ctl;
-    const int *count;
-    int *cs_new;
-    int *status;
-    int *nreb;
-};
-
 struct PermArgs {
     KArena A;
-    int max_slots, force_slot;
-    const int *items_pref;
     const RepDev *rep;
-    const int *need;
     const int *rlist;
-    const Ctl *ctl;
-    const int *cs, *cs_new;
-    const int *corder;
+    const int *count;  // members of each new cell
+    const int *cs;     // old cell starts
+    int *cs_new;
+    const int *corder, *corder_inv;
     const uint4 *snap;
     uint4 *sc_st[3];
     uint4 *sc_snap;
     int4 *sc_meta;
     uint4 *cand; // candidate records of the list build
-    int *status;
+    int *status, *nreb;
 };
 
 struct BuildArgs {
     KArena A;
-    int max_slots, force_slot, from_scratch, xcd;
-    const int *items_pref;
+    int from_scratch, xcd;
     const RepDev *rep;
     const int *rlist;
-    const Ctl *ctl;
     int *cs;
     const int *cs_new;
     const int *corder;
@@ -135,7 +119,7 @@ hipError_t thermo_scratch_init(int dev); // once per device, with that device cu
 double *thermo_scratch(int dev);         // its device address (nullptr before init)
 hipError_t launch_step(int prec, const StepArgs &a, int block, bool obs, hipStream_t s);
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
-hipError_t launch_scan(const ScanArgs &a, hipStream_t s);
+hipError_t launch_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
 hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s);
 hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);

@@ -1,4 +1,4 @@
-// Neighbour-list rebuild kernels (cell count, scan, stable sort, list build)
+// Neighbour-list rebuild kernels (cell count, stable sort, list build)
 // and their launchers.
 #include <type_traits>
 
@@ -23,7 +23,7 @@ __global__ void k_count(const CountArgs a)
     if (meta == NO_SLOT) return;
     int r = slot_of_meta(meta);
     if (r >= a.max_slots) return;
-    if (!slot_selected(r, a.force_slot, nullptr, a.ctl)) return;
+    if (!a.ctl[r].z) return;
     RepDev rp = a.rep[r];
     int cell;
     if (NS == 2) cell = dbl_cell(x, y, z, rp.L, rp.invL, rp.nd);
@@ -31,81 +31,33 @@ __global__ void k_count(const CountArgs a)
     atomicAdd(a.count + rp.coff + sort_key(cell_rank(cell, rp, a.corder), meta, rp.planes, rp.nd), 1);
 }
 
-// ------------------------------------------------------------ k_scan
-// One workgroup (1024 threads) per slot: exclusive scan of the cell counts
-// (every species plane, in order), cell starts written as absolute slots.
-// Tiles of SCAN_CPT x 1024 cells pass through LDS, so that global reads and
-// writes are coalesced while each thread scans SCAN_CPT consecutive cells.
-#define SCAN_CPT 8
-#define SCAN_B 1024
-__global__ void __launch_bounds__(SCAN_B) k_scan(const ScanArgs a)
+// ------------------------------------------------------------ k_enlist
+// Rebuild list of a rebuild or list build asked for by the host: `slot`, or
+// every attached slot (slot < 0).
+__global__ void __launch_bounds__(64) k_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot)
 {
-    int s = blockIdx.x;
-    if (a.force_slot == -1) {
-        if (s >= a.rlist[0]) return;
-        s = a.rlist[1 + s];
-    } else {
-        if (s >= a.max_slots) return;
-        if (!slot_selected(s, a.force_slot, a.need, a.ctl)) return;
+    const int lane = threadIdx.x;
+    int cnt = 0;
+    for (int base = 0; base < max_slots; base += 64) {
+        const int s = base + lane;
+        const bool in = s < max_slots && (slot < 0 ? ctl[s].z != 0 : s == slot);
+        const unsigned long long m = __ballot(in);
+        if (in) rlist[1 + cnt + __popcll(m & ((1ull << lane) - 1ull))] = s;
+        cnt += __popcll(m);
     }
-    const RepDev rp = a.rep[s];
-    const int ncell = rp.planes * rp.nd * rp.nd * rp.nd;
-    const int t = threadIdx.x;
-    const int lane = t & 63, wv = t >> 6, nw = SCAN_B >> 6;
-    const int *cnt = a.count + rp.coff;
-    int *out = a.cs_new + rp.coff;
-    __shared__ int tile[SCAN_CPT * SCAN_B];
-    __shared__ int wsum[SCAN_B / 64];
-    __shared__ int tile_total;
-    int carry = 0;
-    for (int base = 0; base < ncell; base += SCAN_CPT * SCAN_B) {
-#pragma unroll
-        for (int u = 0; u < SCAN_CPT; ++u) {
-            const int c = base + u * SCAN_B + t;
-            tile[u * SCAN_B + t] = c < ncell ? cnt[c] : 0;
-        }
-        __syncthreads();
-        int v[SCAN_CPT];
-        int local = 0;
-#pragma unroll
-        for (int u = 0; u < SCAN_CPT; ++u) {
-            v[u] = tile[SCAN_CPT * t + u];
-            local += v[u];
-        }
-        int incl = local;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int w = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += w;
-        }
-        if (lane == 63) wsum[wv] = incl;
-        __syncthreads();
-        if (t == 0) {
-            int acc = 0;
-            for (int k = 0; k < nw; ++k) { const int w = wsum[k]; wsum[k] = acc; acc += w; }
-            tile_total = acc;
-        }
-        __syncthreads();
-        int run = rp.off + carry + wsum[wv] + incl - local;
-#pragma unroll
-        for (int u = 0; u < SCAN_CPT; ++u) {
-            tile[SCAN_CPT * t + u] = run;
-            run += v[u];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < SCAN_CPT; ++u) {
-            const int c = base + u * SCAN_B + t;
-            if (c < ncell) out[c] = tile[u * SCAN_B + t];
-        }
-        carry += tile_total;
-        __syncthreads();
-    }
-    if (t == 0) {
-        out[ncell] = rp.off + carry;
-        if (carry != rp.n) atomicOr(a.status + s, 4 | 2);
-        a.nreb[s] += 1;
-    }
+    if (lane == 0) rlist[0] = cnt;
+}
+
+// Rank of the cell at an offset of at most one from cell (cx, cy, cz).
+__device__ __forceinline__ int offset_rank(int cx, int cy, int cz, int dx, int dy, int dz, const RepDev &rp,
+                                           const int *corder)
+{
+    const int nd = rp.nd;
+    int x = cx + dx, y = cy + dy, z = cz + dz;
+    x += x < 0 ? nd : 0; x -= x >= nd ? nd : 0;
+    y += y < 0 ? nd : 0; y -= y >= nd ? nd : 0;
+    z += z < 0 ? nd : 0; z -= z >= nd ? nd : 0;
+    return cell_rank(x + nd * (y + nd * z), rp, corder);
 }
 
 // ------------------------------------------------------------ k_permute
@@ -120,6 +72,7 @@ __global__ void __launch_bounds__(SCAN_B) k_scan(const ScanArgs a)
 // a load issued after a store also waits for that store).
 #define PERM_U 8                     // candidate tests per lane in flight
 #define PERM_LIST (64 + 64 * PERM_U) // listed members per wave before a move phase
+#define PERM_BLOCK 256
 template <int P> struct Moved {
     uint4 st[Traits<P>::NW];
     int4 meta;
@@ -222,116 +175,201 @@ __device__ __forceinline__ bool in_cell(const PermArgs &a, const RepDev &rp, int
     return fixed_cell(X.x, X.y, X.z, rp.nd) == c;
 }
 
+struct PermLds { // one per wave
+    int pref[55], pst[54], srt[27];
+    int2 lst[PERM_LIST]; // (old slot, scratch slot) of the members found
+};
+
+// One new cell c (rank rc): plane-0 members go to [dst0, dst0 + want0),
+// plane-1 members to [dst1, dst1 + want1).
+template <int P>
+__device__ __forceinline__ void permute_cell(const PermArgs &a, const RepDev &rp, PermLds &W, int s, int c, int dst0,
+                                             int want0, int dst1, int want1)
+{
+    const int lane = __lane_id();
+    const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes;
+    const int *cs = a.cs + rp.coff;
+    // the old cells that can hold members of new cell c, in ascending
+    // rank: plane 0's, then plane 1's (so that the flattened candidates
+    // are in old slot order); one range per lane
+    const int nold = nd == 1 ? 1 : 27, nr = planes * nold;
+    if (nd > 1) { // rank the 27 neighbour cells (distinct for nd >= 3)
+        int orank = 0x7fffffff;
+        if (lane < 27) {
+            const int cx = c % nd, cy = (c / nd) % nd, cz = c / (nd * nd);
+            orank = offset_rank(cx, cy, cz, lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1, rp, a.corder);
+        }
+        int pos = 0;
+        for (int l = 0; l < 27; ++l) pos += __shfl(orank, l, 64) < orank;
+        if (lane < 27) W.srt[pos] = orank;
+        wave_sync();
+    }
+    int len = 0, st0 = 0;
+    if (lane < nr) {
+        const int pl = lane >= nold, kk = lane - pl * nold;
+        const int oc = pl * nc + (nd > 1 ? W.srt[kk] : 0);
+        st0 = cs[oc];
+        len = cs[oc + 1] - st0;
+    }
+    int incl = len;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += u;
+    }
+    if (lane < nr) { W.pst[lane] = st0; W.pref[lane + 1] = incl; }
+    if (lane == 0) W.pref[0] = 0;
+    wave_sync();
+    const int tot = W.pref[nr], tot0 = W.pref[nold];
+    // move phase: every listed member, loaded before any is stored
+    auto move_listed = [&](int n) {
+        wave_sync();
+        for (int k = lane; k < n; k += 64) {
+            const int2 e = W.lst[k];
+            Moved<P> mv;
+            move_load<P>(a, e.x, mv);
+            move_store<P>(a, rp, mv, e.y);
+        }
+        wave_sync();
+    };
+    int run0 = 0, run1 = 0, nl = 0;
+    int r = 0; // range of the lane's current candidate (only moves forward)
+    const unsigned long long below = (1ull << lane) - 1ull;
+    for (int b = 0; b < tot; b += 64 * PERM_U) {
+        int q[PERM_U];
+        bool m[PERM_U];
+#pragma unroll
+        for (int u = 0; u < PERM_U; ++u) {
+            const int e = b + 64 * u + lane;
+            q[u] = -1;
+            if (e < tot) {
+                while (r + 1 < nr && W.pref[r + 1] <= e) ++r;
+                q[u] = W.pst[r] + (e - W.pref[r]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PERM_U; ++u) m[u] = q[u] >= 0 && (nd == 1 || in_cell<P>(a, rp, q[u], c));
+        // list the members found, in candidate order (at most 64 x
+        // PERM_U, so the list, emptied below once it holds more than
+        // 64, never overflows)
+#pragma unroll
+        for (int u = 0; u < PERM_U; ++u) {
+            const bool p1 = b + 64 * u + lane >= tot0;
+            const unsigned long long bal0 = __ballot(m[u] && !p1), bal1 = __ballot(m[u] && p1);
+            if (m[u]) {
+                const int dst = p1 ? dst1 + run1 + __popcll(bal1 & below) : dst0 + run0 + __popcll(bal0 & below);
+                W.lst[nl + __popcll((bal0 | bal1) & below)] = make_int2(q[u], dst);
+            }
+            run0 += __popcll(bal0);
+            run1 += __popcll(bal1);
+            nl += __popcll(bal0 | bal1);
+        }
+        if (nl > PERM_LIST - 64 * PERM_U) { move_listed(nl); nl = 0; }
+    }
+    move_listed(nl);
+    // every particle counted in this cell must have come from a
+    // neighbouring old cell; a shortfall means a particle jumped further
+    if (lane == 0 && (run0 != want0 || run1 != want1)) atomicOr(a.status + s, 4);
+}
+
+// Sum of count[0 .. n) over the block's threads, this thread's share; 16
+// loads in flight.
+__device__ __forceinline__ int thread_sum(const int *count, int n)
+{
+    int sum = 0;
+    for (int k = threadIdx.x; k < n; k += 16 * PERM_BLOCK) {
+        int v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = k + u * PERM_BLOCK < n ? count[k + u * PERM_BLOCK] : 0;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sum += v[u];
+    }
+    return sum;
+}
+
+// A block takes a range of cells, consecutive in the cell order: it sums the
+// counts of the cells before them (so no scan runs as a launch of its own:
+// an idle one costs every step 1.5 us, and at 1M particles the sums take a
+// block about 15 us where one block's scan took 33 us with the chip idle
+// beside it), then its waves take the range's cells in turn, and it writes
+// the cell starts that the list build reads.
+//
 // The sort waits on chains of memory round trips rather than on issue, so in
 // double-single and FP64 it is compiled for 6 waves per SIMD (at most 80
-// VGPRs, no spills) instead of the 4 its unconstrained register use allows;
-// its grid takes one full residency at that occupancy.  The FP32 and
-// MIXED64 forms would spill at 80 VGPRs and keep their own allocation.
+// VGPRs) instead of the 4 its unconstrained register use allows; its grid
+// takes one full residency at that occupancy.  The FP32 and MIXED64 forms
+// would spill at 80 VGPRs and keep their own allocation.
 template <int P>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(PERM_BLOCK)
 __attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 1))) k_permute(const PermArgs a)
 {
+    __shared__ PermLds lds[PERM_BLOCK / 64];
+    __shared__ int red[3][PERM_BLOCK / 64];
+    constexpr int WPB = PERM_BLOCK / 64;
     const int lane = threadIdx.x & 63;
-    const int wpb = blockDim.x >> 6;
-    const int wv = threadIdx.x >> 6;
-    __shared__ int pref[4][55], pst[4][54], srt[4][27];
-    __shared__ int2 lst[4][PERM_LIST]; // (old slot, scratch slot) of the members found
-    for_items(a.rlist, a.items_pref, a.rep, a.max_slots, a.force_slot, a.ctl, 3,
-              blockIdx.x * wpb + wv, gridDim.x * wpb, [&](int s, int c) {
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto range_of = [&](int nc) { return WPB * ((nc + WPB * (int)gridDim.x - 1) / (WPB * (int)gridDim.x)); };
+    for_items(a.rlist, [&](int sl) {
+        const int nc = a.rep[sl].items3, range = range_of(nc);
+        return (nc + range - 1) / range;
+    }, blockIdx.x, gridDim.x, [&](int s, int item) {
         const RepDev rp = a.rep[s];
-        const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes;
-        const int *cs = a.cs + rp.coff;
-        // new cell c of every plane: plane-0 members go to [dst0, dst0 +
-        // want0), plane-1 members to [dst1, dst1 + want1)
-        const int rc = cell_rank(c, rp, a.corder);
-        const int dst0 = a.cs_new[rp.coff + rc], want0 = a.cs_new[rp.coff + rc + 1] - dst0;
-        const int dst1 = planes > 1 ? a.cs_new[rp.coff + nc + rc] : 0;
-        const int want1 = planes > 1 ? a.cs_new[rp.coff + nc + rc + 1] - dst1 : 0;
-        // the old cells that can hold members of new cell c, in ascending
-        // rank: plane 0's, then plane 1's (so that the flattened candidates
-        // are in old slot order); one range per lane
-        const int nold = nd == 1 ? 1 : 27, nr = planes * nold;
-        if (nd > 1) { // rank the 27 neighbour cells (distinct for nd >= 3)
-            int orank = 0x7fffffff;
-            if (lane < 27) {
-                const int cx = c % nd, cy = (c / nd) % nd, cz = c / (nd * nd);
-                int ox = cx + lane % 3 - 1, oy = cy + (lane / 3) % 3 - 1, oz = cz + lane / 9 - 1;
-                ox += ox < 0 ? nd : 0; ox -= ox >= nd ? nd : 0;
-                oy += oy < 0 ? nd : 0; oy -= oy >= nd ? nd : 0;
-                oz += oz < 0 ? nd : 0; oz -= oz >= nd ? nd : 0;
-                orank = cell_rank(ox + nd * (oy + nd * oz), rp, a.corder);
-            }
-            int pos = 0;
-            for (int l = 0; l < 27; ++l) pos += __shfl(orank, l, 64) < orank;
-            if (lane < 27) srt[wv][pos] = orank;
-            __builtin_amdgcn_wave_barrier();
+        const int nd = rp.nd, nc = nd * nd * nd, range = range_of(nc);
+        const bool two = rp.planes > 1;
+        const int c0 = item * range, c1 = min(nc, c0 + range);
+        const int *cnt = a.count + rp.coff;
+        int *out = a.cs_new + rp.coff;
+        // members before the range: of plane 0; of plane 0 in all and of plane 1
+        int sum[3] = {thread_sum(cnt, c0), 0, 0};
+        if (two) {
+            sum[1] = thread_sum(cnt + c0, nc - c0);
+            sum[2] = thread_sum(cnt + nc, c0);
         }
-        int len = 0, st0 = 0;
-        if (lane < nr) {
-            const int pl = lane >= nold, kk = lane - pl * nold;
-            const int oc = pl * nc + (nd > 1 ? srt[wv][kk] : 0);
-            st0 = cs[oc];
-            len = cs[oc + 1] - st0;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) sum[q] += __shfl_xor(sum[q], o, 64);
+            if (lane == 0) red[q][wv] = sum[q];
         }
-        int incl = len;
+        __syncthreads();
+        int base[2] = {0, 0};
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int u = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += u;
+        for (int w = 0; w < WPB; ++w) {
+            base[0] += red[0][w];
+            base[1] += red[1][w] + red[2][w];
         }
-        if (lane < nr) { pst[wv][lane] = st0; pref[wv][lane + 1] = incl; }
-        if (lane == 0) pref[wv][0] = 0;
-        __builtin_amdgcn_wave_barrier();
-        const int tot = pref[wv][nr], tot0 = pref[wv][nold];
-        // move phase: every listed member, loaded before any is stored
-        auto move_listed = [&](int n) {
-            __builtin_amdgcn_wave_barrier();
-            for (int k = lane; k < n; k += 64) {
-                const int2 e = lst[wv][k];
-                Moved<P> mv;
-                move_load<P>(a, e.x, mv);
-                move_store<P>(a, rp, mv, e.y);
-            }
-            __builtin_amdgcn_wave_barrier();
-        };
-        int run0 = 0, run1 = 0, nl = 0;
-        int r = 0; // range of the lane's current candidate (only moves forward)
-        const unsigned long long below = (1ull << lane) - 1ull;
-        for (int b = 0; b < tot; b += 64 * PERM_U) {
-            int q[PERM_U];
-            bool m[PERM_U];
+        base[1] = rp.off + base[0] + base[1];
+        base[0] += rp.off;
+        for (int b = c0; b < c1; b += 64) {
+            const int k = b + lane;
+            const int n0 = k < c1 ? cnt[k] : 0, n1 = two && k < c1 ? cnt[nc + k] : 0;
+            int i0 = n0, i1 = n1;
 #pragma unroll
-            for (int u = 0; u < PERM_U; ++u) {
-                const int e = b + 64 * u + lane;
-                q[u] = -1;
-                if (e < tot) {
-                    while (r + 1 < nr && pref[wv][r + 1] <= e) ++r;
-                    q[u] = pst[wv][r] + (e - pref[wv][r]);
-                }
+            for (int o = 1; o < 64; o <<= 1) {
+                const int x = __shfl_up(i0, o, 64), y = __shfl_up(i1, o, 64);
+                if (lane >= o) { i0 += x; i1 += y; }
             }
-#pragma unroll
-            for (int u = 0; u < PERM_U; ++u) m[u] = q[u] >= 0 && (nd == 1 || in_cell<P>(a, rp, q[u], c));
-            // list the members found, in candidate order (at most 64 x
-            // PERM_U, so the list, emptied below once it holds more than
-            // 64, never overflows)
-#pragma unroll
-            for (int u = 0; u < PERM_U; ++u) {
-                const bool p1 = b + 64 * u + lane >= tot0;
-                const unsigned long long bal0 = __ballot(m[u] && !p1), bal1 = __ballot(m[u] && p1);
-                if (m[u]) {
-                    const int dst = p1 ? dst1 + run1 + __popcll(bal1 & below) : dst0 + run0 + __popcll(bal0 & below);
-                    lst[wv][nl + __popcll((bal0 | bal1) & below)] = make_int2(q[u], dst);
-                }
-                run0 += __popcll(bal0);
-                run1 += __popcll(bal1);
-                nl += __popcll(bal0 | bal1);
+            const int s0 = base[0] + i0 - n0, s1 = base[1] + i1 - n1;
+            if (wv == 0 && k < c1) {
+                out[k] = s0;
+                if (two) out[nc + k] = s1;
             }
-            if (nl > PERM_LIST - 64 * PERM_U) { move_listed(nl); nl = 0; }
+            for (int q = wv; q < min(64, c1 - b); q += WPB) {
+                const int cell = rp.curve ? a.corder_inv[rp.coff + b + q] : b + q;
+                permute_cell<P>(a, rp, lds[wv], s, cell, __builtin_amdgcn_readlane(s0, q),
+                                __builtin_amdgcn_readlane(n0, q), __builtin_amdgcn_readlane(s1, q),
+                                __builtin_amdgcn_readlane(n1, q));
+            }
+            base[0] += __builtin_amdgcn_readlane(i0, 63);
+            base[1] += __builtin_amdgcn_readlane(i1, 63);
         }
-        move_listed(nl);
-        // every particle counted in this cell must have come from a
-        // neighbouring old cell; a shortfall means a particle jumped further
-        if (lane == 0 && (run0 != want0 || run1 != want1)) atomicOr(a.status + s, 4);
+        if (c1 == nc && threadIdx.x == 0) { // the last range knows the sum
+            const int end = two ? base[1] : base[0];
+            out[two ? 2 * nc : nc] = end;
+            if (end - rp.off != rp.n) atomicOr(a.status + s, 4 | 2);
+            a.nreb[s] += 1;
+        }
+        __syncthreads();
     });
 }
 
@@ -381,18 +419,6 @@ __device__ __forceinline__ void visit_offset(int v, int &dx, int &dy, int &dz)
     dz = sg * (q / 9 - 1);
     dy = sg * ((q / 3) % 3 - 1);
     dx = sg * (q % 3 - 1);
-}
-
-// Rank of the cell at an offset of at most one from cell (cx, cy, cz).
-__device__ __forceinline__ int offset_rank(int cx, int cy, int cz, int dx, int dy, int dz, const RepDev &rp,
-                                           const int *corder)
-{
-    const int nd = rp.nd;
-    int x = cx + dx, y = cy + dy, z = cz + dz;
-    x += x < 0 ? nd : 0; x -= x >= nd ? nd : 0;
-    y += y < 0 ? nd : 0; y -= y >= nd ? nd : 0;
-    z += z < 0 ? nd : 0; z -= z >= nd ? nd : 0;
-    return cell_rank(x + nd * (y + nd * z), rp, corder);
 }
 
 // A position as the list test reads it: the snapshot (fixed point), or its
@@ -910,7 +936,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
 {
     __shared__ BuildLds lds[BUILD_BLOCK / 64];
     const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for_items(a.rlist, a.items_pref, a.rep, a.max_slots, a.force_slot, a.ctl, 4,
+    for_items(a.rlist, [&](int sl) { return a.rep[sl].items4; },
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
               [&](int s, int item) { build_item<P>(a, lds[wv], s, item); });
 }
@@ -937,16 +963,16 @@ hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
     LAUNCH_CHECK();
 }
 
-hipError_t launch_scan(const ScanArgs &a, hipStream_t s)
+hipError_t launch_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_scan, dim3(a.max_slots), dim3(SCAN_B), 0, s, a);
+    hipLaunchKernelGGL(k_enlist, dim3(1), dim3(64), 0, s, rlist, ctl, max_slots, slot);
     LAUNCH_CHECK();
 }
 
 hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s)
 {
     switch (prec) {
-    case PREC_FP32: hipLaunchKernelGGL((k_permute<PREC_FP32>), dim3(grid), dim3(256), 0, s, a); break;
+    case PREC_FP32: hipLaunchKernelGGL((k_permute<PREC_FP32>), dim3(grid), dim3(PERM_BLOCK), 0, s, a); break;
     case PREC_DS: hipLaunchKernelGGL((k_permute<PREC_DS>), dim3(grid), dim3(256), 0, s, a); break;
     case PREC_MIX: hipLaunchKernelGGL((k_permute<PREC_MIX>), dim3(grid), dim3(256), 0, s, a); break;
     default: hipLaunchKernelGGL((k_permute<PREC_FP64>), dim3(grid), dim3(256), 0, s, a); break;
