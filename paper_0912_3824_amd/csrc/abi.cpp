@@ -513,7 +513,7 @@ static md_status launch_build_main(md_system *s, int slot)
 static md_status launch_one_step(md_system *s, int p)
 {
     StepArgs a = step_args(s, p);
-    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, false, s->stream));
+    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, s->n_cu, false, s->stream));
     return launch_rebuild(s, p);
 }
 
@@ -1188,7 +1188,7 @@ md_status md_forces(md_system *s, int32_t slot, double *f_host, double *e_host)
 {
     if (!s) return MD_E_ARG;
     StepArgs a = step_args(s, s->parity);
-    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, true, s->stream));
+    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, s->n_cu, true, s->stream));
     HIPCHK(s, void_stored_after_obs(s));
     if (!f_host && !e_host) return MD_OK;
     md_status st = check_slot(s, slot, true);
@@ -1263,7 +1263,7 @@ md_status md_observables(md_system *s, md_obs *out)
     if (!s || !out) return MD_E_ARG;
     const int S = (int)s->lay.slots;
     StepArgs a = step_args(s, s->parity);
-    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, true, s->stream));
+    HIPCHK(s, launch_step(s->prec, a, s->launch.step_block, s->n_cu, true, s->stream));
     HIPCHK(s, void_stored_after_obs(s));
     ObsArgs oa;
     oa.max_slots = S;
@@ -1425,7 +1425,7 @@ md_status md_profile_steps(md_system *s, int64_t n_steps, double *out)
         const int p = s->parity;
         StepArgs a = step_args(s, p);
         chk(hipEventRecord(ev[3 * k], s->stream), "event");
-        chk(launch_step(s->prec, a, s->launch.step_block, false, s->stream), "step launch");
+        chk(launch_step(s->prec, a, s->launch.step_block, s->n_cu, false, s->stream), "step launch");
         chk(hipEventRecord(ev[3 * k + 1], s->stream), "event");
         if (st == MD_OK) st = launch_rebuild(s, p);
         chk(hipEventRecord(ev[3 * k + 2], s->stream), "event");

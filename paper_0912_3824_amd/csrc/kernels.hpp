@@ -117,7 +117,7 @@ hipError_t launch_thermostat(int prec, const ThermoArgs &a, hipStream_t s);
 #define THERMO_SCRATCH_CHUNKS 16384
 hipError_t thermo_scratch_init(int dev); // once per device, with that device current
 double *thermo_scratch(int dev);         // its device address (nullptr before init)
-hipError_t launch_step(int prec, const StepArgs &a, int block, bool obs, hipStream_t s);
+hipError_t launch_step(int prec, const StepArgs &a, int block, int n_cu, bool obs, hipStream_t s);
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
 hipError_t launch_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
 hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s);
