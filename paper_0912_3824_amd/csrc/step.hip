@@ -48,6 +48,7 @@ template <> struct FAcc<PREC_MIX> {
 // of the group end with the same bits).
 __device__ __forceinline__ void lane_sum(float &x, int m) { x += __shfl_xor(x, m, 64); }
 __device__ __forceinline__ void lane_sum(double &x, int m) { x += __shfl_xor(x, m, 64); }
+
 // ------------------------------------------------------------ integration
 // Velocity-Verlet pieces: kick v += (dt/2m) F, drift r += dt v.
 __device__ __forceinline__ void kick(State<PREC_FP32> &s, const FAcc<PREC_FP32> &f, const IntegDev &g)
@@ -359,7 +360,26 @@ __device__ __forceinline__ void force_dbl(const KArena &A, const uint4 *__restri
 // ------------------------------------------------------------ k_step
 enum { M_ADV = 0, M_FIN = 1, M_IDLE = 2 };
 
-template <int P, bool OBS, int KIND, int LPP>
+// A uniform index into memory that no kernel writes while this one runs:
+// scalar loads.
+template <class T> __device__ __forceinline__ T ld_uniform(const T *p, int k)
+{
+    typedef const __attribute__((address_space(4))) int CW;
+    struct Words { int w[sizeof(T) / 4]; } v;
+    CW *q = (CW *)(uintptr_t)(p + k);
+#pragma unroll
+    for (unsigned u = 0; u < sizeof(T) / 4; ++u) v.w[u] = q[u];
+    T t;
+    __builtin_memcpy(&t, &v, sizeof t);
+    return t;
+}
+
+// ONE: a pool of one slot.  Its records are read by scalar loads before
+// anything is known of the particle, two round trips to memory earlier than
+// through the slot in the particle's snapshot, and stay in scalar registers.
+// us per step, before -> after: 64,000 particles 22.2 -> 20.7, 37,000 FP32
+// 16.1 -> 15.7, 200,000 FP64 82.5 -> 77.6 (114 instead of 128 VGPRs).
+template <int P, bool OBS, int KIND, int LPP, bool ONE>
 __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
 {
     const KArena &A = a.A;
@@ -375,6 +395,14 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
         const int gt = blockIdx.x * blockDim.x + threadIdx.x;
         for (int c = gt; c < a.cell_cap; c += nblk * blockDim.x) a.count_other[c] = 0;
         if (gt == 0) a.rlist_other[0] = 0;
+    }
+    Ctl ctl0;
+    RepDev rp0;
+    int tgt0;
+    if (ONE) {
+        ctl0 = ld_uniform(a.ctl_cur, 0);
+        rp0 = ld_uniform(a.rep, 0);
+        tgt0 = ld_uniform(a.target, 0);
     }
     if (i >= A.P) return;
 
@@ -399,14 +427,14 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
     if (meta == NO_SLOT) return;
     const int r = slot_of_meta(meta);
     if (r >= a.max_slots) return;
-    const Ctl ctl = a.ctl_cur[r];
+    const Ctl ctl = ONE ? ctl0 : a.ctl_cur[r];
     if (!ctl.z) return;
-    const RepDev rp = a.rep[r];
+    const RepDev rp = ONE ? rp0 : a.rep[r];
+    const int tgt = OBS ? 0 : ONE ? tgt0 : a.target[r];
     int mode;
     if (OBS) {
         mode = M_FIN;
     } else {
-        const int tgt = a.target[r];
         // A replica with an error bit (a list that overflowed its capacity
         // or could not be padded, lost particles, a non-finite position)
         // stops where it is: no step runs on a truncated list.
@@ -592,25 +620,30 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
 }
 
 // ------------------------------------------------------------ launcher
+template <int P, int KIND, int LPP>
+static void launch_step_k(const StepArgs &a, int grid, int block, bool obs, hipStream_t s)
+{
+    if (obs) hipLaunchKernelGGL((k_step<P, true, KIND, LPP, false>), dim3(grid), dim3(block), 0, s, a);
+    else if (a.max_slots == 1) hipLaunchKernelGGL((k_step<P, false, KIND, LPP, true>), dim3(grid), dim3(block), 0, s, a);
+    else hipLaunchKernelGGL((k_step<P, false, KIND, LPP, false>), dim3(grid), dim3(block), 0, s, a);
+}
+
 template <int P, int LPP>
 static hipError_t launch_step_l(const StepArgs &a, int block, bool obs, hipStream_t s)
 {
     const long long threads = (long long)a.A.P * LPP;
     const int grid = (int)((threads + block - 1) / block);
     if (a.pp.smooth) {
-        if (obs) hipLaunchKernelGGL((k_step<P, true, PK_SMOOTH, LPP>), dim3(grid), dim3(block), 0, s, a);
-        else hipLaunchKernelGGL((k_step<P, false, PK_SMOOTH, LPP>), dim3(grid), dim3(block), 0, s, a);
+        launch_step_k<P, PK_SMOOTH, LPP>(a, grid, block, obs, s);
         LAUNCH_CHECK();
     }
     if constexpr (P != PREC_FP64) {
         if (a.pp.uniform) {
-            if (obs) hipLaunchKernelGGL((k_step<P, true, PK_UNIFORM, LPP>), dim3(grid), dim3(block), 0, s, a);
-            else hipLaunchKernelGGL((k_step<P, false, PK_UNIFORM, LPP>), dim3(grid), dim3(block), 0, s, a);
+            launch_step_k<P, PK_UNIFORM, LPP>(a, grid, block, obs, s);
             LAUNCH_CHECK();
         }
     }
-    if (obs) hipLaunchKernelGGL((k_step<P, true, PK_GENERAL, LPP>), dim3(grid), dim3(block), 0, s, a);
-    else hipLaunchKernelGGL((k_step<P, false, PK_GENERAL, LPP>), dim3(grid), dim3(block), 0, s, a);
+    launch_step_k<P, PK_GENERAL, LPP>(a, grid, block, obs, s);
     LAUNCH_CHECK();
 }
 
