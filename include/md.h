@@ -74,9 +74,8 @@ typedef enum {
 /* Arithmetic of the path (Sec. 2.4 defines the double-single split). */
 typedef enum {
     MD_FP32 = 0,    /* FP32 pair force, FP32 force sum, FP32 velocity Verlet */
-    MD_DS = 1,      /* FP32 pair force, force sum to double-single (the FP32
-                       terms are summed in FP64, which holds more than a pair of
-                       floats does), double-single velocity Verlet (Alg. 1) */
+    MD_DS = 1,      /* FP32 pair force, double-single force sum (error-free
+                       transformations), double-single velocity Verlet (Alg. 1) */
     MD_MIXED64 = 2, /* FP32 pair force, FP64 force sum, FP64 velocity Verlet */
     MD_FP64 = 3     /* everything in FP64 */
 } md_precision;
@@ -428,7 +427,7 @@ void md_tcf_destroy(md_tcf *tcf);
  * pairs, on the given stream: op 0 = add (Alg. 1), 1 = subtract,
  * 2 = multiply (exact FMA product of the high words plus cross terms),
  * 3 = compensated sum of a[k].hi over k (out[0] only; Sum2-style error-free
- * accumulation).  Asynchronous. */
+ * accumulation as used for the force sum).  Asynchronous. */
 md_status md_ds_eval(int32_t op, int64_t n, const float *a, const float *b, float *out,
                      void *hip_stream);
 

@@ -13,21 +13,21 @@ template <> struct FAcc<PREC_FP32> {
         y = __builtin_fmaf(fs, dy, y);
         z = __builtin_fmaf(fs, dz, z);
     }
+    __device__ void get(double &fx, double &fy, double &fz) const { fx = x; fy = y; fz = z; }
 };
 
-// Double-single: the FP32 terms are summed in FP64, whose add runs at the
-// FP32 rate on gfx950, and the sum is rounded to double-single once at the
-// end.  Every partial sum keeps 53 bits, where the error-free sum of two
-// floats it replaces kept about 48, for 3 instructions per term (multiply,
-// widen, add) instead of 8.
 template <> struct FAcc<PREC_DS> {
-    double x, y, z;
-    __device__ void init() { x = y = z = 0.0; }
+    sum2f x, y, z;
+    __device__ void init() { x.init(); y.init(); z.init(); }
     __device__ void add(float fs, float dx, float dy, float dz, int, int, int)
     {
-        x += (double)(fs * dx);
-        y += (double)(fs * dy);
-        z += (double)(fs * dz);
+        x.add(fs * dx);
+        y.add(fs * dy);
+        z.add(fs * dz);
+    }
+    __device__ void get(double &fx, double &fy, double &fz) const
+    {
+        fx = ds_to_double(x.result()); fy = ds_to_double(y.result()); fz = ds_to_double(z.result());
     }
 };
 
@@ -41,6 +41,7 @@ template <> struct FAcc<PREC_MIX> {
         y = __builtin_fma(f, (double)iy, y);
         z = __builtin_fma(f, (double)iz, z);
     }
+    __device__ void get(double &fx, double &fy, double &fz) const { fx = x; fy = y; fz = z; }
 };
 
 // Butterfly sum of the partial sums of the LPP lanes that share a particle
@@ -48,6 +49,11 @@ template <> struct FAcc<PREC_MIX> {
 // of the group end with the same bits).
 __device__ __forceinline__ void lane_sum(float &x, int m) { x += __shfl_xor(x, m, 64); }
 __device__ __forceinline__ void lane_sum(double &x, int m) { x += __shfl_xor(x, m, 64); }
+__device__ __forceinline__ void lane_sum(dsf &x, int m)
+{
+    dsf o = {__shfl_xor(x.hi, m, 64), __shfl_xor(x.lo, m, 64)};
+    x = ds_add(x, o);
+}
 
 // ------------------------------------------------------------ integration
 // Velocity-Verlet pieces: kick v += (dt/2m) F, drift r += dt v.
@@ -522,12 +528,13 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
             const LaneConsts c = lane_consts(a.pp, si, rp);
             force_fixed<P, OBS, KIND>(A, a.snap_cur, i, s0, c, a.pp, si, acc, e_sum, w_sum, sub, LPP, lh);
             // combine the lanes' partial sums (a no-op for one lane per particle)
+            if constexpr (P == PREC_DS) F = {acc.x.result(), acc.y.result(), acc.z.result()};
 #pragma unroll
             for (int m = 1; m < LPP; m <<= 1) {
-                lane_sum(acc.x, m); lane_sum(acc.y, m); lane_sum(acc.z, m);
+                if constexpr (P == PREC_DS) { lane_sum(F.x, m); lane_sum(F.y, m); lane_sum(F.z, m); }
+                else { lane_sum(acc.x, m); lane_sum(acc.y, m); lane_sum(acc.z, m); }
                 if (OBS) { lane_sum(e_sum, m); lane_sum(w_sum, m); }
             }
-            if constexpr (P == PREC_DS) F = {ds_from_double(acc.x), ds_from_double(acc.y), ds_from_double(acc.z)};
         }
         if (sub != 0) return;
         if (mode == M_FIN && !OBS) { // keep the forces for the next step
@@ -539,7 +546,7 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
         }
         if (OBS) {
             if constexpr (P == PREC_DS) { fxd = ds_to_double(F.x); fyd = ds_to_double(F.y); fzd = ds_to_double(F.z); }
-            else { fxd = acc.x; fyd = acc.y; fzd = acc.z; }
+            else acc.get(fxd, fyd, fzd);
             double *o = a.obs + (size_t)i * 8;
             o[0] = fxd; o[1] = fyd; o[2] = fzd; o[3] = e_sum; o[4] = w_sum;
             double vx, vy, vz;
