@@ -102,7 +102,12 @@ struct md_system {
     int *target = nullptr, *need[2]{}, *rlist[2]{}, *status = nullptr, *nreb = nullptr;
     int *chunks = nullptr;
     double *partial = nullptr;
+    uint4 *stage = nullptr;         // stage_bytes: small read-backs on their way to `pin`
+    SlotWords *words = nullptr;     // [slots], where there is no `pin`
+    int *bad = nullptr;             // set by a read-back that met a corrupt particle id: the first word of `stage`
     // host state
+    void *pin = nullptr;            // pinned host memory of pin_bytes(), made by the first read-back
+    bool no_pin = false;            // it could not be had
     PairDev pp{};
     IntegDev ig{};
     md_launch launch{};
@@ -225,6 +230,13 @@ struct Carver {
     }
 };
 
+// Read-backs of up to STAGE_BYTES go through device memory of the workspace
+// to pinned host memory in two launches and one synchronisation; each of the
+// pageable copies they replace costs 10 us and more before its first byte.
+constexpr int64_t STAGE_BYTES = 1 << 20;
+constexpr int64_t FRAME_BYTES = 60; // a particle's position, velocity and images
+static int64_t stage_words(int64_t P) { return std::min(STAGE_BYTES, align_up(P * FRAME_BYTES, 64)) / 16 + 1; }
+
 static int64_t carve(md_system *s, const Layout &L, char *base)
 {
     Carver c{base};
@@ -261,6 +273,9 @@ static int64_t carve(md_system *s, const Layout &L, char *base)
     d->chunks = c.take<int>(L.slots + 1);
     d->partial = c.take<double>((L.P / 4096 + L.slots + 1) * 8);
     d->obs_out = c.take<double>(L.slots * 8);
+    d->stage = c.take<uint4>(stage_words(L.P));
+    d->words = c.take<SlotWords>(L.slots);
+    d->bad = (int *)d->stage;
     return align_up(c.off, ALIGN);
 }
 
@@ -596,10 +611,6 @@ static void put_f4(uint4 &u, float a, float b, float c, float d)
 {
     memcpy(&u.x, &a, 4); memcpy(&u.y, &b, 4); memcpy(&u.z, &c, 4); memcpy(&u.w, &d, 4);
 }
-static void get_f4(const uint4 &u, float &a, float &b, float &c, float &d)
-{
-    memcpy(&a, &u.x, 4); memcpy(&b, &u.y, 4); memcpy(&c, &u.z, 4); memcpy(&d, &u.w, 4);
-}
 
 // ------------------------------------------------------------ cell order
 // Keys of cell (x, y, z) on a 2^bits grid.  Morton: the coordinates' bits
@@ -861,13 +872,13 @@ static md_status status_of_bits(int bits)
 
 // Record the device status bits read at a synchronising call; report the
 // first failed slot.
-static md_status note_failures(md_system *s, const int *bits)
+static md_status note_failures(md_system *s, const std::vector<SlotWords> &w)
 {
     md_status worst = MD_OK;
     for (size_t k = 0; k < s->slots.size(); ++k) {
         SlotHost &h = s->slots[k];
         if (!h.attached) continue;
-        h.failed = bits[k] & MD_ST_ERRORS;
+        h.failed = w[k].status & MD_ST_ERRORS;
         const md_status st = status_of_bits(h.failed);
         if (st != MD_OK && worst == MD_OK) {
             worst = fail(s, st, "replica in slot %d stopped: status bits 0x%x (%s)", (int)k, h.failed,
@@ -912,6 +923,127 @@ static md_status finish_attach(md_system *s, int slot)
     HIPCHK(s, hipMemcpy(&status, s->status + slot, 4, hipMemcpyDeviceToHost));
     if (status & MD_ST_LIST_OVERFLOW)
         return fail(s, MD_E_CAPACITY, "neighbour list overflow at attach (capacity %lld)", (long long)s->lay.cap);
+    return MD_OK;
+}
+
+// The pool's pinned buffer: a small read-back or every slot's words and sums.
+// Null where it cannot be had; callers then copy from device memory.
+static void *pinned(md_system *s)
+{
+    if (s->pin || s->no_pin) return s->pin;
+    const size_t bytes = std::max<size_t>(16 * stage_words(s->lay.P), s->lay.slots * (sizeof(SlotWords) + 64));
+    if (hipHostMalloc(&s->pin, bytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        s->pin = nullptr;
+        s->no_pin = true;
+    }
+    return s->pin;
+}
+
+// Launch a.pos .. a.energy (those that are set, as host pointers) of a slot by
+// particle id and copy them to the host.
+static md_status read_frame(md_system *s, const SlotHost &h, FrameArgs a, double *pos, double *vel, int32_t *image,
+                            double *force, double *energy)
+{
+    const int64_t n = h.n;
+    a.A = arena_of(s);
+    a.off = (int)h.off;
+    a.n = h.n;
+    a.L = h.L;
+    a.obs = s->obs;
+    a.bad = s->bad;
+    struct Part { void *host; int64_t bytes; void **arg; };
+    const Part parts[5] = {{pos, 24 * n, (void **)&a.pos},       {vel, 24 * n, (void **)&a.vel},
+                           {image, 12 * n, (void **)&a.image},   {force, 24 * n, (void **)&a.force},
+                           {energy, 8 * n, (void **)&a.energy}};
+    int64_t all = 0;
+    for (const Part &p : parts) all += p.host ? align_up(p.bytes, 16) : 0;
+    int bad = 0;
+    if (all + 16 <= 16 * stage_words(s->lay.P) && pinned(s)) {
+        char *d = (char *)s->stage;
+        int64_t off = 16; // the first word holds the id check
+        for (const Part &p : parts)
+            if (p.host) {
+                *p.arg = d + off;
+                off += align_up(p.bytes, 16);
+            }
+        HIPCHK(s, launch_frame(s->prec, a, s->stream));
+        HIPCHK(s, launch_words_out(s->stage, (uint4 *)s->pin, (int)(off / 16), s->stream));
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        const char *b = (const char *)s->pin;
+        memcpy(&bad, b, 4);
+        off = 16;
+        for (const Part &p : parts)
+            if (p.host) {
+                if (!bad) memcpy(p.host, b + off, p.bytes);
+                off += align_up(p.bytes, 16);
+            }
+        if (bad) HIPCHK(s, launch_poke(s->bad, 0, s->stream));
+        return bad ? fail(s, MD_E_STATE, "corrupt particle ids") : MD_OK;
+    }
+    // Through the sort's scratch arrays, which are free between rebuilds: as
+    // many parts at a time as the scratch state words hold, image counters in
+    // the scratch meta words.
+    const int64_t room = 16 * s->lay.NW * s->lay.P;
+    for (int k = 0; k < 5;) {
+        FrameArgs part = a;
+        part.pos = part.vel = part.force = part.energy = nullptr;
+        part.image = nullptr;
+        int64_t off = 0;
+        int last = k;
+        void *dev[5] = {};
+        for (; last < 5; ++last) {
+            const Part &p = parts[last];
+            if (!p.host) continue;
+            const bool meta = last == 2;
+            if (!meta && off + p.bytes > room) break;
+            dev[last] = meta ? (char *)s->sc_meta : (char *)s->sc_st[0] + off;
+            if (!meta) off += align_up(p.bytes, 16);
+        }
+        part.pos = (double *)dev[0];
+        part.vel = (double *)dev[1];
+        part.image = (int *)dev[2];
+        part.force = (double *)dev[3];
+        part.energy = (double *)dev[4];
+        HIPCHK(s, launch_frame(s->prec, part, s->stream));
+        for (int q = k; q < last; ++q)
+            if (dev[q]) HIPCHK(s, hipMemcpyAsync(parts[q].host, dev[q], parts[q].bytes, hipMemcpyDeviceToHost, s->stream));
+        k = last;
+    }
+    HIPCHK(s, hipMemcpyAsync(&bad, s->bad, 4, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    if (bad) {
+        HIPCHK(s, launch_poke(s->bad, 0, s->stream));
+        return fail(s, MD_E_STATE, "corrupt particle ids");
+    }
+    return MD_OK;
+}
+
+// Every slot's control words, status bits and build counts at the current
+// parity, after all work on the stream; `sums` too where an observation
+// launch wrote them.
+static md_status read_words(md_system *s, std::vector<SlotWords> &w, std::vector<double> *sums, const ObsArgs *oa)
+{
+    const int S = (int)s->lay.slots;
+    w.resize(S);
+    if (sums) sums->resize(8 * (size_t)S);
+    char *p = (char *)pinned(s);
+    SlotWords *words = p ? (SlotWords *)(p + 64 * (size_t)S) : s->words;
+    if (oa) {
+        ObsArgs o = *oa;
+        o.words = words;
+        if (p) o.out = (double *)p;
+        HIPCHK(s, launch_obs_reduce(o, s->stream));
+    } else HIPCHK(s, launch_poll(s->ctl[s->parity], s->status, s->nreb, words, S, s->stream));
+    if (!p) {
+        HIPCHK(s, hipMemcpyAsync(w.data(), words, sizeof(SlotWords) * S, hipMemcpyDeviceToHost, s->stream));
+        if (sums) HIPCHK(s, hipMemcpyAsync(sums->data(), s->obs_out, 64 * (size_t)S, hipMemcpyDeviceToHost, s->stream));
+    }
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    if (p) {
+        memcpy(w.data(), words, sizeof(SlotWords) * S);
+        if (sums) memcpy(sums->data(), p, 64 * (size_t)S);
+    }
     return MD_OK;
 }
 
@@ -1031,6 +1163,7 @@ md_status md_create(const md_config *cfg, void *workspace, int64_t ws_bytes, voi
     if (!done(hipMemsetAsync(s->target, 0, 4 * L.slots, st))) return MD_E_HIP;
     if (!done(hipMemsetAsync(s->status, 0, 4 * L.slots, st))) return MD_E_HIP;
     if (!done(hipMemsetAsync(s->nreb, 0, 4 * L.slots, st))) return MD_E_HIP;
+    if (!done(hipMemsetAsync(s->bad, 0, 4, st))) return MD_E_HIP;
     if (!done(hipStreamSynchronize(st))) return MD_E_HIP;
     if (upload_items(s) != MD_OK) { delete s; return MD_E_HIP; }
     *out = s;
@@ -1041,6 +1174,7 @@ void md_destroy(md_system *s)
 {
     if (!s) return;
     drop_graphs(s);
+    if (s->pin) (void)hipHostFree(s->pin);
     delete s;
 }
 
@@ -1193,19 +1327,7 @@ md_status md_forces(md_system *s, int32_t slot, double *f_host, double *e_host)
     if (!f_host && !e_host) return MD_OK;
     md_status st = check_slot(s, slot, true);
     if (st != MD_OK) return st;
-    const SlotHost &h = s->slots[slot];
-    std::vector<double> o((size_t)h.n * 8);
-    std::vector<int4> mt(h.n);
-    HIPCHK(s, hipMemcpyAsync(o.data(), s->obs + h.off * 8, 8 * o.size(), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(mt.data(), s->meta + h.off, 16 * (size_t)h.n, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
-    for (int k = 0; k < h.n; ++k) {
-        int id = mt[k].w;
-        if (id < 0 || id >= h.n) return fail(s, MD_E_STATE, "corrupt particle ids");
-        if (f_host) for (int d = 0; d < 3; ++d) f_host[3 * id + d] = o[8 * k + d];
-        if (e_host) e_host[id] = o[8 * k + 3];
-    }
-    return MD_OK;
+    return read_frame(s, s->slots[slot], FrameArgs{}, nullptr, nullptr, nullptr, f_host, e_host);
 }
 
 md_status md_step(md_system *s, int64_t n_steps)
@@ -1245,17 +1367,15 @@ md_status md_poll(md_system *s, int64_t *steps, int32_t *status)
 {
     if (!s) return MD_E_ARG;
     const int S = (int)s->lay.slots;
-    std::vector<Ctl> c(S);
-    std::vector<int> stv(S);
-    HIPCHK(s, hipMemcpyAsync(c.data(), s->ctl[s->parity], sizeof(Ctl) * S, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(stv.data(), s->status, 4 * S, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
+    std::vector<SlotWords> w;
+    md_status st = read_words(s, w, nullptr, nullptr);
+    if (st != MD_OK) return st;
     for (int k = 0; k < S; ++k) {
         bool att = s->slots[k].attached;
-        if (steps) steps[k] = att ? c[k].x : -1;
-        if (status) status[k] = att ? (stv[k] | (c[k].y ? MD_ST_AT_FULL_STEP : 0)) : 0;
+        if (steps) steps[k] = att ? w[k].ctl.x : -1;
+        if (status) status[k] = att ? (w[k].status | (w[k].ctl.y ? MD_ST_AT_FULL_STEP : 0)) : 0;
     }
-    return note_failures(s, stv.data());
+    return note_failures(s, w);
 }
 
 md_status md_observables(md_system *s, md_obs *out)
@@ -1274,15 +1394,13 @@ md_status md_observables(md_system *s, md_obs *out)
     oa.chunk_pref = s->chunks;
     oa.partial = s->partial;
     oa.out = s->obs_out;
-    HIPCHK(s, launch_obs_reduce(oa, s->stream));
-    std::vector<double> r((size_t)S * 8);
-    std::vector<Ctl> c(S);
-    std::vector<int> stv(S), nr(S);
-    HIPCHK(s, hipMemcpyAsync(r.data(), s->obs_out, 8 * r.size(), hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(c.data(), s->ctl[s->parity], sizeof(Ctl) * S, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(stv.data(), s->status, 4 * S, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipMemcpyAsync(nr.data(), s->nreb, 4 * S, hipMemcpyDeviceToHost, s->stream));
-    HIPCHK(s, hipStreamSynchronize(s->stream));
+    oa.status = s->status;
+    oa.nreb = s->nreb;
+    oa.words = nullptr;
+    std::vector<double> r;
+    std::vector<SlotWords> w;
+    md_status st = read_words(s, w, &r, &oa);
+    if (st != MD_OK) return st;
     for (int k = 0; k < S; ++k) {
         md_obs &o = out[k];
         memset(&o, 0, sizeof o);
@@ -1297,12 +1415,12 @@ md_status md_observables(md_system *s, md_obs *out)
         o.temperature = 2.0 * o.ekin / (3.0 * h.n);
         o.pressure = (2.0 * o.ekin + o.virial) / (3.0 * V);
         for (int d = 0; d < 3; ++d) o.momentum[d] = m * r[8 * k + 3 + d];
-        o.step = c[k].x;
+        o.step = w[k].ctl.x;
         o.list_entries = (int64_t)r[8 * k + 6];
-        o.n_rebuilds = nr[k];
-        o.status = stv[k];
+        o.n_rebuilds = w[k].nreb;
+        o.status = w[k].status;
     }
-    return note_failures(s, stv.data());
+    return note_failures(s, w);
 }
 
 md_status md_scale_velocities(md_system *s, int32_t slot, double factor)
@@ -1489,65 +1607,15 @@ static md_status download_slot(md_system *s, const SlotHost &h, HostRep &hr, std
     return MD_OK;
 }
 
-// Decode a particle's state words into FP64 position and velocity.
-static void decode_particle(const md_system *s, const uint4 *w, double x[3], double v[3])
-{
-    switch (s->prec) {
-    case PREC_FP32: {
-        float a, b, c, d;
-        get_f4(w[0], a, b, c, d);
-        x[0] = a; x[1] = b; x[2] = c;
-        get_f4(w[1], a, b, c, d);
-        v[0] = a; v[1] = b; v[2] = c;
-        break;
-    }
-    case PREC_DS: {
-        float a0, a1, a2, a3, b0, b1, b2, b3, c0, c1, c2, c3;
-        get_f4(w[0], a0, a1, a2, a3);
-        get_f4(w[1], b0, b1, b2, b3);
-        get_f4(w[2], c0, c1, c2, c3);
-        x[0] = (double)a0 + (double)a3;
-        x[1] = (double)a1 + (double)b0;
-        x[2] = (double)a2 + (double)b1;
-        v[0] = (double)b2 + (double)c1;
-        v[1] = (double)b3 + (double)c2;
-        v[2] = (double)c0 + (double)c3;
-        break;
-    }
-    default:
-        get_dbl2(w[0], x[0], x[1]);
-        get_dbl2(w[1], x[2], v[0]);
-        get_dbl2(w[2], v[1], v[2]);
-    }
-}
-
 md_status md_get_state(md_system *s, int32_t slot, double *pos, double *vel, int32_t *image)
 {
     md_status st = check_slot(s, slot, true);
     if (st != MD_OK) return st;
-    const SlotHost &h = s->slots[slot];
-    HostRep hr;
-    std::vector<uint4> xr;
-    if ((st = download_slot(s, h, hr, xr)) != MD_OK) return st;
-    for (int k = 0; k < h.n; ++k) {
-        uint4 w[3] = {hr.st[0][k], hr.st[1][k], s->lay.NW > 2 ? hr.st[2][k] : make_uint4(0, 0, 0, 0)};
-        double x[3], v[3];
-        decode_particle(s, w, x, v);
-        int img[3] = {hr.meta[k].x, hr.meta[k].y, hr.meta[k].z};
-        int id = hr.meta[k].w;
-        if (id < 0 || id >= h.n) return fail(s, MD_E_STATE, "corrupt particle ids");
-        for (int d = 0; d < 3; ++d) {
-            double f = std::floor(x[d] / h.L);
-            double q = x[d] - f * h.L;
-            int im = img[d] + (int)f;
-            if (q >= h.L) { q -= h.L; im += 1; }
-            if (q < 0) { q += h.L; im -= 1; }
-            if (pos) pos[3 * id + d] = q;
-            if (vel) vel[3 * id + d] = v[d];
-            if (image) image[3 * id + d] = im;
-        }
+    if (!pos && !vel && !image) {
+        HIPCHK(s, hipStreamSynchronize(s->stream));
+        return MD_OK;
     }
-    return MD_OK;
+    return read_frame(s, s->slots[slot], FrameArgs{}, pos, vel, image, nullptr, nullptr);
 }
 
 struct CkptHeader {

@@ -48,10 +48,21 @@ __global__ void __launch_bounds__(256) k_obs_partial(const ObsArgs a)
     }
 }
 
+__device__ __forceinline__ SlotWords slot_words(const Ctl *ctl, const int *status, const int *nreb, int s)
+{
+    SlotWords w;
+    w.ctl = ctl[s];
+    w.status = status[s];
+    w.nreb = nreb[s];
+    return w;
+}
+
 __global__ void __launch_bounds__(256) k_obs_reduce(const ObsArgs a)
 {
     const int s = blockIdx.x;
-    if (s >= a.max_slots || !a.ctl[s].z) return;
+    if (s >= a.max_slots) return;
+    if (threadIdx.x == 0) a.words[s] = slot_words(a.ctl, a.status, a.nreb, s);
+    if (!a.ctl[s].z) return;
     __shared__ double red[OBS_Q][256];
     double acc[OBS_Q] = {0, 0, 0, 0, 0, 0, 0};
     const int c0 = a.chunk_pref[s], c1 = a.chunk_pref[s + 1];
@@ -60,6 +71,73 @@ __global__ void __launch_bounds__(256) k_obs_reduce(const ObsArgs a)
         for (int q = 0; q < OBS_Q; ++q) acc[q] += a.partial[(size_t)c * 8 + q];
     block_sum7(acc, red);
     if (threadIdx.x < OBS_Q) a.out[s * 8 + threadIdx.x] = red[threadIdx.x][0];
+}
+
+__global__ void __launch_bounds__(256) k_poll(const Ctl *ctl, const int *status, const int *nreb, SlotWords *out,
+                                              int max_slots)
+{
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s < max_slots) out[s] = slot_words(ctl, status, nreb, s);
+}
+
+// ------------------------------------------------------------ k_frame
+// A replica's state or forces by particle id, in the layout the host gets:
+// positions folded into [0, L) in FP64 with the image counters that go with
+// them, velocities, forces and energies.  The host used to fetch 64 to 112
+// bytes a particle and decode and scatter them itself: at 1M 39 ms a frame,
+// now 60 bytes a particle and 5 ms, most of it the copy to pageable memory.
+// The scattered stores (24 bytes a particle at an id unrelated to its slot)
+// bound the kernel: 90 us at 1M.
+template <int P>
+__global__ void __launch_bounds__(256) k_frame(const FrameArgs a)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= a.n) return;
+    const int i = a.off + k;
+    const int4 m = a.A.meta[i];
+    const int id = m.w;
+    if (id < 0 || id >= a.n) { // not a particle of this replica
+        *a.bad = 1;
+        return;
+    }
+    if (a.force || a.energy) {
+        const double *o = a.obs + (size_t)i * 8;
+        if (a.force)
+#pragma unroll
+            for (int d = 0; d < 3; ++d) a.force[3 * (size_t)id + d] = o[d];
+        if (a.energy) a.energy[id] = o[3];
+        return;
+    }
+    State<P> st;
+    st.load(a.A, i);
+    double x[3], v[3];
+    if constexpr (P == PREC_DS) {
+        x[0] = ds_to_double(st.x); x[1] = ds_to_double(st.y); x[2] = ds_to_double(st.z);
+        v[0] = ds_to_double(st.vx); v[1] = ds_to_double(st.vy); v[2] = ds_to_double(st.vz);
+    } else {
+        x[0] = st.x; x[1] = st.y; x[2] = st.z;
+        v[0] = st.vx; v[1] = st.vy; v[2] = st.vz;
+    }
+    const int img[3] = {m.x, m.y, m.z};
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        const double f = floor(x[d] / a.L);
+        double q = x[d] - f * a.L;
+        // (a non-finite position counts INT_MIN boxes, as the host's conversion does)
+        int im = (int)((unsigned)img[d] + (unsigned)(fabs(f) < 2147483648.0 ? (int)f : (int)0x80000000));
+        if (q >= a.L) { q -= a.L; im += 1; }
+        if (q < 0) { q += a.L; im -= 1; }
+        if (a.pos) a.pos[3 * (size_t)id + d] = q;
+        if (a.vel) a.vel[3 * (size_t)id + d] = v[d];
+        if (a.image) a.image[3 * (size_t)id + d] = im;
+    }
+}
+
+// Copy to pinned host memory (16-byte words, coalesced).
+__global__ void __launch_bounds__(256) k_words_out(const uint4 *src, uint4 *dst, int n)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) dst[k] = src[k];
 }
 
 // ------------------------------------------------------------ k_scale_vel
@@ -279,6 +357,32 @@ __global__ void k_ds_eval(int op, long long n, const float *a, const float *b, f
 }
 
 // ------------------------------------------------------------ launchers
+hipError_t launch_frame(int prec, const FrameArgs &a, hipStream_t s)
+{
+    const int grid = (a.n + 255) / 256;
+    if (grid == 0) return hipSuccess;
+    switch (prec) {
+    case PREC_FP32: hipLaunchKernelGGL((k_frame<PREC_FP32>), dim3(grid), dim3(256), 0, s, a); break;
+    case PREC_DS: hipLaunchKernelGGL((k_frame<PREC_DS>), dim3(grid), dim3(256), 0, s, a); break;
+    case PREC_MIX: hipLaunchKernelGGL((k_frame<PREC_MIX>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((k_frame<PREC_FP64>), dim3(grid), dim3(256), 0, s, a); break;
+    }
+    LAUNCH_CHECK();
+}
+
+hipError_t launch_words_out(const uint4 *src, uint4 *dst, int n, hipStream_t s)
+{
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_words_out, dim3((n + 255) / 256), dim3(256), 0, s, src, dst, n);
+    LAUNCH_CHECK();
+}
+
+hipError_t launch_poll(const Ctl *ctl, const int *status, const int *nreb, SlotWords *out, int max_slots, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_poll, dim3((max_slots + 255) / 256), dim3(256), 0, s, ctl, status, nreb, out, max_slots);
+    LAUNCH_CHECK();
+}
+
 hipError_t launch_obs_reduce(const ObsArgs &a, hipStream_t s)
 {
     hipLaunchKernelGGL(k_obs_partial, dim3(1024), dim3(256), 0, s, a);

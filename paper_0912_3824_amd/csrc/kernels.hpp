@@ -79,6 +79,8 @@ struct BuildArgs {
     PairDev pp;
 };
 
+struct SlotWords;
+
 struct ObsArgs {
     int max_slots, pad0;
     const RepDev *rep;
@@ -88,6 +90,25 @@ struct ObsArgs {
     const int *chunk_pref; // per slot prefix of ceil(n / 4096) chunks
     double *partial;       // [chunks][8]
     double *out;           // [max_slots][8]
+    const int *status, *nreb;
+    SlotWords *words;      // [max_slots] (device or pinned host memory)
+};
+
+// What a synchronising call reads of a slot besides its sums.
+struct SlotWords {
+    Ctl ctl;
+    int status, nreb;
+};
+
+// A replica's state or forces in particle-id order (any output may be null).
+struct FrameArgs {
+    KArena A;
+    int off, n;
+    double L;
+    const double *obs;
+    double *pos, *vel, *force, *energy; // [n][3], [n][3], [n][3], [n]
+    int *image;                         // [n][3]
+    int *bad;                           // set where a particle id is out of range
 };
 
 struct ScaleArgs {
@@ -125,6 +146,9 @@ hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
 hipError_t occupancy_permute(int prec, int *per_cu);
 hipError_t occupancy_build(int prec, int *per_cu);
+hipError_t launch_frame(int prec, const FrameArgs &a, hipStream_t s);
+hipError_t launch_words_out(const uint4 *src, uint4 *dst, int n, hipStream_t s);
+hipError_t launch_poll(const Ctl *ctl, const int *status, const int *nreb, SlotWords *out, int max_slots, hipStream_t s);
 hipError_t launch_obs_reduce(const ObsArgs &a, hipStream_t s);
 hipError_t launch_scale_vel(int prec, const ScaleArgs &a, hipStream_t s);
 hipError_t launch_ds_eval(int op, long long n, const float *a, const float *b, float *out, hipStream_t s);
