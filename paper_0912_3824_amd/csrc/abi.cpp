@@ -498,9 +498,10 @@ static md_status launch_rebuild(md_system *s, int p)
     return MD_OK;
 }
 
-// List build only, from the main arrays (attach / restore).  The rebuild list
+// List build only, from the main arrays (attach / restore), after the
+// candidate records where they are not there yet.  The rebuild list
 // of the parity that the next step clears serves as this one's.
-static md_status launch_build_main(md_system *s, int slot)
+static md_status launch_build_main(md_system *s, int slot, bool make_cand)
 {
     int *rlist = s->rlist[s->parity ^ 1];
     HIPCHK(s, launch_enlist(rlist, s->ctl[0], (int)s->lay.slots, slot, s->stream));
@@ -520,7 +521,8 @@ static md_status launch_build_main(md_system *s, int slot)
     ba.status = s->status;
     ba.pp = s->pp;
     const SlotHost &h = s->slots[slot];
-    if (build_mode(h.n, h.nd) == BUILD_CELLS) HIPCHK(s, launch_cand(s->prec, ba, s->cand, slot, h.n, s->stream));
+    if (make_cand && build_mode(h.n, h.nd) == BUILD_CELLS)
+        HIPCHK(s, launch_cand(s->prec, ba, s->cand, slot, h.n, s->stream));
     HIPCHK(s, launch_build(s->prec, ba, s->grid_build, s->stream));
     return MD_OK;
 }
@@ -607,11 +609,6 @@ static void get_dbl2(const uint4 &u, double &a, double &b)
     memcpy(&a, &x, 8);
     memcpy(&b, &y, 8);
 }
-static void put_f4(uint4 &u, float a, float b, float c, float d)
-{
-    memcpy(&u.x, &a, 4); memcpy(&u.y, &b, 4); memcpy(&u.z, &c, 4); memcpy(&u.w, &d, 4);
-}
-
 // ------------------------------------------------------------ cell order
 // Keys of cell (x, y, z) on a 2^bits grid.  Morton: the coordinates' bits
 // interleaved (x lowest).  Hilbert: Skilling's method (J. Skilling,
@@ -726,54 +723,6 @@ static RepDev repdev_of(const md_system *s, const SlotHost &h)
     return r;
 }
 
-// Convert one particle's FP64 position (already folded into [0, L)) and
-// velocity into state words and its snapshot.
-static void encode_particle(const md_system *s, const RepDev &r, double x[3], double v[3], int *img,
-                            uint32_t meta, uint4 *w, uint4 *snap)
-{
-    const double h_L = r.L;
-    switch (s->prec) {
-    case PREC_FP32: {
-        float f[3];
-        for (int d = 0; d < 3; ++d) {
-            // x is in [0, L); its float may round up to L or past it, which
-            // is folded by the exact edge (the box need not be a float)
-            f[d] = (float)x[d];
-            if ((double)f[d] >= h_L) { f[d] = (float)((double)f[d] - h_L); img[d] += 1; }
-            x[d] = (double)f[d];
-        }
-        put_f4(w[0], f[0], f[1], f[2], 0.0f);
-        put_f4(w[1], (float)v[0], (float)v[1], (float)v[2], 0.0f);
-        break;
-    }
-    case PREC_DS: {
-        float h[3], l[3], vh[3], vl[3];
-        for (int d = 0; d < 3; ++d) {
-            h[d] = (float)x[d];
-            l[d] = (float)(x[d] - (double)h[d]);
-            x[d] = (double)h[d] + (double)l[d];
-            vh[d] = (float)v[d];
-            vl[d] = (float)(v[d] - (double)vh[d]);
-        }
-        put_f4(w[0], h[0], h[1], h[2], l[0]);
-        put_f4(w[1], l[1], l[2], vh[0], vh[1]);
-        put_f4(w[2], vh[2], vl[0], vl[1], vl[2]);
-        break;
-    }
-    default:
-        put_dbl2(w[0], x[0], x[1]);
-        put_dbl2(w[1], x[2], v[0]);
-        put_dbl2(w[2], v[1], v[2]);
-        break;
-    }
-    if (s->prec == PREC_FP64) {
-        put_dbl2(snap[0], x[0], x[1]);
-        put_dbl2(snap[1], x[2], bits_of_meta(meta));
-    } else {
-        snap[0] = make_uint4(to_fixed(x[0], r.fxs), to_fixed(x[1], r.fxs), to_fixed(x[2], r.fxs), meta);
-    }
-}
-
 static int cell_of_snap(const md_system *s, const RepDev &r, const uint4 *sn)
 {
     if (r.nd == 1) return 0;
@@ -798,6 +747,20 @@ static md_status validate_rep(md_system *s, const md_replica *rep)
     return MD_OK;
 }
 
+// A replica's cell rank table and its inverse, for the curve orders.
+struct CellTables { std::vector<int> rank, inv; };
+
+static md_status upload_cell_tables(md_system *s, const SlotHost &h, const RepDev &r, CellTables &t)
+{
+    if (!r.curve) return MD_OK;
+    t.rank = ranks_of(s, h);
+    t.inv.resize(t.rank.size());
+    for (size_t c = 0; c < t.rank.size(); ++c) t.inv[t.rank[c]] = (int)c;
+    HIPCHK(s, hipMemcpyAsync(s->corder + h.coff, t.rank.data(), 4 * t.rank.size(), hipMemcpyHostToDevice, s->stream));
+    HIPCHK(s, hipMemcpyAsync(s->corder_inv + h.coff, t.inv.data(), 4 * t.inv.size(), hipMemcpyHostToDevice, s->stream));
+    return MD_OK;
+}
+
 static md_status upload_slot(md_system *s, int slot, const SlotHost &h, const HostRep &hr,
                              const std::vector<uint4> *xref_override, Ctl c, int64_t nreb, int status)
 {
@@ -817,13 +780,8 @@ static md_status upload_slot(md_system *s, int slot, const SlotHost &h, const Ho
     HIPCHK(s, hipMemcpyAsync(s->cs + h.coff, hr.cs.data(), 4 * hr.cs.size(), hipMemcpyHostToDevice, st));
     HIPCHK(s, hipMemcpyAsync(s->cs_new + h.coff, hr.cs.data(), 4 * hr.cs.size(), hipMemcpyHostToDevice, st));
     RepDev r = repdev_of(s, h);
-    const std::vector<int> rk = ranks_of(s, h); // kept until the stream synchronises below
-    std::vector<int> inv(r.curve ? rk.size() : 0);
-    if (r.curve) {
-        for (size_t c = 0; c < rk.size(); ++c) inv[rk[c]] = (int)c;
-        HIPCHK(s, hipMemcpyAsync(s->corder + h.coff, rk.data(), 4 * rk.size(), hipMemcpyHostToDevice, st));
-        HIPCHK(s, hipMemcpyAsync(s->corder_inv + h.coff, inv.data(), 4 * inv.size(), hipMemcpyHostToDevice, st));
-    }
+    CellTables tables; // kept until the stream synchronises below
+    if (md_status ct = upload_cell_tables(s, h, r, tables); ct != MD_OK) return ct;
     HIPCHK(s, hipMemcpyAsync(s->rep + slot, &r, sizeof r, hipMemcpyHostToDevice, st));
     for (int p = 0; p < 2; ++p) {
         HIPCHK(s, hipMemcpyAsync(s->ctl[p] + slot, &c, sizeof c, hipMemcpyHostToDevice, st));
@@ -916,7 +874,7 @@ static md_status finish_attach(md_system *s, int slot)
 {
     md_status st = upload_items(s);
     if (st != MD_OK) return st;
-    st = launch_build_main(s, slot);
+    st = launch_build_main(s, slot, true);
     if (st != MD_OK) return st;
     HIPCHK(s, hipStreamSynchronize(s->stream));
     int status = 0;
@@ -1044,6 +1002,75 @@ static md_status read_words(md_system *s, std::vector<SlotWords> &w, std::vector
         memcpy(w.data(), words, sizeof(SlotWords) * S);
         if (sums) memcpy(sums->data(), p, 64 * (size_t)S);
     }
+    return MD_OK;
+}
+
+// The replica of a slot from the caller's host arrays: input by id into the
+// slot's observation rows (64 bytes a particle, unused until forces are kept),
+// conversion and sort on the device, first lists.
+static md_status attach_on_device(md_system *s, int slot, const SlotHost &h, const int32_t *species, const double *pos,
+                                  const double *vel)
+{
+    const int64_t n = h.n;
+    char *rows = (char *)(s->obs + h.off * 8);
+    const int64_t bytes = (species ? 52 : 48) * n, words = (bytes + 15) / 16;
+    if (words <= stage_words(s->lay.P) && pinned(s)) {
+        char *p = (char *)s->pin;
+        memcpy(p, pos, 24 * n);
+        memcpy(p + 24 * n, vel, 24 * n);
+        if (species) memcpy(p + 48 * n, species, 4 * n);
+        HIPCHK(s, launch_words_out((const uint4 *)p, (uint4 *)rows, (int)words, s->stream));
+    } else {
+        HIPCHK(s, hipMemcpyAsync(rows, pos, 24 * n, hipMemcpyHostToDevice, s->stream));
+        HIPCHK(s, hipMemcpyAsync(rows + 24 * n, vel, 24 * n, hipMemcpyHostToDevice, s->stream));
+        if (species) HIPCHK(s, hipMemcpyAsync(rows + 48 * n, species, 4 * n, hipMemcpyHostToDevice, s->stream));
+    }
+    AttachArgs a;
+    memset(&a, 0, sizeof a);
+    a.A = arena_of(s);
+    a.slot = slot;
+    a.off = (int)h.off;
+    a.n = h.n;
+    a.rep = repdev_of(s, h);
+    a.ncell = a.rep.planes * h.nd * h.nd * h.nd;
+    a.pos = (const double *)rows;
+    a.vel = (const double *)(rows + 24 * n);
+    a.species = species ? (const int *)(rows + 48 * n) : nullptr;
+    a.key = (int *)(rows + 52 * n);
+    a.arrival = a.key + n;
+    a.ids = a.arrival + n;
+    a.corder = s->corder;
+    a.cs = s->cs;
+    a.cs_new = s->cs_new;
+    a.snap0 = s->snap[0];
+    a.snap1 = s->snap[1];
+    a.cand = s->cand;
+    a.reps = s->rep;
+    a.ctl0 = s->ctl[0];
+    a.ctl1 = s->ctl[1];
+    a.need0 = s->need[0];
+    a.need1 = s->need[1];
+    a.target = s->target;
+    a.status = s->status;
+    a.nreb = s->nreb;
+    a.chunks = s->chunks;
+    a.max_slots = (int)s->lay.slots;
+    a.n_species = s->cfg.n_species;
+    CellTables tables; // kept until the stream synchronises below
+    md_status st = upload_cell_tables(s, h, a.rep, tables);
+    if (st != MD_OK) return st;
+    HIPCHK(s, launch_attach(s->prec, a, s->stream));
+    if ((st = launch_build_main(s, slot, false)) != MD_OK) return st;
+    SlotWords w;
+    SlotWords *out = pinned(s) ? (SlotWords *)s->pin : s->words;
+    HIPCHK(s, launch_poll(s->ctl[0] + slot, s->status + slot, s->nreb + slot, out, 1, s->stream));
+    if (!s->pin) HIPCHK(s, hipMemcpyAsync(&w, out, sizeof w, hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(s, hipStreamSynchronize(s->stream));
+    if (s->pin) memcpy(&w, out, sizeof w);
+    if (w.status & ST_BAD_INPUT) return fail(s, MD_E_NONFINITE, "non-finite input");
+    if (w.status & ST_BAD_SPECIES) return fail(s, MD_E_ARG, "species out of range");
+    if (w.status & MD_ST_LIST_OVERFLOW)
+        return fail(s, MD_E_CAPACITY, "neighbour list overflow at attach (capacity %lld)", (long long)s->lay.cap);
     return MD_OK;
 }
 
@@ -1186,68 +1213,31 @@ md_status md_attach(md_system *s, int32_t slot, const md_replica *rep, const int
     if ((st = validate_rep(s, rep)) != MD_OK) return st;
     if (!pos || !vel || (!species && s->cfg.n_species == 2)) return fail(s, MD_E_ARG, "null input array");
     const int n = rep->n;
-    for (int64_t k = 0; k < 3LL * n; ++k)
-        if (!std::isfinite(pos[k]) || !std::isfinite(vel[k])) return fail(s, MD_E_NONFINITE, "non-finite input");
-    if (species)
-        for (int k = 0; k < n; ++k)
-            if (species[k] < 0 || species[k] >= s->cfg.n_species) return fail(s, MD_E_ARG, "species out of range");
     SlotHost h;
-    if ((st = alloc_slot_ranges(s, slot, n, rep->box, h)) != MD_OK) return st;
-    RepDev r = repdev_of(s, h);
-    const std::vector<int> rank = ranks_of(s, h);
-    const int NW = s->lay.NW, NS = s->lay.NS;
-    std::vector<uint4> w(3 * (size_t)n), sn(2 * (size_t)n);
-    std::vector<int4> mt(n);
-    std::vector<int> cell(n);
-    for (int k = 0; k < n; ++k) {
-        double x[3], v[3];
-        int img[3];
-        for (int d = 0; d < 3; ++d) {
-            double q = pos[3 * k + d];
-            double f = std::floor(q / h.L);
-            x[d] = q - f * h.L;
-            img[d] = (int)f;
-            if (x[d] >= h.L) { x[d] -= h.L; img[d] += 1; }
-            if (x[d] < 0) { x[d] += h.L; img[d] -= 1; }
-            v[d] = vel[3 * k + d];
-        }
-        uint32_t m = meta_word(slot, species ? species[k] : 0);
-        encode_particle(s, r, x, v, img, m, &w[3 * (size_t)k], &sn[2 * (size_t)k]);
-        mt[k] = make_int4(img[0], img[1], img[2], k);
-        cell[k] = sort_key(rank[cell_of_snap(s, r, &sn[2 * (size_t)k])], m, r.planes, r.nd);
-    }
-    // stable counting sort by species plane and cell
-    const int ncell = r.planes * h.nd * h.nd * h.nd;
-    HostRep hr;
-    hr.cs.assign(ncell + 1, 0);
-    for (int k = 0; k < n; ++k) hr.cs[cell[k] + 1]++;
-    for (int c = 0; c < ncell; ++c) hr.cs[c + 1] += hr.cs[c];
-    std::vector<int> pos_in(ncell);
-    for (int c = 0; c < ncell; ++c) pos_in[c] = hr.cs[c];
-    std::vector<int> order(n);
-    for (int k = 0; k < n; ++k) order[pos_in[cell[k]]++] = k;
-    for (int c = 0; c <= ncell; ++c) hr.cs[c] += (int)h.off;
-    for (int q = 0; q < NW; ++q) hr.st[q].resize(n);
-    hr.snap.resize((size_t)NS * n);
-    hr.meta.resize(n);
-    for (int k = 0; k < n; ++k) {
-        int o = order[k];
-        for (int q = 0; q < NW; ++q) hr.st[q][k] = w[3 * (size_t)o + q];
-        for (int q = 0; q < NS; ++q) hr.snap[(size_t)q * n + k] = sn[2 * (size_t)o + q];
-        hr.meta[k] = mt[o];
+    if ((st = alloc_slot_ranges(s, slot, n, rep->box, h)) != MD_OK) {
+        // no room to check the input on the device: a fault of the input goes
+        // before the lack of room, as it does there
+        const std::string why = s->err;
+        for (int64_t k = 0; k < 3LL * n; ++k)
+            if (!std::isfinite(pos[k]) || !std::isfinite(vel[k])) return fail(s, MD_E_NONFINITE, "non-finite input");
+        if (species)
+            for (int k = 0; k < n; ++k)
+                if (species[k] < 0 || species[k] >= s->cfg.n_species) return fail(s, MD_E_ARG, "species out of range");
+        s->err = why;
+        return st;
     }
     h.attached = true;
     h.target = 0;
     s->slots[slot] = h;
-    Ctl c = make_int4(0, 1, 1, 0);
-    st = upload_slot(s, slot, h, hr, nullptr, c, 1, 0);
-    if (st == MD_OK) st = finish_attach(s, slot);
+    st = attach_on_device(s, slot, h, species, pos, vel);
     if (st != MD_OK) {
         release_slot_ranges(s, s->slots[slot]);
         Ctl z = make_int4(0, 0, 0, 0);
         for (int p = 0; p < 2; ++p) (void)hipMemcpyAsync(s->ctl[p] + slot, &z, sizeof z, hipMemcpyHostToDevice, s->stream);
         (void)hipStreamSynchronize(s->stream);
+        const std::string why = s->err;
         upload_items(s);
+        s->err = why;
         return st;
     }
     return MD_OK;

@@ -146,6 +146,26 @@ hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
 hipError_t occupancy_permute(int prec, int *per_cu);
 hipError_t occupancy_build(int prec, int *per_cu);
+// A replica handed in as host arrays: by-id input rows on the device, the cell
+// tables and the arrays of the slot it becomes.
+struct AttachArgs {
+    KArena A;
+    int slot, off, n, ncell; // ncell: cells of every plane
+    RepDev rep;
+    const double *pos, *vel; // [n][3]
+    const int *species;      // [n], or null
+    int *key, *arrival;      // [n]: cell (sort key) of each particle, its place among the cell's arrivals
+    int *ids;                // [n]: particle ids by slot, unordered within a cell
+    const int *corder;
+    int *cs, *cs_new;
+    uint4 *snap0, *snap1, *cand;
+    // words of the slot
+    RepDev *reps;
+    Ctl *ctl0, *ctl1;
+    int *need0, *need1, *target, *status, *nreb, *chunks;
+    int max_slots, n_species;
+};
+hipError_t launch_attach(int prec, const AttachArgs &a, hipStream_t s);
 hipError_t launch_frame(int prec, const FrameArgs &a, hipStream_t s);
 hipError_t launch_words_out(const uint4 *src, uint4 *dst, int n, hipStream_t s);
 hipError_t launch_poll(const Ctl *ctl, const int *status, const int *nreb, SlotWords *out, int max_slots, hipStream_t s);

@@ -127,6 +127,9 @@ __host__ __device__ __forceinline__ double bits_of_meta(uint32_t m)
 // C ABI): list overflow, non-finite position, lost particles, unpaddable
 // list.  Any of them stops the replica.
 #define ST_HALT (1 | 2 | 4 | 8)
+// Set while a replica is attached: its input is refused.
+#define ST_BAD_INPUT (1 << 16)   // a position or velocity is not finite
+#define ST_BAD_SPECIES (1 << 17) // a species is out of range
 
 #define SLOT_SHIFT 4
 #define MAX_ARENA_SLOTS (1 << 28) // list entries are 32-bit byte offsets (slot x 16)
