@@ -271,10 +271,10 @@ md_status md_forces(md_system *sys, int32_t slot, double *f_host, double *e_host
  * The launch that brings a replica to its full step keeps its forces, and the
  * next call's first launch uses them instead of evaluating forces again at
  * the same positions, so n calls of one step cost as many force passes as one
- * call of n steps, with bitwise the same trajectory.  md_rebuild_neighbours,
- * md_thermostat and, in double-single mode, md_forces and md_observables
- * (which overwrite the rows that hold them) drop the kept forces; the next
- * call then evaluates them. */
+ * call of n steps, with bitwise the same trajectory.  md_rebuild_neighbours
+ * and, in double-single mode, md_forces and md_observables (which overwrite
+ * the rows that hold them) drop the kept forces; the next call then evaluates
+ * them. */
 md_status md_step(md_system *sys, int64_t n_steps);
 
 /* Serving form: set the absolute step at which a replica stops
@@ -322,8 +322,8 @@ md_status md_thermostat(md_system *sys, int32_t slot, double temperature, uint64
 /* md_thermostat for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
  * Same arguments, same arithmetic and bitwise the same velocities as
- * md_thermostat, but it neither allocates nor touches the pool's scratch
- * rows (which md_forces results occupy): its per-call partial sums live in
+ * md_thermostat, and like it neither allocates nor touches the rows that
+ * md_forces results occupy; its per-call partial sums live in
  * a static device array inside the library, one per GPU, of at most 16384
  * chunks of 4096 particles, so a replica may hold at most 67,108,864
  * particles (else MD_E_CAPACITY, nothing launched).  The array is shared by

@@ -1005,6 +1005,30 @@ static md_status read_words(md_system *s, std::vector<SlotWords> &w, std::vector
     return MD_OK;
 }
 
+// The draws of a thermostat call go through the sort's scratch arrays, which
+// are free between rebuilds: the kept forces and md_forces' rows stay.
+static ThermoArgs thermo_args(const md_system *s, const SlotHost &h, double temperature, uint64_t seed, int64_t call,
+                              int32_t remove_mean, double *partial, int chunk0)
+{
+    ThermoArgs a;
+    memset(&a, 0, sizeof a);
+    a.A = arena_of(s);
+    a.drawn = (double *)s->sc_st[0]; // the scratch words lie one after another: 32 bytes a particle or more
+    a.partial = partial;
+    a.off = (int)h.off;
+    a.n = h.n;
+    a.chunk0 = chunk0;
+    a.nchunk = (h.n + 4095) / 4096;
+    a.remove_mean = remove_mean ? 1 : 0;
+    a.levels = h.n <= 1 << 8 ? 1 : h.n <= 1 << 16 ? 2 : h.n <= 1 << 24 ? 3 : 4;
+    const uint64_t x0 = ((seed & 0xFFFFFFFFULL) << 16) | 0x330EULL; // the state srand48(seed) sets
+    for (int r = 0; r < 4; ++r) a.x0[r] = rand48_jump(x0, (uint64_t)h.n * (4ULL * (uint64_t)call + r));
+    a.temperature = temperature;
+    a.mass = s->cfg.mass;
+    a.scale = std::sqrt(temperature / s->cfg.mass);
+    return a;
+}
+
 // The replica of a slot from the caller's host arrays: input by id into the
 // slot's observation rows (64 bytes a particle, unused until forces are kept),
 // conversion and sort on the device, first lists.
@@ -1443,24 +1467,8 @@ md_status md_thermostat(md_system *s, int32_t slot, double temperature, uint64_t
     int chunk0 = 0; // this slot's first row of chunk partials (4096 particles per chunk)
     for (int k = 0; k < slot; ++k)
         if (s->slots[k].attached) chunk0 += (s->slots[k].n + 4095) / 4096;
-    ThermoArgs a;
-    memset(&a, 0, sizeof a);
-    a.A = arena_of(s);
-    a.obs = s->obs;
-    a.partial = s->partial;
-    a.off = (int)h.off;
-    a.n = h.n;
-    a.chunk0 = chunk0;
-    a.nchunk = (h.n + 4095) / 4096;
-    a.remove_mean = remove_mean ? 1 : 0;
-    a.x0 = ((seed & 0xFFFFFFFFULL) << 16) | 0x330EULL; // the state srand48(seed) sets
-    a.call = call;
-    a.temperature = temperature;
-    a.mass = s->cfg.mass;
-    a.scale = std::sqrt(temperature / s->cfg.mass);
-    HIPCHK(s, launch_thermostat(s->prec, a, s->stream));
-    // the draws went through the scratch rows that hold stored forces
-    HIPCHK(s, launch_poke((int *)(s->ctl[s->parity] + slot) + 3, 0, s->stream));
+    HIPCHK(s, launch_thermostat(s->prec, thermo_args(s, h, temperature, seed, call, remove_mean, s->partial, chunk0),
+                                s->stream));
     return MD_OK;
 }
 
@@ -1468,36 +1476,19 @@ md_status md_thermostat_noalloc(md_system *s, int32_t slot, double temperature, 
                                 int32_t remove_mean)
 {
     // The same kernels and arithmetic as md_thermostat; the chunk partial
-    // sums go to the library's file-scope scratch array of this device, the
-    // drawn velocities are drawn again when applied, and nothing here
-    // allocates (host or device).
+    // sums go to the library's file-scope scratch array of this device, and
+    // nothing here allocates (host or device).
     md_status st = check_slot(s, slot, true);
     if (st != MD_OK) return st;
     if (!(temperature > 0) || !std::isfinite(temperature)) return fail(s, MD_E_ARG, "temperature must be positive");
     if (call < 0 || call > ((int64_t)1 << 40)) return fail(s, MD_E_ARG, "call index out of range");
     const SlotHost &h = s->slots[slot];
-    const int nchunk = (h.n + 4095) / 4096;
-    if (nchunk > THERMO_SCRATCH_CHUNKS)
+    if ((h.n + 4095) / 4096 > THERMO_SCRATCH_CHUNKS)
         return fail(s, MD_E_CAPACITY, "md_thermostat_noalloc: %d particles exceed its scratch limit of %d",
                     h.n, THERMO_SCRATCH_CHUNKS * 4096);
     double *scr = thermo_scratch(s->dev);
     if (!scr) return fail(s, MD_E_STATE, "scratch array of device %d not set up", s->dev);
-    ThermoArgs a;
-    memset(&a, 0, sizeof a);
-    a.A = arena_of(s);
-    a.obs = nullptr;
-    a.partial = scr;
-    a.off = (int)h.off;
-    a.n = h.n;
-    a.chunk0 = 0;
-    a.nchunk = nchunk;
-    a.remove_mean = remove_mean ? 1 : 0;
-    a.x0 = ((seed & 0xFFFFFFFFULL) << 16) | 0x330EULL;
-    a.call = call;
-    a.temperature = temperature;
-    a.mass = s->cfg.mass;
-    a.scale = std::sqrt(temperature / s->cfg.mass);
-    HIPCHK(s, launch_thermostat(s->prec, a, s->stream));
+    HIPCHK(s, launch_thermostat(s->prec, thermo_args(s, h, temperature, seed, call, remove_mean, scr, 0), s->stream));
     return MD_OK;
 }
 

@@ -162,37 +162,55 @@ __global__ void k_scale_vel(const ScaleArgs a)
 
 // ------------------------------------------------------------ thermostat
 // rand48 (Sec. 2.3): x_{k+1} = (a x_k + c) mod 2^48.  Element j from x0 is
-// A_j x0 + C_j, the j-fold composition of the affine map, by repeated
-// squaring; particle id i at call k takes elements i + n (4k + r), r = 0..3
-// (the leap-frog of stride n over the particles), so no generator state is
-// stored and the draws do not depend on slot order or launch shape.
-#define R48_A 0x5DEECE66DULL
-#define R48_C 0xBULL
-#define R48_M ((1ULL << 48) - 1ULL)
-
-__device__ __forceinline__ unsigned long long r48_element(unsigned long long x0, unsigned long long j)
+// A_j x0 + C_j, the j-fold composition of the affine map; particle id i at
+// call k takes elements i + n (4k + r), r = 0..3 (the leap-frog of stride n
+// over the particles), so no generator state is stored and the draws do not
+// depend on slot order or launch shape.
+//
+// The host jumps to the elements n (4k + r) (rand48_jump); from there a
+// particle is i steps away, one table entry per byte of i, where jumping
+// from x0 by repeated squaring took 20 to 40 rounds of four products for
+// each of the four elements.
+#define TH_LEVELS 4 // ids are below 2^28
+struct R48Map { unsigned long long a, c; };
+struct R48Table { R48Map m[TH_LEVELS][256]; };
+constexpr R48Map r48_then(const R48Map &f, const R48Map &g) // f, then g
 {
-    unsigned long long A = 1, C = 0, a = R48_A, c = R48_C;
-    while (j) {
-        if (j & 1) { A = (a * A) & R48_M; C = (a * C + c) & R48_M; }
-        c = (a * c + c) & R48_M;
-        a = (a * a) & R48_M;
-        j >>= 1;
-    }
-    return (A * x0 + C) & R48_M;
+    return {(g.a * f.a) & R48_M, (g.a * f.c + g.c) & R48_M};
 }
+constexpr R48Table make_r48_table()
+{
+    R48Table t{};
+    R48Map step{R48_A, R48_C}; // 256^l steps
+    for (int l = 0; l < TH_LEVELS; ++l) {
+        R48Map m{1, 0};
+        for (int k = 0; k < 256; ++k) {
+            t.m[l][k] = m;
+            m = r48_then(m, step);
+        }
+        step = m;
+    }
+    return t;
+}
+__device__ const R48Table r48_table = make_r48_table();
 
 #define TH_CHUNK 4096
 
 // The Maxwell-Boltzmann velocity of particle id at this call (Box-Muller on
 // four leap-frogged rand48 elements); a pure function of (seed, call, id).
-__device__ __noinline__ void thermo_velocity(const ThermoArgs &a, int id, double v[3])
+__device__ __forceinline__ void thermo_velocity(const ThermoArgs &a, int id, double v[3])
 {
-    const unsigned long long base = (unsigned long long)id + (unsigned long long)a.n * (4ULL * a.call);
+    unsigned long long x[4] = {a.x0[0], a.x0[1], a.x0[2], a.x0[3]};
+#pragma unroll
+    for (int l = 0; l < TH_LEVELS; ++l) {
+        if (l >= a.levels) break;
+        const R48Map m = r48_table.m[l][(id >> (8 * l)) & 255];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = m.a * x[r] + m.c; // (masked below: only the low 48 bits count)
+    }
     double u[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        u[r] = (double)r48_element(a.x0, base + (unsigned long long)a.n * r) * (1.0 / 281474976710656.0);
+    for (int r = 0; r < 4; ++r) u[r] = (double)(x[r] & R48_M) * (1.0 / 281474976710656.0);
     const double ra = sqrt(-2.0 * log(1.0 - u[0])), rb = sqrt(-2.0 * log(1.0 - u[2]));
     const double ph = 6.283185307179586 * u[1], ph2 = 6.283185307179586 * u[3];
     v[0] = a.scale * ra * cos(ph);
@@ -200,28 +218,36 @@ __device__ __noinline__ void thermo_velocity(const ThermoArgs &a, int id, double
     v[2] = a.scale * rb * cos(ph2);
 }
 
-// Draw Maxwell-Boltzmann velocities into the scratch rows (when a.obs is
-// set; the allocation-free form draws them again when it applies them) and
-// reduce sum(v) and sum(v^2) per chunk of TH_CHUNK particles into
-// a.partial[(chunk0 + c) * 8 + q].
+// Draw Maxwell-Boltzmann velocities into the sort's scratch state words
+// (three doubles per slot), one thread a particle; a slot without a particle
+// of the replica gets none.
 __global__ void __launch_bounds__(256) k_thermo_draw(const ThermoArgs a)
+{
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= a.n) return;
+    const int id = a.A.meta[a.off + k].w;
+    double v[3] = {0, 0, 0};
+    if (id >= 0 && id < a.n) thermo_velocity(a, id, v);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) a.drawn[3 * (size_t)k + d] = v[d];
+}
+
+// sum(v) and sum(v^2) per chunk of TH_CHUNK particles into a.partial[(chunk0 +
+// c) * 8 + q]: each thread adds every 256th particle in order, then a tree.
+__global__ void __launch_bounds__(256) k_thermo_sum(const ThermoArgs a)
 {
     __shared__ double red[4][256];
     const int c = blockIdx.x;
     const int k0 = c * TH_CHUNK, k1 = min(k0 + TH_CHUNK, a.n);
     double acc[4] = {0, 0, 0, 0};
-    for (int k = k0 + threadIdx.x; k < k1; k += blockDim.x) {
-        const int i = a.off + k;
-        const int id = a.A.meta[i].w;
+#pragma unroll 4
+    for (int k = k0 + threadIdx.x; k < k1; k += 256) {
+        const int id = a.A.meta[a.off + k].w;
+        const double *v = a.drawn + 3 * (size_t)k;
+        const double x = v[0], y = v[1], z = v[2];
         if (id < 0 || id >= a.n) continue;
-        double v[3];
-        thermo_velocity(a, id, v);
-        if (a.obs) {
-            double *o = a.obs + (size_t)i * 8;
-            o[0] = v[0]; o[1] = v[1]; o[2] = v[2];
-        }
-        acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2];
-        acc[3] += v[0] * v[0] + v[1] * v[1] + v[2] * v[2];
+        acc[0] += x; acc[1] += y; acc[2] += z;
+        acc[3] += x * x + y * y + z * z;
     }
     for (int q = 0; q < 4; ++q) red[q][threadIdx.x] = acc[q];
     __syncthreads();
@@ -239,13 +265,22 @@ __global__ void __launch_bounds__(256) k_thermo_draw(const ThermoArgs a)
 template <int P>
 __global__ void __launch_bounds__(256) k_thermo_apply(const ThermoArgs a)
 {
-    __shared__ double tot[4];
-    if (threadIdx.x < 4) {
-        double t = 0;
-        for (int c = 0; c < a.nchunk; ++c) t += a.partial[(size_t)(a.chunk0 + c) * 8 + threadIdx.x];
-        tot[threadIdx.x] = t;
+    __shared__ double rows[256][4];
+    double t = 0;
+    for (int c0 = 0; c0 < a.nchunk; c0 += 256) {
+        const int m = min(256, a.nchunk - c0);
+        if ((int)threadIdx.x < m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rows[threadIdx.x][q] = a.partial[(size_t)(a.chunk0 + c0 + threadIdx.x) * 8 + q];
+        __syncthreads();
+        if (threadIdx.x < 4)
+#pragma unroll 8
+            for (int c = 0; c < m; ++c) t += rows[c][threadIdx.x];
+        __syncthreads();
     }
+    if (threadIdx.x < 4) rows[0][threadIdx.x] = t;
     __syncthreads();
+    const double *tot = rows[0];
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     const double n = (double)a.n;
@@ -255,15 +290,9 @@ __global__ void __launch_bounds__(256) k_thermo_apply(const ThermoArgs a)
     const double ss = tot[3] - n * (mean[0] * mean[0] + mean[1] * mean[1] + mean[2] * mean[2]);
     const double f = sqrt(a.temperature / (a.mass * ss / (3.0 * n)));
     const int i = a.off + k;
-    double w[3];
-    if (a.obs) {
-        const double *o = a.obs + (size_t)i * 8;
-        w[0] = o[0]; w[1] = o[1]; w[2] = o[2];
-    } else { // allocation-free form: the same draw again (a pure function of the id)
-        const int id = a.A.meta[i].w;
-        if (id < 0 || id >= a.n) return;
-        thermo_velocity(a, id, w);
-    }
+    const int id = a.A.meta[i].w;
+    if (id < 0 || id >= a.n) return;
+    const double *w = a.drawn + 3 * (size_t)k;
     const double v[3] = {(w[0] - mean[0]) * f, (w[1] - mean[1]) * f, (w[2] - mean[2]) * f};
     State<P> st;
     st.load(a.A, i);
@@ -284,8 +313,9 @@ __global__ void __launch_bounds__(256) k_thermo_apply(const ThermoArgs a)
 hipError_t launch_thermostat(int prec, const ThermoArgs &a, hipStream_t s)
 {
     if (a.n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_thermo_draw, dim3(a.nchunk), dim3(256), 0, s, a);
     const int grid = (a.n + 255) / 256;
+    hipLaunchKernelGGL(k_thermo_draw, dim3(grid), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_thermo_sum, dim3(a.nchunk), dim3(256), 0, s, a);
     switch (prec) {
     case PREC_FP32: hipLaunchKernelGGL((k_thermo_apply<PREC_FP32>), dim3(grid), dim3(256), 0, s, a); break;
     case PREC_DS: hipLaunchKernelGGL((k_thermo_apply<PREC_DS>), dim3(grid), dim3(256), 0, s, a); break;
@@ -298,9 +328,7 @@ hipError_t launch_thermostat(int prec, const ThermoArgs &a, hipStream_t s)
 // ------------------------------------------- allocation-free thermostat
 // For callers that cannot allocate device memory (code under graph capture,
 // tight serving loops): the chunk partial sums of md_thermostat_noalloc live
-// in this file-scope device array instead of the pool's workspace, and the
-// drawn velocities are not stored at all (they are drawn again when
-// applied).  Each GPU holds its own copy; host code must use the address
+// in this file-scope device array instead of the pool's workspace.  Each GPU holds its own copy; host code must use the address
 // hipGetSymbolAddress returns for the current device, never the array's
 // name.  Every chunk row a call reads was written by the same call, so
 // nothing needs clearing; calls that overlap on one GPU race on it.

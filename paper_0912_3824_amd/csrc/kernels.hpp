@@ -122,15 +122,30 @@ struct ScaleArgs {
 // stride n over the replica's particles.
 struct ThermoArgs {
     KArena A;
-    double *obs;      // per-slot scratch rows (8 doubles); velocities drawn here
-                      // (nullptr: drawn again when applied, nothing stored)
+    double *drawn;    // [n][3] drawn velocities, by slot (the sort's scratch state words)
     double *partial;  // chunk partial sums (8 doubles per chunk)
-    int off, n, chunk0, nchunk, remove_mean, pad0;
-    unsigned long long x0; // rand48 state of the seed (stream element 0)
-    long long call;        // thermostat call index
-    double scale;          // sqrt(T / m)
+    int off, n, chunk0, nchunk, remove_mean;
+    int levels;       // bytes of the largest particle id
+    unsigned long long x0[4]; // rand48 elements n (4 call + r), r = 0..3, from the seed's
+    double scale;             // sqrt(T / m)
     double temperature, mass;
 };
+
+// rand48's affine map and the element j steps from x0 (A_j x0 + C_j by
+// repeated squaring).
+#define R48_A 0x5DEECE66DULL
+#define R48_C 0xBULL
+#define R48_M ((1ULL << 48) - 1ULL)
+inline unsigned long long rand48_jump(unsigned long long x0, unsigned long long j)
+{
+    unsigned long long A = 1, C = 0, a = R48_A, c = R48_C;
+    for (; j; j >>= 1) {
+        if (j & 1) { A = (a * A) & R48_M; C = (a * C + c) & R48_M; }
+        c = (a * c + c) & R48_M;
+        a = (a * a) & R48_M;
+    }
+    return (A * x0 + C) & R48_M;
+}
 
 hipError_t launch_thermostat(int prec, const ThermoArgs &a, hipStream_t s);
 // Chunk rows of the allocation-free thermostat's scratch array (aux_kernels.hip):
