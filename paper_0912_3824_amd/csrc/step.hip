@@ -301,42 +301,50 @@ __device__ __forceinline__ void force_fixed(const KArena &A, const uint4 *__rest
 }
 
 // FP64 path: double snapshots, textbook minimum image, FP64 pair term
-// (smoothed as in entry_fixed when SMOOTH).
+// (smoothed as in entry_fixed when SMOOTH).  Two gathers of 16 bytes an entry
+// through the texture pipeline bound it at 200,000 particles and more; small
+// systems wait for the list rows and the snapshots in turn, so the rows are
+// read two blocks ahead.
 template <bool SMOOTH>
 __device__ __forceinline__ void force_dbl(const KArena &A, const uint4 *__restrict__ snap, int i,
                                           double xi, double yi, double zi, int si, const RepDev &r,
                                           const PairDev &pp, double &fx, double &fy, double &fz,
-                                          bool en, double &e_sum, double &w_sum, int sub, int lpp)
+                                          bool en, double &e_sum, double &w_sum, int sub, int lpp,
+                                          const ListHead &h)
 {
-    const int cnt = A.nbr_cnt[i];
-    const size_t P_ = (size_t)A.P;
-    const uint4 *__restrict__ snap1 = snap + P_;
+    const uint4 *__restrict__ snap1 = snap + (size_t)A.P;
     fx = fy = fz = 0.0;
+    const int nq = h.nq;
+    if (sub >= nq) return;
     double rc2[2], sig2[2], e24[2];
     rc2[0] = pp.rc2d[si * 2]; rc2[1] = pp.rc2d[si * 2 + 1];
     sig2[0] = pp.sig2d[si * 2]; sig2[1] = pp.sig2d[si * 2 + 1];
     e24[0] = pp.eps24d[si * 2]; e24[1] = pp.eps24d[si * 2 + 1];
-    const int nq = list_rows(cnt, A.lg); // rows of four (a partial group is completed by padding)
+    const int last = nq - 1;
+    int4 jj = h.r0, jn = h.r1;
     for (int q = sub; q < nq; q += lpp) {
-        const int4 jj = list_row(A, i, q);
         const int js[4] = {jj.x, jj.y, jj.z, jj.w};
+        uint4 xa[4], xb[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = list_slot(js[u]); // padding entries lie beyond the cutoff
+        for (int u = 0; u < 4; ++u) { xa[u] = ld_snap(snap, js[u]); xb[u] = ld_snap(snap1, js[u]); }
+        jj = jn;
+        jn = list_row(A, i, min(q + 2 * lpp, last));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { // padding entries lie beyond the cutoff
             double xj, yj, zj, wj;
-            u4_to_dbl2(snap[j], xj, yj);
-            u4_to_dbl2(snap1[j], zj, wj);
+            u4_to_dbl2(xa[u], xj, yj);
+            u4_to_dbl2(xb[u], zj, wj);
             double dx = xi - xj, dy = yi - yj, dz = zi - zj;
             dx -= r.L * rint(dx * r.invL);
             dy -= r.L * rint(dy * r.invL);
             dz -= r.L * rint(dz * r.invL);
-            double r2 = dx * dx + dy * dy + dz * dz;
-            int b = species_of(meta_of_bits(wj));
-            double ir2 = 1.0 / r2;
-            double s2 = sig2[b] * ir2;
-            double s6 = s2 * s2 * s2;
+            const double r2 = dx * dx + dy * dy + dz * dz;
+            const int b = species_of(meta_of_bits(wj));
+            const double ir2 = 1.0 / r2;
+            const double s2 = sig2[b] * ir2;
+            const double s6 = s2 * s2 * s2;
             double ff = e24[b] * ir2 * s6 * (2.0 * s6 - 1.0);
-            bool in = r2 < rc2[b];
+            const bool in = r2 < rc2[b];
             double vs = 0.0;
             if (en || SMOOTH) {
                 const int tt = si * 2 + b;
@@ -416,8 +424,7 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
     // control words are known (in bounds for every slot of the arena)
     State<P> st;
     st.load(A, i);
-    ListHead lh;
-    if constexpr (P != PREC_FP64) lh = list_head(A, i, sub, LPP);
+    const ListHead lh = list_head(A, i, sub, LPP);
 
     uint4 s0 = a.snap_cur[i];
     uint4 s1;
@@ -493,7 +500,7 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
             fxd = ost[0]; fyd = ost[1]; fzd = ost[2];
         } else {
             force_dbl<KIND == PK_SMOOTH>(A, a.snap_cur, i, xi, yi, zi, si, rp, a.pp, fxd, fyd, fzd, OBS, e_sum,
-                                         w_sum, sub, LPP);
+                                         w_sum, sub, LPP, lh);
 #pragma unroll
             for (int m = 1; m < LPP; m <<= 1) {
                 lane_sum(fxd, m); lane_sum(fyd, m); lane_sum(fzd, m);
