@@ -99,7 +99,7 @@ struct md_system {
     int *corder = nullptr, *corder_inv = nullptr; // per-replica cell rank tables and their inverses (cell arena offsets)
     RepDev *rep = nullptr;
     Ctl *ctl[2]{};
-    int *target = nullptr, *need[2]{}, *rlist[2]{}, *status = nullptr, *nreb = nullptr;
+    int *target = nullptr, *need[2]{}, *rlist[2]{}, *sync[2]{}, *status = nullptr, *nreb = nullptr;
     int *chunks = nullptr;
     double *partial = nullptr;
     uint4 *stage = nullptr;         // stage_bytes: small read-backs on their way to `pin`
@@ -268,6 +268,8 @@ static int64_t carve(md_system *s, const Layout &L, char *base)
     d->need[1] = c.take<int>(L.slots);
     d->rlist[0] = c.take<int>(L.slots + 1);
     d->rlist[1] = c.take<int>(L.slots + 1);
+    d->sync[0] = c.take<int>(SYNC_WORDS);
+    d->sync[1] = c.take<int>(SYNC_WORDS);
     d->status = c.take<int>(L.slots);
     d->nreb = c.take<int>(L.slots);
     d->chunks = c.take<int>(L.slots + 1);
@@ -443,6 +445,7 @@ static StepArgs step_args(const md_system *s, int p)
     a.need_other = s->need[p ^ 1];
     a.rlist_cur = s->rlist[p];
     a.rlist_other = s->rlist[p ^ 1];
+    a.sync_other = s->sync[p ^ 1];
     a.count_cur = s->count[p];
     a.count_other = s->count[p ^ 1];
     a.corder = s->corder;
@@ -453,8 +456,16 @@ static StepArgs step_args(const md_system *s, int p)
     return a;
 }
 
-// The two rebuild launches that follow a step of parity p: the replicas on
-// its rebuild list are sorted and their lists built.
+// One rebuild launch instead of two (k_rebuild) for pools of one slot up to
+// this size.  With several slots some replica rebuilds every few steps, and the
+// barrier in the kernel costs those steps more (5 to 30 us) than the idle
+// launch that the others save (1.5 us); for one slot both forms take the same
+// time at 64,000 particles, which rebuild every 25 steps.
+#define ONE_REBUILD_MAX 49152
+static bool one_rebuild(const md_system *s) { return s->lay.slots == 1 && s->lay.P <= ONE_REBUILD_MAX; }
+
+// The rebuild launches that follow a step of parity p: the replicas on its
+// rebuild list are sorted and their lists built.
 static md_status launch_rebuild(md_system *s, int p)
 {
     const int prec = s->prec;
@@ -475,7 +486,6 @@ static md_status launch_rebuild(md_system *s, int p)
     pa.cand = s->cand;
     pa.status = s->status;
     pa.nreb = s->nreb;
-    HIPCHK(s, launch_permute(prec, pa, s->grid_perm, s->stream));
 
     BuildArgs ba;
     memset(&ba, 0, sizeof ba);
@@ -494,6 +504,11 @@ static md_status launch_rebuild(md_system *s, int p)
     ba.sc_meta = s->sc_meta;
     ba.status = s->status;
     ba.pp = s->pp;
+    if (one_rebuild(s)) {
+        HIPCHK(s, launch_rebuild_one(prec, pa, ba, s->sync[p], s->grid_build, s->stream));
+        return MD_OK;
+    }
+    HIPCHK(s, launch_permute(prec, pa, s->grid_perm, s->stream));
     HIPCHK(s, launch_build(prec, ba, s->grid_build, s->stream));
     return MD_OK;
 }
@@ -504,7 +519,7 @@ static md_status launch_rebuild(md_system *s, int p)
 static md_status launch_build_main(md_system *s, int slot, bool make_cand)
 {
     int *rlist = s->rlist[s->parity ^ 1];
-    HIPCHK(s, launch_enlist(rlist, s->ctl[0], (int)s->lay.slots, slot, s->stream));
+    HIPCHK(s, launch_enlist(rlist, s->sync[s->parity ^ 1], s->ctl[0], (int)s->lay.slots, slot, s->stream));
     BuildArgs ba;
     memset(&ba, 0, sizeof ba);
     ba.A = arena_of(s);
@@ -1210,6 +1225,7 @@ md_status md_create(const md_config *cfg, void *workspace, int64_t ws_bytes, voi
         if (!done(hipMemsetAsync(s->ctl[p], 0, sizeof(Ctl) * L.slots, st))) return MD_E_HIP;
         if (!done(hipMemsetAsync(s->need[p], 0, 4 * L.slots, st))) return MD_E_HIP;
         if (!done(hipMemsetAsync(s->rlist[p], 0, 4 * (L.slots + 1), st))) return MD_E_HIP;
+        if (!done(hipMemsetAsync(s->sync[p], 0, 4 * SYNC_WORDS, st))) return MD_E_HIP;
     }
     if (!done(hipMemsetAsync(s->target, 0, 4 * L.slots, st))) return MD_E_HIP;
     if (!done(hipMemsetAsync(s->status, 0, 4 * L.slots, st))) return MD_E_HIP;
@@ -1327,7 +1343,7 @@ md_status md_rebuild_neighbours(md_system *s)
     ca.count = s->count[kp];
     ca.corder = s->corder;
     HIPCHK(s, launch_count(s->prec, ca, s->stream));
-    HIPCHK(s, launch_enlist(s->rlist[kp], s->ctl[p], (int)s->lay.slots, -1, s->stream));
+    HIPCHK(s, launch_enlist(s->rlist[kp], s->sync[kp], s->ctl[p], (int)s->lay.slots, -1, s->stream));
     // the rebuild kernels of a step of parity kp read snap[kp ^ 1] == snap[p]
     return launch_rebuild(s, kp);
 }

@@ -5,7 +5,8 @@
 // Overview of the kernels (step.hip, rebuild.hip, aux_kernels.hip):
 //
 // One MD step (Sec. 2.2, velocity Verlet with Verlet lists) is one fused
-// launch of k_step plus two rebuild kernels that exit at once unless the
+// launch of k_step plus two rebuild kernels (one, k_rebuild, in small pools of
+// one slot) that exit at once unless the
 // replica's maximum displacement since its last list build exceeded skin/2:
 //
 //   k_step<P>    per particle: force over its Verlet list (FP32 pair term,
@@ -103,6 +104,20 @@ __device__ __forceinline__ void for_items(const int *rlist, N items, int unit, i
             cum += n;
         }
     }
+}
+
+// A uniform index into memory that no kernel writes while this one runs:
+// scalar loads.
+template <class T> __device__ __forceinline__ T ld_uniform(const T *p, int k)
+{
+    typedef const __attribute__((address_space(4))) int CW;
+    struct Words { int w[sizeof(T) / 4]; } v;
+    CW *q = (CW *)(uintptr_t)(p + k);
+#pragma unroll
+    for (unsigned u = 0; u < sizeof(T) / 4; ++u) v.w[u] = q[u];
+    T t;
+    __builtin_memcpy(&t, &v, sizeof t);
+    return t;
 }
 
 __device__ __forceinline__ uint4 dbl2_to_u4(double a, double b)

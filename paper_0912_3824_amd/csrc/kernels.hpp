@@ -29,6 +29,7 @@ struct StepArgs {
     const int *target;
     int *need_cur, *need_other;
     int *rlist_cur, *rlist_other; // [0] = count, [1..] = slots that must rebuild
+    int *sync_other; // counters of the one-launch rebuild, cleared with rlist_other
     int *count_cur, *count_other;
     const int *corder; // per-replica cell rank tables (cell arena offsets)
     int *status;
@@ -36,6 +37,12 @@ struct StepArgs {
     PairDev pp;
     IntegDev ig;
 };
+
+// Counters of the one-launch rebuild (k_rebuild): a cache line each, SYNC_GROUPS
+// of sort units taken, then SYNC_GROUPS of sort units done.
+#define SYNC_GROUPS 8
+#define SYNC_STRIDE 32
+#define SYNC_WORDS (2 * SYNC_GROUPS * SYNC_STRIDE)
 
 struct CountArgs {
     int P, max_slots;
@@ -155,8 +162,9 @@ hipError_t thermo_scratch_init(int dev); // once per device, with that device cu
 double *thermo_scratch(int dev);         // its device address (nullptr before init)
 hipError_t launch_step(int prec, const StepArgs &a, int block, int n_cu, bool obs, hipStream_t s);
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
-hipError_t launch_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
+hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
 hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s);
+hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s);
 hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
 hipError_t occupancy_permute(int prec, int *per_cu);

@@ -34,9 +34,11 @@ __global__ void k_count(const CountArgs a)
 // ------------------------------------------------------------ k_enlist
 // Rebuild list of a rebuild or list build asked for by the host: `slot`, or
 // every attached slot (slot < 0).
-__global__ void __launch_bounds__(64) k_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot)
+__global__ void __launch_bounds__(64) k_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots,
+                                               int slot)
 {
     const int lane = threadIdx.x;
+    if (lane < SYNC_WORDS / SYNC_STRIDE) sync[lane * SYNC_STRIDE] = 0;
     int cnt = 0;
     for (int base = 0; base < max_slots; base += 64) {
         const int s = base + lane;
@@ -299,78 +301,99 @@ __device__ __forceinline__ int thread_sum(const int *count, int n)
 // VGPRs) instead of the 4 its unconstrained register use allows; its grid
 // takes one full residency at that occupancy.  The FP32 and MIXED64 forms
 // would spill at 80 VGPRs and keep their own allocation.
+struct PermBlockLds {
+    PermLds wave[PERM_BLOCK / 64];
+    int red[3][PERM_BLOCK / 64];
+};
+
+// Cells per sort unit and sort units of a replica of nc cells, for a grid of
+// nblk blocks.
+__device__ __forceinline__ int perm_range(int nc, int nblk)
+{
+    constexpr int WPB = PERM_BLOCK / 64;
+    return WPB * ((nc + WPB * nblk - 1) / (WPB * nblk));
+}
+__device__ __forceinline__ int perm_units(int nc, int nblk)
+{
+    const int range = perm_range(nc, nblk);
+    return (nc + range - 1) / range;
+}
+
+template <int P>
+__device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp, PermBlockLds &lds, int s, int item, int nblk)
+{
+    constexpr int WPB = PERM_BLOCK / 64;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nd = rp.nd, nc = nd * nd * nd, range = perm_range(nc, nblk);
+    const bool two = rp.planes > 1;
+    const int c0 = item * range, c1 = min(nc, c0 + range);
+    const int *cnt = a.count + rp.coff;
+    int *out = a.cs_new + rp.coff;
+    // members before the range: of plane 0; of plane 0 in all and of plane 1
+    int sum[3] = {thread_sum(cnt, c0), 0, 0};
+    if (two) {
+        sum[1] = thread_sum(cnt + c0, nc - c0);
+        sum[2] = thread_sum(cnt + nc, c0);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) sum[q] += __shfl_xor(sum[q], o, 64);
+        if (lane == 0) lds.red[q][wv] = sum[q];
+    }
+    __syncthreads();
+    int base[2] = {0, 0};
+#pragma unroll
+    for (int w = 0; w < WPB; ++w) {
+        base[0] += lds.red[0][w];
+        base[1] += lds.red[1][w] + lds.red[2][w];
+    }
+    base[1] = rp.off + base[0] + base[1];
+    base[0] += rp.off;
+    for (int b = c0; b < c1; b += 64) {
+        const int k = b + lane;
+        const int n0 = k < c1 ? cnt[k] : 0, n1 = two && k < c1 ? cnt[nc + k] : 0;
+        int i0 = n0, i1 = n1;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(i0, o, 64), y = __shfl_up(i1, o, 64);
+            if (lane >= o) { i0 += x; i1 += y; }
+        }
+        const int s0 = base[0] + i0 - n0, s1 = base[1] + i1 - n1;
+        if (wv == 0 && k < c1) {
+            out[k] = s0;
+            if (two) out[nc + k] = s1;
+        }
+        for (int q = wv; q < min(64, c1 - b); q += WPB) {
+            const int cell = rp.curve ? a.corder_inv[rp.coff + b + q] : b + q;
+            permute_cell<P>(a, rp, lds.wave[wv], s, cell, __builtin_amdgcn_readlane(s0, q),
+                            __builtin_amdgcn_readlane(n0, q), __builtin_amdgcn_readlane(s1, q),
+                            __builtin_amdgcn_readlane(n1, q));
+        }
+        base[0] += __builtin_amdgcn_readlane(i0, 63);
+        base[1] += __builtin_amdgcn_readlane(i1, 63);
+    }
+    if (c1 == nc && threadIdx.x == 0) { // the last range knows the sum
+        const int end = two ? base[1] : base[0];
+        out[two ? 2 * nc : nc] = end;
+        if (end - rp.off != rp.n) atomicOr(a.status + s, 4 | 2);
+        a.nreb[s] += 1;
+    }
+    __syncthreads();
+}
+
 template <int P>
 __global__ void __launch_bounds__(PERM_BLOCK)
 __attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 1))) k_permute(const PermArgs a)
 {
-    __shared__ PermLds lds[PERM_BLOCK / 64];
-    __shared__ int red[3][PERM_BLOCK / 64];
-    constexpr int WPB = PERM_BLOCK / 64;
-    const int lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    auto range_of = [&](int nc) { return WPB * ((nc + WPB * (int)gridDim.x - 1) / (WPB * (int)gridDim.x)); };
-    for_items(a.rlist, [&](int sl) {
-        const int nc = a.rep[sl].items3, range = range_of(nc);
-        return (nc + range - 1) / range;
-    }, blockIdx.x, gridDim.x, [&](int s, int item) {
-        const RepDev rp = a.rep[s];
-        const int nd = rp.nd, nc = nd * nd * nd, range = range_of(nc);
-        const bool two = rp.planes > 1;
-        const int c0 = item * range, c1 = min(nc, c0 + range);
-        const int *cnt = a.count + rp.coff;
-        int *out = a.cs_new + rp.coff;
-        // members before the range: of plane 0; of plane 0 in all and of plane 1
-        int sum[3] = {thread_sum(cnt, c0), 0, 0};
-        if (two) {
-            sum[1] = thread_sum(cnt + c0, nc - c0);
-            sum[2] = thread_sum(cnt + nc, c0);
-        }
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) sum[q] += __shfl_xor(sum[q], o, 64);
-            if (lane == 0) red[q][wv] = sum[q];
-        }
-        __syncthreads();
-        int base[2] = {0, 0};
-#pragma unroll
-        for (int w = 0; w < WPB; ++w) {
-            base[0] += red[0][w];
-            base[1] += red[1][w] + red[2][w];
-        }
-        base[1] = rp.off + base[0] + base[1];
-        base[0] += rp.off;
-        for (int b = c0; b < c1; b += 64) {
-            const int k = b + lane;
-            const int n0 = k < c1 ? cnt[k] : 0, n1 = two && k < c1 ? cnt[nc + k] : 0;
-            int i0 = n0, i1 = n1;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int x = __shfl_up(i0, o, 64), y = __shfl_up(i1, o, 64);
-                if (lane >= o) { i0 += x; i1 += y; }
-            }
-            const int s0 = base[0] + i0 - n0, s1 = base[1] + i1 - n1;
-            if (wv == 0 && k < c1) {
-                out[k] = s0;
-                if (two) out[nc + k] = s1;
-            }
-            for (int q = wv; q < min(64, c1 - b); q += WPB) {
-                const int cell = rp.curve ? a.corder_inv[rp.coff + b + q] : b + q;
-                permute_cell<P>(a, rp, lds[wv], s, cell, __builtin_amdgcn_readlane(s0, q),
-                                __builtin_amdgcn_readlane(n0, q), __builtin_amdgcn_readlane(s1, q),
-                                __builtin_amdgcn_readlane(n1, q));
-            }
-            base[0] += __builtin_amdgcn_readlane(i0, 63);
-            base[1] += __builtin_amdgcn_readlane(i1, 63);
-        }
-        if (c1 == nc && threadIdx.x == 0) { // the last range knows the sum
-            const int end = two ? base[1] : base[0];
-            out[two ? 2 * nc : nc] = end;
-            if (end - rp.off != rp.n) atomicOr(a.status + s, 4 | 2);
-            a.nreb[s] += 1;
-        }
-        __syncthreads();
-    });
+    __shared__ PermBlockLds lds;
+    const int nblk = gridDim.x;
+    for_items(a.rlist, [&](int sl) { return perm_units(a.rep[sl].items3, nblk); }, blockIdx.x, nblk,
+              [&](int s, int item) {
+                  const RepDev rp = a.rep[s];
+                  permute_item<P>(a, rp, lds, s, item, nblk);
+              });
 }
 
 // ------------------------------------------------------------ k_build
@@ -862,9 +885,8 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
 }
 
 template <int P>
-__device__ __forceinline__ void build_item(const BuildArgs &a, BuildLds &W, int s, int item)
+__device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, int s, int item)
 {
-    const RepDev rp = a.rep[s];
     const int lane = __lane_id();
     const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes, items = rp.items4;
     const int *cs = a.cs_new + rp.coff;
@@ -938,7 +960,97 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
     const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for_items(a.rlist, [&](int sl) { return a.rep[sl].items4; },
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
-              [&](int s, int item) { build_item<P>(a, lds[wv], s, item); });
+              [&](int s, int item) {
+                  const RepDev rp = a.rep[s];
+                  build_item<P>(a, rp, lds[wv], s, item);
+              });
+}
+
+// ------------------------------------------------------------ k_rebuild
+// The sort and the list build in one launch, for small pools of one slot.
+//
+// An idle launch costs every step 1.5 us, so a small system pays more for the
+// second rebuild kernel than the barrier that replaces it costs the rare step
+// that rebuilds: 600 particles 14.3 -> 12.9 us a step, 4,000 in FP64 12.1 ->
+// 10.6, 10,000 in FP32 12.6 -> 11.2, 37,000 15.9 -> 15.2 (a rebuild there 77
+// -> 95 us).  At 64,000 the two are equal, 21.8 (a rebuild 90 -> 123 us): the
+// barrier's cost grows with the sort units, each of which writes its XCD's L2
+// back.  (In every thread instead of one wave a block that takes 50 us more.)
+//
+// The barrier needs no particular number of resident blocks.  Sort units are
+// taken from shared counters, by blocks that run, and no block waits while it
+// holds one.  A block waits for the units done; when that takes long it takes
+// what units are left itself, after which every unit is done or held by a
+// block at work on it.  (A count of polls ends the wait all the same, and the
+// replica is then halted.)  The counters are split over SYNC_GROUPS cache
+// lines: atomics on one address take 15 to 40 ns each.
+#define SYNC_POLLS 64     // polls (about 1 us each) before a waiting block helps
+#define SYNC_ROUNDS 65536 // rounds of that many polls before it gives up
+
+template <int P>
+__global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, const BuildArgs ba, int *sync)
+{
+    static_assert(PERM_BLOCK == BUILD_BLOCK, "the sort and the list build share the block");
+    constexpr int G = SYNC_GROUPS, WPB = BUILD_BLOCK / 64;
+    if (ba.rlist[0] == 0) return;
+    __shared__ union {
+        PermBlockLds perm;
+        BuildLds build[WPB];
+    } lds;
+    __shared__ int word;
+    const RepDev rp = ld_uniform(ba.rep, 0);
+    const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nblk = gridDim.x;
+    const int np = perm_units(rp.items3, nblk), nb = rp.items4; // sort units, list-build items
+    const int first = remap_block(blockIdx.x, nblk, ba.xcd) * WPB; // the block's first list-build item
+    int g = (int)(blockIdx.x % G), left = (int)blockIdx.x < np ? 1 : 0; // groups to take units from: g and on
+    for (int round = 0;;) {
+        __syncthreads(); // (word)
+        if (left > 0) {
+            if (threadIdx.x == 0)
+                word = __hip_atomic_fetch_add(sync + g * SYNC_STRIDE, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            const int unit = g + G * __builtin_amdgcn_readfirstlane(word);
+            if (unit < np) {
+                permute_item<P>(pa, rp, lds.perm, 0, unit, nblk);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0); // the wave's stores have reached the L2
+                __syncthreads();
+                if (wv == 0) { // one write-back for the block
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    if (lane == 0)
+                        __hip_atomic_fetch_add(sync + (G + g) * SYNC_STRIDE, 1, __ATOMIC_RELAXED,
+                                               __HIP_MEMORY_SCOPE_AGENT);
+                }
+                if (np <= nblk && round == 0) left = 0; // the other blocks take one each
+            } else {
+                --left;
+                g = (g + 1) % G;
+            }
+            continue;
+        }
+        if (first >= nb) return; // nothing to build
+        if (wv == 0) {
+            const int want = lane < G ? (np - lane + G - 1) / G : 0; // units of group `lane`
+            bool all = false;
+            for (int k = 0; k < SYNC_POLLS && !all; ++k) {
+                if (k > 0) __builtin_amdgcn_s_sleep(32);
+                const int got = lane < G ? __hip_atomic_load(sync + (G + lane) * SYNC_STRIDE, __ATOMIC_RELAXED,
+                                                            __HIP_MEMORY_SCOPE_AGENT)
+                                         : 0;
+                all = __all(got >= want);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (lane == 0) word = all;
+        }
+        __syncthreads();
+        if (word) break;
+        if (round == 0) left = G;
+        if (++round > SYNC_ROUNDS) {
+            if (threadIdx.x == 0) atomicOr(ba.status, 4);
+            return;
+        }
+    }
+    for (int item = first + wv; item < nb; item += nblk * WPB) build_item<P>(ba, rp, lds.build[wv], 0, item);
 }
 
 // Candidate records of a slot's particles (k_permute writes those of a
@@ -963,9 +1075,9 @@ hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
     LAUNCH_CHECK();
 }
 
-hipError_t launch_enlist(int *rlist, const Ctl *ctl, int max_slots, int slot, hipStream_t s)
+hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, int slot, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_enlist, dim3(1), dim3(64), 0, s, rlist, ctl, max_slots, slot);
+    hipLaunchKernelGGL(k_enlist, dim3(1), dim3(64), 0, s, rlist, sync, ctl, max_slots, slot);
     LAUNCH_CHECK();
 }
 
@@ -1006,6 +1118,18 @@ hipError_t occupancy_build(int prec, int *per_cu)
     default: f = (const void *)k_build<PREC_FP64>; break;
     }
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, BUILD_BLOCK, 0);
+}
+
+hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s)
+{
+    const dim3 g(grid), b(BUILD_BLOCK);
+    switch (prec) {
+    case PREC_FP32: hipLaunchKernelGGL((k_rebuild<PREC_FP32>), g, b, 0, s, pa, ba, sync); break;
+    case PREC_DS: hipLaunchKernelGGL((k_rebuild<PREC_DS>), g, b, 0, s, pa, ba, sync); break;
+    case PREC_MIX: hipLaunchKernelGGL((k_rebuild<PREC_MIX>), g, b, 0, s, pa, ba, sync); break;
+    default: hipLaunchKernelGGL((k_rebuild<PREC_FP64>), g, b, 0, s, pa, ba, sync); break;
+    }
+    LAUNCH_CHECK();
 }
 
 hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s)

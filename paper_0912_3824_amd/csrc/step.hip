@@ -374,20 +374,6 @@ __device__ __forceinline__ void force_dbl(const KArena &A, const uint4 *__restri
 // ------------------------------------------------------------ k_step
 enum { M_ADV = 0, M_FIN = 1, M_IDLE = 2 };
 
-// A uniform index into memory that no kernel writes while this one runs:
-// scalar loads.
-template <class T> __device__ __forceinline__ T ld_uniform(const T *p, int k)
-{
-    typedef const __attribute__((address_space(4))) int CW;
-    struct Words { int w[sizeof(T) / 4]; } v;
-    CW *q = (CW *)(uintptr_t)(p + k);
-#pragma unroll
-    for (unsigned u = 0; u < sizeof(T) / 4; ++u) v.w[u] = q[u];
-    T t;
-    __builtin_memcpy(&t, &v, sizeof t);
-    return t;
-}
-
 // ONE: a pool of one slot.  Its records are read by scalar loads before
 // anything is known of the particle, two round trips to memory earlier than
 // through the slot in the particle's snapshot, and stay in scalar registers.
@@ -409,6 +395,7 @@ __global__ void __launch_bounds__(1024) k_step(const StepArgs a)
         const int gt = blockIdx.x * blockDim.x + threadIdx.x;
         for (int c = gt; c < a.cell_cap; c += nblk * blockDim.x) a.count_other[c] = 0;
         if (gt == 0) a.rlist_other[0] = 0;
+        if (gt < SYNC_WORDS / SYNC_STRIDE) a.sync_other[gt * SYNC_STRIDE] = 0;
     }
     Ctl ctl0;
     RepDev rp0;
