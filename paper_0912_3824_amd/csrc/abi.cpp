@@ -731,7 +731,8 @@ static RepDev repdev_of(const md_system *s, const SlotHost &h)
         r.hs2s = (float)(p.hs2d / (u * u));
         r.hs2s_early = (float)(p.hs2d_early / (u * u));
     }
-    r.items3 = h.nd * h.nd * h.nd; // a sort work item covers a cell in every plane
+    // the sort works on cells (in every plane), or on the particles of a single cell
+    r.items3 = h.nd == 1 ? h.n : h.nd * h.nd * h.nd;
     r.items4 = items4_of(h.n, h.nd);
     r.bmode = build_mode(h.n, h.nd);
     r.bparts = build_parts(h.n, h.nd);

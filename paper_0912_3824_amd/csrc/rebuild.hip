@@ -194,22 +194,21 @@ __device__ __forceinline__ void permute_cell(const PermArgs &a, const RepDev &rp
     // the old cells that can hold members of new cell c, in ascending
     // rank: plane 0's, then plane 1's (so that the flattened candidates
     // are in old slot order); one range per lane
-    const int nold = nd == 1 ? 1 : 27, nr = planes * nold;
-    if (nd > 1) { // rank the 27 neighbour cells (distinct for nd >= 3)
-        int orank = 0x7fffffff;
-        if (lane < 27) {
-            const int cx = c % nd, cy = (c / nd) % nd, cz = c / (nd * nd);
-            orank = offset_rank(cx, cy, cz, lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1, rp, a.corder);
-        }
-        int pos = 0;
-        for (int l = 0; l < 27; ++l) pos += __shfl(orank, l, 64) < orank;
-        if (lane < 27) W.srt[pos] = orank;
-        wave_sync();
+    const int nold = 27, nr = planes * nold;
+    // rank the 27 neighbour cells (distinct for nd >= 3)
+    int orank = 0x7fffffff;
+    if (lane < 27) {
+        const int cx = c % nd, cy = (c / nd) % nd, cz = c / (nd * nd);
+        orank = offset_rank(cx, cy, cz, lane % 3 - 1, (lane / 3) % 3 - 1, lane / 9 - 1, rp, a.corder);
     }
+    int before = 0;
+    for (int l = 0; l < 27; ++l) before += __shfl(orank, l, 64) < orank;
+    if (lane < 27) W.srt[before] = orank;
+    wave_sync();
     int len = 0, st0 = 0;
     if (lane < nr) {
         const int pl = lane >= nold, kk = lane - pl * nold;
-        const int oc = pl * nc + (nd > 1 ? W.srt[kk] : 0);
+        const int oc = pl * nc + W.srt[kk];
         st0 = cs[oc];
         len = cs[oc + 1] - st0;
     }
@@ -250,7 +249,7 @@ __device__ __forceinline__ void permute_cell(const PermArgs &a, const RepDev &rp
             }
         }
 #pragma unroll
-        for (int u = 0; u < PERM_U; ++u) m[u] = q[u] >= 0 && (nd == 1 || in_cell<P>(a, rp, q[u], c));
+        for (int u = 0; u < PERM_U; ++u) m[u] = q[u] >= 0 && in_cell<P>(a, rp, q[u], c);
         // list the members found, in candidate order (at most 64 x
         // PERM_U, so the list, emptied below once it holds more than
         // 64, never overflows)
@@ -300,23 +299,23 @@ __device__ __forceinline__ int thread_sum(const int *count, int n)
 // double-single and FP64 it is compiled for 6 waves per SIMD (at most 80
 // VGPRs) instead of the 4 its unconstrained register use allows; its grid
 // takes one full residency at that occupancy.  The FP32 and MIXED64 forms
-// would spill at 80 VGPRs and keep their own allocation.
+// spill more than that gains and are compiled for 4.
 struct PermBlockLds {
     PermLds wave[PERM_BLOCK / 64];
     int red[3][PERM_BLOCK / 64];
 };
 
-// Cells per sort unit and sort units of a replica of nc cells, for a grid of
-// nblk blocks.
+// Cells per sort unit and sort units of a replica, for a grid of nblk blocks.
+// A unit of a single-cell replica is PERM_BLOCK of its particles.
 __device__ __forceinline__ int perm_range(int nc, int nblk)
 {
     constexpr int WPB = PERM_BLOCK / 64;
     return WPB * ((nc + WPB * nblk - 1) / (WPB * nblk));
 }
-__device__ __forceinline__ int perm_units(int nc, int nblk)
+__device__ __forceinline__ int perm_units(const RepDev &rp, int nblk)
 {
-    const int range = perm_range(nc, nblk);
-    return (nc + range - 1) / range;
+    const int range = rp.nd == 1 ? PERM_BLOCK : perm_range(rp.items3, nblk);
+    return (rp.items3 + range - 1) / range;
 }
 
 template <int P>
@@ -327,9 +326,29 @@ __device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nd = rp.nd, nc = nd * nd * nd, range = perm_range(nc, nblk);
     const bool two = rp.planes > 1;
-    const int c0 = item * range, c1 = min(nc, c0 + range);
     const int *cnt = a.count + rp.coff;
     int *out = a.cs_new + rp.coff;
+    // A single cell is sorted by plane alone: every particle keeps its place
+    // (one wave listing and moving 600 particles took 9 us more).
+    if (nd == 1) {
+        const int k = item * PERM_BLOCK + (int)threadIdx.x;
+        if (k < rp.n) {
+            Moved<P> mv;
+            move_load<P>(a, rp.off + k, mv);
+            move_store<P>(a, rp, mv, rp.off + k);
+        }
+        if (k == 0) {
+            const int n0 = cnt[0], n1 = two ? cnt[1] : 0;
+            out[0] = rp.off;
+            out[1] = rp.off + n0;
+            if (two) out[2] = rp.off + n0 + n1;
+            if (n0 + n1 != rp.n) atomicOr(a.status + s, 4 | 2);
+            if (a.cs[rp.coff + 1] - a.cs[rp.coff] != n0) atomicOr(a.status + s, 4);
+            a.nreb[s] += 1;
+        }
+        return;
+    }
+    const int c0 = item * range, c1 = min(nc, c0 + range);
     // members before the range: of plane 0; of plane 0 in all and of plane 1
     int sum[3] = {thread_sum(cnt, c0), 0, 0};
     if (two) {
@@ -385,11 +404,11 @@ __device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp
 
 template <int P>
 __global__ void __launch_bounds__(PERM_BLOCK)
-__attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 1))) k_permute(const PermArgs a)
+__attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 4))) k_permute(const PermArgs a)
 {
     __shared__ PermBlockLds lds;
     const int nblk = gridDim.x;
-    for_items(a.rlist, [&](int sl) { return perm_units(a.rep[sl].items3, nblk); }, blockIdx.x, nblk,
+    for_items(a.rlist, [&](int sl) { return perm_units(a.rep[sl], nblk); }, blockIdx.x, nblk,
               [&](int s, int item) {
                   const RepDev rp = a.rep[s];
                   permute_item<P>(a, rp, lds, s, item, nblk);
@@ -1000,7 +1019,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
     __shared__ int word;
     const RepDev rp = ld_uniform(ba.rep, 0);
     const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nblk = gridDim.x;
-    const int np = perm_units(rp.items3, nblk), nb = rp.items4; // sort units, list-build items
+    const int np = perm_units(rp, nblk), nb = rp.items4; // sort units, list-build items
     const int first = remap_block(blockIdx.x, nblk, ba.xcd) * WPB; // the block's first list-build item
     int g = (int)(blockIdx.x % G), left = (int)blockIdx.x < np ? 1 : 0; // groups to take units from: g and on
     for (int round = 0;;) {
