@@ -299,7 +299,7 @@ __device__ __forceinline__ int thread_sum(const int *count, int n)
 // double-single and FP64 it is compiled for 6 waves per SIMD (at most 80
 // VGPRs) instead of the 4 its unconstrained register use allows; its grid
 // takes one full residency at that occupancy.  The FP32 and MIXED64 forms
-// spill more than that gains and are compiled for 4.
+// would spill at 80 VGPRs and are compiled for 4.
 struct PermBlockLds {
     PermLds wave[PERM_BLOCK / 64];
     int red[3][PERM_BLOCK / 64];
@@ -709,35 +709,31 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
 // 171 us, an aligned rebuild of 256 small replicas 461 -> 360 us.
 #define BUILD_EDGE (CELL_UNITS * CELL_UNITS / 16384.0f)
 
-// Per visit: 2 d in half precision as the candidate words multiply it (x y,
-// z x, y z), -2 d and |d|^2.
-struct VisitTab {
-    struct { unsigned xy, zx, yz; float x, y, z, sq; int pad; } v[27];
+// Per visit, in LDS: 2 d in half precision as the candidate words multiply it
+// (x y, z x, y z; for the lower half of the wave, zero for the upper), and -2 d
+// and |d|^2.
+struct VisitLds {
+    uint4 w[2][27];
+    float4 d[27];
 };
-constexpr VisitTab make_visit_tab()
+__device__ __forceinline__ void fill_visits(VisitLds &V) // by threads of one block, before a barrier
 {
-    VisitTab t{};
-    for (int v = 0; v < 27; ++v) {
-        const int q = v > 0 ? 14 + ((v - 1) >> 1) : 13, sg = (v & 1) ? 1 : -1;
-        const int o[3] = {sg * (q % 3 - 1), sg * ((q / 3) % 3 - 1), sg * (q / 9 - 1)};
-        unsigned b[3] = {0, 0, 0};
-        for (int d = 0; d < 3; ++d) b[d] = o[d] == 0 ? 0u : o[d] > 0 ? 0x5800u : 0xD800u; // +-128 = 2 CELL_UNITS
-        t.v[v].xy = b[0] | b[1] << 16;
-        t.v[v].zx = b[2] | b[0] << 16;
-        t.v[v].yz = b[1] | b[2] << 16;
-        t.v[v].x = -2.0f * CELL_UNITS * o[0];
-        t.v[v].y = -2.0f * CELL_UNITS * o[1];
-        t.v[v].z = -2.0f * CELL_UNITS * o[2];
-        t.v[v].sq = CELL_UNITS * CELL_UNITS * (o[0] * o[0] + o[1] * o[1] + o[2] * o[2]);
-    }
-    return t;
+    static_assert(CELL_UNITS == 64.0f, "2 CELL_UNITS in half precision");
+    const int v = threadIdx.x;
+    if (v >= 27) return;
+    int o[3];
+    visit_offset(v, o[0], o[1], o[2]);
+    unsigned b[3];
+    for (int d = 0; d < 3; ++d) b[d] = o[d] == 0 ? 0u : o[d] > 0 ? 0x5800u : 0xD800u; // +-128 = 2 CELL_UNITS
+    V.w[0][v] = make_uint4(b[0] | b[1] << 16, b[2] | b[0] << 16, b[1] | b[2] << 16, 0);
+    V.w[1][v] = make_uint4(0, 0, 0, 0);
+    V.d[v] = make_float4(-2.0f * CELL_UNITS * o[0], -2.0f * CELL_UNITS * o[1], -2.0f * CELL_UNITS * o[2],
+                         CELL_UNITS * CELL_UNITS * (o[0] * o[0] + o[1] * o[1] + o[2] * o[2]));
 }
-static_assert(CELL_UNITS == 64.0f, "the half-precision words of VisitTab");
-__constant__ const VisitTab visit_tab = make_visit_tab();
 
 template <int P>
-__device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev &rp, int s, BuildLds &W, int ns,
-                                                const Members &mem, int first, int stride)
+__device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev &rp, int s, BuildLds &W,
+                                                const VisitLds &V, int ns, const Members &mem, int first, int stride)
 {
     const KArena &A = a.A;
     const int lane = __lane_id(), col = lane & 31, h = lane >> 5;
@@ -748,7 +744,7 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
     // the upper half of the terms: candidate words (high words, 1, 1, B, B, 0)
     const unsigned keep1 = h ? 0x0000FFFFu : ~0u, set1 = h ? 0x3C000000u : 0u;
     const unsigned keep2 = h ? 0u : ~0u, setA = h ? 0x00003C00u : 0u, setB = h ? 0x3C003C00u : 0u;
-    const unsigned setB3 = h ? 0x00003C00u : 0u;
+    const unsigned setB3 = h ? 0x00003C00u : 0u, gkeep = h ? ~0u : 0u;
     auto chunk = [&](int k) { // the same for all lanes
         const int4 t = W.tab[k];
         return make_int4(__builtin_amdgcn_readfirstlane(t.x), __builtin_amdgcn_readfirstlane(t.y),
@@ -780,46 +776,53 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
                            dl = (_Float16)(d - (float)dh), one = (_Float16)1.0f, zero = (_Float16)0.0f;
             mb = h ? half8{xl, yl, zl, ch, cl, dh, dl, zero} : half8{xh, yh, zh, xh, yh, zh, one, one};
         }
-        // acceptance bits of this lane's 16 candidates of chunk t, whose
-        // record of row `col` is rec
+        // the tests of this lane's 16 candidates of chunk t, whose record of row
+        // `col` is rec
         auto product = [&](const int4 &t, const uint4 &rec) {
-            const auto &vt = visit_tab.v[t.w >> 16];
+            const uint4 vw = V.w[h][t.w >> 16];
+            const float4 vd = V.d[t.w >> 16];
             const bool isb = ci >= t.z;
             uint4 ra, ob;
             ra.x = rec.x;
             ra.y = (rec.y & keep1) | set1;
             ra.z = (rec.z & keep2) | (isb ? setB : setA);
             ra.w = (rec.w & keep2) | (isb ? setB3 : 0u);
-            const float g = __builtin_fmaf(vt.x, u[0], __builtin_fmaf(vt.y, u[1], __builtin_fmaf(vt.z, u[2], vt.sq)));
+            const float g = __builtin_fmaf(vd.x, u[0], __builtin_fmaf(vd.y, u[1], __builtin_fmaf(vd.z, u[2], vd.w)));
             const _Float16 gh = (_Float16)g;
             const unsigned gw = half2_bits((_Float16)(g - (float)gh), gh);
-            ob.x = vt.xy & keep2;
-            ob.y = h ? gw & 0xFFFF0000u : vt.zx;
-            ob.z = h ? gw & 0x0000FFFFu : vt.yz;
+            ob.x = vw.x;
+            ob.y = vw.y | (gw & gkeep & 0xFFFF0000u);
+            ob.z = vw.z | (gw & gkeep & 0x0000FFFFu);
             ob.w = 0;
             float16v T;
 #pragma unroll
             for (int q = 0; q < 16; ++q) T[q] = 0.0f;
             const half8 ca = __builtin_bit_cast(half8, ra);
             T = __builtin_amdgcn_mfma_f32_32x32x16_f16(ca, __builtin_bit_cast(half8, ob), T, 0, 0, 0);
-            T = __builtin_amdgcn_mfma_f32_32x32x16_f16(ca, mb, T, 0, 0, 0);
+            return __builtin_amdgcn_mfma_f32_32x32x16_f16(ca, mb, T, 0, 0, 0);
+        };
+        auto signs = [&](const float16v &T) {
             unsigned hit = 0;
 #pragma unroll
             for (int q = 15; q >= 0; --q) hit = __builtin_amdgcn_alignbit(hit, __float_as_uint(T[q]), 31);
+            return hit;
+        };
+        auto nearest = [&](const float16v &T) {
             float near = fminf(fabsf(T[0]), fabsf(T[1]));
 #pragma unroll
             for (int q = 2; q < 16; q += 2) near = fminf(fminf(near, fabsf(T[q])), fabsf(T[q + 1]));
-            if (near < BUILD_EDGE) { // too close to call: the list test itself
-                unsigned again = 0;
+            return near;
+        };
+        // the tests too close to call, by the list test itself
+        auto retest = [&](const int4 &t, const float16v &T, unsigned &hit) {
+            unsigned again = 0;
 #pragma unroll
-                for (int q = 0; q < 16; ++q) again |= fabsf(T[q]) < BUILD_EDGE ? 1u << q : 0u;
-                for (; again; again &= again - 1) {
-                    const int b = __ffs(again) - 1, e = min(16 * h + b, (t.w & 0xFFFF) - 1);
-                    const bool in = in_list<P>(rp, xi, rl, ld_pos<P>(a, (e < t.z ? t.x : t.y) + e));
-                    hit = (hit & ~(1u << b)) | (in ? 1u << b : 0u);
-                }
+            for (int q = 0; q < 16; ++q) again |= fabsf(T[q]) < BUILD_EDGE ? 1u << q : 0u;
+            for (; again; again &= again - 1) {
+                const int b = __ffs(again) - 1, e = min(16 * h + b, (t.w & 0xFFFF) - 1);
+                const bool in = in_list<P>(rp, xi, rl, ld_pos<P>(a, (e < t.z ? t.x : t.y) + e));
+                hit = (hit & ~(1u << b)) | (in ? 1u << b : 0u);
             }
-            return hit;
         };
         int cnt = 0, pad = -1;
         int4 t0 = chunk(0), t1 = chunk(min(1, ns - 1));
@@ -832,7 +835,12 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
             t1 = chunk(min(k + 3, ns - 1));
             r0 = load(t0);
             r1 = load(t1);
-            const unsigned h0 = product(c0, q0), h1 = product(c1, q1);
+            const float16v T0 = product(c0, q0), T1 = product(c1, q1);
+            unsigned h0 = signs(T0), h1 = signs(T1);
+            if (fminf(nearest(T0), nearest(T1)) < BUILD_EDGE) {
+                retest(c0, T0, h0);
+                retest(c1, T1, h1);
+            }
             // this lane's chunk: the first of the two for the lower half
             const auto sw = __builtin_amdgcn_permlane32_swap(h0, h1, false, false);
             unsigned hit = sw[0] | (sw[1] << 16);
@@ -904,7 +912,8 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
 }
 
 template <int P>
-__device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, int s, int item)
+__device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, const VisitLds &V, int s,
+                                           int item)
 {
     const int lane = __lane_id();
     const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes, items = rp.items4;
@@ -961,7 +970,7 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
         for (int c = 0, k = chunks_upto - chunks; c < chunks; ++c, ++k)
             W.tab[k] = make_int4(gA + 32 * c, gB - nA + 32 * c, nA - 32 * c, (n - 32 * c) | (lane << 16));
         wave_sync();
-        build_cell_mfma<P>(a, rp, s, W, ns, mem, 32 * part, 32 * parts);
+        build_cell_mfma<P>(a, rp, s, W, V, ns, mem, 32 * part, 32 * parts);
     } else if (part == 0) { // few members per cell (or a neighbourhood beyond the chunk table)
         if (lane < 27) W.tab[lane] = make_int4(upto - n, gA, gB - nA, nA);
         wave_sync();
@@ -976,12 +985,16 @@ template <int P>
 __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
 {
     __shared__ BuildLds lds[BUILD_BLOCK / 64];
+    __shared__ VisitLds visits;
+    if (a.rlist[0] == 0) return;
+    fill_visits(visits);
+    __syncthreads();
     const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for_items(a.rlist, [&](int sl) { return a.rep[sl].items4; },
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
               [&](int s, int item) {
                   const RepDev rp = a.rep[s];
-                  build_item<P>(a, rp, lds[wv], s, item);
+                  build_item<P>(a, rp, lds[wv], visits, s, item);
               });
 }
 
@@ -1016,7 +1029,9 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
         PermBlockLds perm;
         BuildLds build[WPB];
     } lds;
+    __shared__ VisitLds visits;
     __shared__ int word;
+    fill_visits(visits); // (before the loop's barriers)
     const RepDev rp = ld_uniform(ba.rep, 0);
     const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nblk = gridDim.x;
     const int np = perm_units(rp, nblk), nb = rp.items4; // sort units, list-build items
@@ -1069,7 +1084,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
             return;
         }
     }
-    for (int item = first + wv; item < nb; item += nblk * WPB) build_item<P>(ba, rp, lds.build[wv], 0, item);
+    for (int item = first + wv; item < nb; item += nblk * WPB) build_item<P>(ba, rp, lds.build[wv], visits, 0, item);
 }
 
 // Candidate records of a slot's particles (k_permute writes those of a
