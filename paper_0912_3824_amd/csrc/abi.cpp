@@ -343,11 +343,14 @@ static int cells_per_edge(double L, double rl)
     return nd;
 }
 
+// The sort's form (k_permute): pools that hold one large replica.
+static bool sort_large(const md_system *s) { return s->lay.slots == 1 && s->lay.P > 131072; }
+
 // Grids of the sort and list-build kernels: one full residency of the device.
 static md_status size_grids(md_system *s)
 {
     int per_cu = 0;
-    HIPCHK(s, occupancy_permute(s->prec, &per_cu));
+    HIPCHK(s, occupancy_permute(s->prec, sort_large(s), &per_cu));
     s->grid_perm = std::max(1, per_cu) * s->n_cu;
     per_cu = 0;
     HIPCHK(s, occupancy_build(s->prec, &per_cu));
@@ -508,7 +511,7 @@ static md_status launch_rebuild(md_system *s, int p)
         HIPCHK(s, launch_rebuild_one(prec, pa, ba, s->sync[p], s->grid_build, s->stream));
         return MD_OK;
     }
-    HIPCHK(s, launch_permute(prec, pa, s->grid_perm, s->stream));
+    HIPCHK(s, launch_permute(prec, sort_large(s), pa, s->grid_perm, s->stream));
     HIPCHK(s, launch_build(prec, ba, s->grid_build, s->stream));
     return MD_OK;
 }

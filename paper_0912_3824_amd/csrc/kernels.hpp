@@ -163,11 +163,11 @@ double *thermo_scratch(int dev);         // its device address (nullptr before i
 hipError_t launch_step(int prec, const StepArgs &a, int block, int n_cu, bool obs, hipStream_t s);
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
 hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
-hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s);
+hipError_t launch_permute(int prec, bool large, const PermArgs &a, int grid, hipStream_t s);
 hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s);
 hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
-hipError_t occupancy_permute(int prec, int *per_cu);
+hipError_t occupancy_permute(int prec, bool large, int *per_cu);
 hipError_t occupancy_build(int prec, int *per_cu);
 // A replica handed in as host arrays: by-id input rows on the device, the cell
 // tables and the arrays of the slot it becomes.

@@ -295,11 +295,14 @@ __device__ __forceinline__ int thread_sum(const int *count, int n)
 // beside it), then its waves take the range's cells in turn, and it writes
 // the cell starts that the list build reads.
 //
-// The sort waits on chains of memory round trips rather than on issue, so in
-// double-single and FP64 it is compiled for 6 waves per SIMD (at most 80
-// VGPRs) instead of the 4 its unconstrained register use allows; its grid
-// takes one full residency at that occupancy.  The FP32 and MIXED64 forms
-// would spill at 80 VGPRs and are compiled for 4.
+// The sort waits on chains of memory round trips rather than on issue.  In
+// large pools of one slot, in double-single and FP64, it is compiled for 6
+// waves per SIMD (at most 80 VGPRs) instead of the 4 its unconstrained register
+// use allows: 1M particles 229 -> 195 us, 250,000 69 -> 58.  Replicas of up
+// to 131,072 particles have few cells a wave, and there the registers that
+// spill at 80 cost more than the waves give: 256 replicas at once 131 us at 4
+// waves and 170 at 6, one of 64,000 24 and 28.  The FP32 and MIXED64 forms
+// spill more and keep 4.
 struct PermBlockLds {
     PermLds wave[PERM_BLOCK / 64];
     int red[3][PERM_BLOCK / 64];
@@ -402,9 +405,8 @@ __device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp
     __syncthreads();
 }
 
-template <int P>
-__global__ void __launch_bounds__(PERM_BLOCK)
-__attribute__((amdgpu_waves_per_eu((P == PREC_DS || P == PREC_FP64) ? 6 : 4))) k_permute(const PermArgs a)
+template <int P, int WAVES>
+__global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu(WAVES))) k_permute(const PermArgs a)
 {
     __shared__ PermBlockLds lds;
     const int nblk = gridDim.x;
@@ -701,12 +703,16 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
 // the second.  The entries go to LDS as 16-bit codes (chunk, candidate), and
 // from there to the list as whole rows, coalesced over the members.
 //
-// What bounds it is VALU issue: about 86 instructions per product of 1024
-// tests (16 of them for the acceptance bits), 10 per entry of the longest of
-// a wave's lists, 4,900 per cell of 28 members, against 10,500 with a lane
-// per member and 14 per test.  Before and after, whole rebuild group: 1M
-// mixture in double-single 953 -> 564 us, 200,000 particles in FP64 556 ->
-// 171 us, an aligned rebuild of 256 small replicas 461 -> 360 us.
+// What bounds it is VALU issue (about 80 instructions per product of 1024
+// tests, 16 of them for the acceptance bits; 10 per entry of the longest of a
+// wave's lists; 4,900 per cell of 28 members, against 10,500 with a lane per
+// member and 14 per test), and in small systems the chain of one cell's
+// products: the visits' constants come from LDS, and the retest follows both
+// products of a pair, so that nothing parts the two (through scalar loads and
+// two branches a product the 1M rebuild took 555 us, 4,000 particles' 58).
+// Before and after, whole rebuild group: 1M mixture in double-single 953 -> 539
+// us, 200,000 particles in FP64 556 -> 167 us, an aligned rebuild of 256 small
+// replicas 461 -> 354 us.
 #define BUILD_EDGE (CELL_UNITS * CELL_UNITS / 16384.0f)
 
 // Per visit, in LDS: 2 d in half precision as the candidate words multiply it
@@ -1115,14 +1121,19 @@ hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, i
     LAUNCH_CHECK();
 }
 
-hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s)
+static void (*permute_kernel(int prec, bool large))(PermArgs)
 {
     switch (prec) {
-    case PREC_FP32: hipLaunchKernelGGL((k_permute<PREC_FP32>), dim3(grid), dim3(PERM_BLOCK), 0, s, a); break;
-    case PREC_DS: hipLaunchKernelGGL((k_permute<PREC_DS>), dim3(grid), dim3(256), 0, s, a); break;
-    case PREC_MIX: hipLaunchKernelGGL((k_permute<PREC_MIX>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_permute<PREC_FP64>), dim3(grid), dim3(256), 0, s, a); break;
+    case PREC_FP32: return k_permute<PREC_FP32, 4>;
+    case PREC_DS: return large ? k_permute<PREC_DS, 6> : k_permute<PREC_DS, 4>;
+    case PREC_MIX: return k_permute<PREC_MIX, 4>;
+    default: return large ? k_permute<PREC_FP64, 6> : k_permute<PREC_FP64, 4>;
     }
+}
+
+hipError_t launch_permute(int prec, bool large, const PermArgs &a, int grid, hipStream_t s)
+{
+    hipLaunchKernelGGL(permute_kernel(prec, large), dim3(grid), dim3(PERM_BLOCK), 0, s, a);
     LAUNCH_CHECK();
 }
 
@@ -1130,16 +1141,9 @@ hipError_t launch_permute(int prec, const PermArgs &a, int grid, hipStream_t s)
 // are sized to one full residency: the kernels walk their work items in a
 // grid-stride loop, and a second partial round of workgroups would idle most
 // of the chip while it runs).
-hipError_t occupancy_permute(int prec, int *per_cu)
+hipError_t occupancy_permute(int prec, bool large, int *per_cu)
 {
-    const void *f;
-    switch (prec) {
-    case PREC_FP32: f = (const void *)k_permute<PREC_FP32>; break;
-    case PREC_DS: f = (const void *)k_permute<PREC_DS>; break;
-    case PREC_MIX: f = (const void *)k_permute<PREC_MIX>; break;
-    default: f = (const void *)k_permute<PREC_FP64>; break;
-    }
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, 256, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void *)permute_kernel(prec, large), PERM_BLOCK, 0);
 }
 
 hipError_t occupancy_build(int prec, int *per_cu)

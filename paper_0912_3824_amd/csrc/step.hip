@@ -591,8 +591,10 @@ enum { M_ADV = 0, M_FIN = 1, M_IDLE = 2 };
 // ONE: a pool of one slot.  Its records are read by scalar loads before
 // anything is known of the particle, two round trips to memory earlier than
 // through the slot in the particle's snapshot, and stay in scalar registers.
-// us per step, before -> after: 64,000 particles 22.2 -> 20.7, 37,000 FP32
-// 16.1 -> 15.7, 200,000 FP64 82.5 -> 77.6 (114 instead of 128 VGPRs).
+// us per step, before -> after: 64,000 particles 22.4 -> 21.8, 37,000 FP32
+// 15.4 -> 14.8, 200,000 FP64 75.9 -> 74.9.  Such pools also read the reference
+// position and the status early (after the list rows: before them they delay
+// the first gathers, 4,000 particles in FP64 10.6 -> 10.9).
 //
 // H: lanes that share one of the particle's LPP lists (1, or QUAD in small
 // pools of one slot).
@@ -935,9 +937,10 @@ static hipError_t launch_step_t(const StepArgs &a, int block, int h, bool obs, h
 // g blocks holds ceil(g / CUs) blocks, and a smaller block is taken as long
 // as that brings the fullest CU's load down by a tenth.  Beyond 32 waves per
 // CU the hardware refills CUs as blocks end, and neighbouring waves sharing
-// an L1 count for more.  Measured against blocks of 512, us per step: N = 600
-// 15.5 -> 12.7, 10,000 FP32 16.5 -> 12.7, 37,000 FP32 18.4 -> 16.1, 200,000
-// FP64 90.6 -> 82.5; at 64,000 all sizes load the fullest CU alike (22.4).
+// an L1 count for more.  Measured against blocks of 512 (256 for quads), us per
+// step: N = 600 9.8 -> 9.0, 10,000 FP32 10.1 -> 9.9, 37,000 FP32 16.9 -> 14.8,
+// 200,000 FP64 80.5 -> 74.9, jobs of 1,000 to 64,000 in one pool 48.2 -> 42.7
+// ms; at 64,000 all sizes load the fullest CU alike (21.8).
 hipError_t launch_step(int prec, const StepArgs &a, int block, int n_cu, bool obs, hipStream_t s)
 {
     const long long lanes = (long long)a.A.P * a.lpp;
