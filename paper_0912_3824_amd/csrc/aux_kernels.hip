@@ -328,9 +328,9 @@ hipError_t launch_thermostat(int prec, const ThermoArgs &a, hipStream_t s)
 // ------------------------------------------- allocation-free thermostat
 // For callers that cannot allocate device memory (code under graph capture,
 // tight serving loops): the chunk partial sums of md_thermostat_noalloc live
-// in this file-scope device array instead of the pool's workspace.  Each GPU holds its own copy; host code must use the address
-// hipGetSymbolAddress returns for the current device, never the array's
-// name.  Every chunk row a call reads was written by the same call, so
+// in this file-scope device array instead of the pool's workspace.  Each GPU
+// holds its own copy; host code must use the address hipGetSymbolAddress
+// returns for the current device, never the array's name.  Every chunk row a call reads was written by the same call, so
 // nothing needs clearing; calls that overlap on one GPU race on it.
 static __device__ __align__(256) double scratch[THERMO_SCRATCH_CHUNKS * 8];
 
