@@ -28,8 +28,9 @@
  *     workspace of md_workspace_bytes() bytes and a hipStream_t (as void*);
  *     the library never allocates or frees device memory.  The library owns
  *     only the host handle (freed by md_destroy), its host-side mirrors and,
- *     from the first call that reads data back, up to 1 MiB of pinned host
- *     memory for small transfers (freed by md_destroy too).
+ *     from the first call that reads data back, about 1 MiB of pinned host
+ *     memory for small transfers (96 bytes a slot where that is more; freed by
+ *     md_destroy too).
  *   - Host arrays passed in are read before the call returns; host arrays
  *     passed out are written before the call returns.
  *   - Asynchrony: calls that only launch work (md_step, md_advance,
