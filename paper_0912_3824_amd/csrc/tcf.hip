@@ -65,64 +65,84 @@ __global__ void __launch_bounds__(TCF_BLOCK) k_tcf_store(const TcfArgs a, int en
     a.species[id] = species_of(meta);
 }
 
-__device__ __forceinline__ double tcf_wave_sum(double x)
+// Sums of (msd, vacf, fs, count) over the wave's lanes of species A (lower half
+// of the result lanes) and B: each exchange passes on the values that the other
+// side keeps, so that eight sums take 10 exchanges.  Lane k ends with value
+// 2 (k >> 4 & 1) + (k >> 3 & 1) of species k >> 5.
+__device__ __forceinline__ double tcf_wave_sums(int lane, bool b, const double x[4])
 {
+    const bool hi = lane & 32, up = lane & 16, odd = lane & 8;
+    double y[4], z[2];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
+    for (int c = 0; c < 4; ++c) {
+        const double mine = b == hi ? x[c] : 0.0, other = b == hi ? 0.0 : x[c];
+        y[c] = mine + __shfl_xor(other, 32, 64);
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const double mine = up ? y[2 + c] : y[c], other = up ? y[c] : y[2 + c];
+        z[c] = mine + __shfl_xor(other, 16, 64);
+    }
+    const double mine = odd ? z[1] : z[0], other = odd ? z[0] : z[1];
+    double s = mine + __shfl_xor(other, 8, 64);
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    return s;
 }
 
 // One correlation pass: origin entry `head` against entries head+1 .. head+l-1
 // (mod l) of level `level`.  partial[block][j][species][4] = sums of MSD,
 // VACF, F_s and the particle count over this workgroup's particles.
+//
+// Each lag reads 64 bytes a particle, the next while one is worked on.  Eight
+// wave sums of six exchanges and two barriers per lag took longer than the
+// reads: 250,000 particles and nine lags 54 -> 29 us, what a large copy needs
+// for the 160 MB.
+#define TCF_LAGS 32 // at most (block <= 33)
 __global__ void __launch_bounds__(TCF_BLOCK) k_tcf_corr(const TcfArgs a, int level, int head)
 {
-    __shared__ double red[TCF_BLOCK / 64][8];
+    constexpr int WAVES = TCF_BLOCK / 64;
+    __shared__ double red[TCF_LAGS][WAVES][8];
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int id = blockIdx.x * blockDim.x + t;
     const int l = a.block;
     const bool live = id < a.n;
+    const int k = min(id, a.n - 1);
     const size_t base = (size_t)level * l;
-    double4 p0 = make_double4(0, 0, 0, 0);
-    double4 v0 = make_double4(0, 0, 0, 0);
-    int sp = 0;
-    if (live) {
-        p0 = a.pos[(base + head) * a.n + id];
-        v0 = a.vel[(base + head) * a.n + id];
-        sp = a.species[id];
-    }
-    for (int j = 1; j < l; ++j) {
+    auto entry = [&](int j) {
         int e = head + j;
         e -= e >= l ? l : 0;
-        double msd = 0, vacf = 0, fs = 0;
-        if (live) {
-            const double4 p = a.pos[(base + e) * a.n + id];
-            const double4 v = a.vel[(base + e) * a.n + id];
-            const double dx = p.x - p0.x, dy = p.y - p0.y, dz = p.z - p0.z;
-            msd = dx * dx + dy * dy + dz * dz;
-            vacf = v.x * v0.x + v.y * v0.y + v.z * v0.z;
-            fs = (cos(a.q * dx) + cos(a.q * dy) + cos(a.q * dz)) / 3.0;
+        return (base + e) * a.n + k;
+    };
+    const double4 p0 = a.pos[entry(0)], v0 = a.vel[entry(0)];
+    const bool b = a.species[k] != 0;
+    double4 p = a.pos[entry(1)], v = a.vel[entry(1)];
+    for (int j = 1; j < l; ++j) {
+        double4 pn = p, vn = v;
+        if (j + 1 < l) {
+            const size_t e = entry(j + 1);
+            pn = a.pos[e];
+            vn = a.vel[e];
         }
-        // species-split sums: (msd, vacf, fs, count) for A then B
-        double s[8];
+        const double dx = p.x - p0.x, dy = p.y - p0.y, dz = p.z - p0.z;
+        double x[4];
+        x[0] = dx * dx + dy * dy + dz * dz;
+        x[1] = v.x * v0.x + v.y * v0.y + v.z * v0.z;
+        x[2] = (cos(a.q * dx) + cos(a.q * dy) + cos(a.q * dz)) / 3.0;
+        x[3] = 1.0;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s[c] = 0.0;
-        const int o = sp ? 4 : 0;
-        if (live) {
-            s[o] = msd; s[o + 1] = vacf; s[o + 2] = fs; s[o + 3] = 1.0;
-        }
+        for (int c = 0; c < 4; ++c) x[c] = live ? x[c] : 0.0;
+        const double s = tcf_wave_sums(lane, b, x);
+        if ((lane & 7) == 0) red[j - 1][wv][lane >> 3 & 7] = s;
+        p = pn;
+        v = vn;
+    }
+    __syncthreads();
+    for (int r = t; r < 8 * (l - 1); r += TCF_BLOCK) {
+        double acc = 0;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) s[c] = tcf_wave_sum(s[c]);
-        if (lane == 0)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) red[wv][c] = s[c];
-        __syncthreads();
-        if (t < 8) {
-            double acc = 0;
-            for (int w = 0; w < TCF_BLOCK / 64; ++w) acc += red[w][t];
-            a.partial[((size_t)blockIdx.x * (l - 1) + (j - 1)) * 8 + t] = acc;
-        }
-        __syncthreads();
+        for (int w = 0; w < WAVES; ++w) acc += red[r >> 3][w][r & 7];
+        a.partial[(size_t)blockIdx.x * (l - 1) * 8 + r] = acc;
     }
 }
 
