@@ -837,6 +837,34 @@ static void release_slot_ranges(md_system *s, SlotHost &h)
     h.attached = false;
 }
 
+// Take a replica off the device: its control words are cleared, and the
+// snapshots of its range say "no replica" again (a record left there would be
+// stepped as a particle of the slot's next replica).  Waits for the stream.
+static hipError_t clear_slot(md_system *s, int slot)
+{
+    const SlotHost &h = s->slots[slot];
+    const Ctl z = make_int4(0, 0, 0, 0);
+    hipError_t err = hipSuccess;
+    auto run = [&](hipError_t e) { if (err == hipSuccess) err = e; };
+    for (int p = 0; p < 2; ++p) {
+        run(hipMemcpyAsync(s->ctl[p] + slot, &z, sizeof z, hipMemcpyHostToDevice, s->stream));
+        for (int w = 0; w < s->lay.NS; ++w)
+            run(hipMemsetAsync(s->snap[p] + w * s->lay.P + h.off, 0xFF, 16 * (size_t)h.n, s->stream));
+    }
+    run(hipStreamSynchronize(s->stream));
+    return err;
+}
+
+// A replica that could not be attached leaves nothing behind but the error.
+static void abandon_slot(md_system *s, int slot)
+{
+    const std::string why = s->err;
+    if (clear_slot(s, slot) != hipSuccess) (void)hipGetLastError();
+    release_slot_ranges(s, s->slots[slot]);
+    (void)upload_items(s);
+    s->err = why;
+}
+
 // Error bits that stop a replica, and the status a call reports for them.
 constexpr int MD_ST_ERRORS = MD_ST_LIST_OVERFLOW | MD_ST_NONFINITE | MD_ST_LOST | MD_ST_NO_PAD;
 
@@ -1274,17 +1302,8 @@ md_status md_attach(md_system *s, int32_t slot, const md_replica *rep, const int
     h.target = 0;
     s->slots[slot] = h;
     st = attach_on_device(s, slot, h, species, pos, vel);
-    if (st != MD_OK) {
-        release_slot_ranges(s, s->slots[slot]);
-        Ctl z = make_int4(0, 0, 0, 0);
-        for (int p = 0; p < 2; ++p) (void)hipMemcpyAsync(s->ctl[p] + slot, &z, sizeof z, hipMemcpyHostToDevice, s->stream);
-        (void)hipStreamSynchronize(s->stream);
-        const std::string why = s->err;
-        upload_items(s);
-        s->err = why;
-        return st;
-    }
-    return MD_OK;
+    if (st != MD_OK) abandon_slot(s, slot);
+    return st;
 }
 
 md_status md_init(const md_config *cfg, const md_replica *reps, int32_t n_rep, const int32_t *species,
@@ -1308,13 +1327,7 @@ md_status md_detach(md_system *s, int32_t slot)
     md_status st = check_slot(s, slot, true);
     if (st != MD_OK) return st;
     SlotHost &h = s->slots[slot];
-    Ctl z = make_int4(0, 0, 0, 0);
-    for (int p = 0; p < 2; ++p) {
-        HIPCHK(s, hipMemcpyAsync(s->ctl[p] + slot, &z, sizeof z, hipMemcpyHostToDevice, s->stream));
-        for (int w = 0; w < s->lay.NS; ++w)
-            HIPCHK(s, hipMemsetAsync(s->snap[p] + w * s->lay.P + h.off, 0xFF, 16 * (size_t)h.n, s->stream));
-    }
-    HIPCHK(s, hipStreamSynchronize(s->stream));
+    HIPCHK(s, clear_slot(s, slot));
     release_slot_ranges(s, h);
     h.failed = 0;
     return upload_items(s);

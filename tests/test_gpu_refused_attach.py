@@ -1,0 +1,53 @@
+"""An attach that is refused leaves nothing in the arena: what is attached
+afterwards, to the same slot or over the same range, runs as in a pool of its
+own."""
+import numpy as np
+import pytest
+
+import md_inputs as I
+from gpu_helpers import pool_for
+from paper_0912_3824_amd import mdx
+
+pytestmark = pytest.mark.gpu
+
+CAP = 96  # list entries: enough at density 0.5 (28 on average), not at 1.4 (129)
+
+
+def _lj(n, rho, seed):
+    return I.make_lj(n, rho=rho, temperature=1.5, jitter=0.05, seed=seed)
+
+
+def _same(a, b):
+    return all(np.array_equal(x, y) for x, y in zip(a, b))
+
+
+def _faulty(fault, n):
+    s = _lj(n, 1.4 if fault == "lists" else 0.5, seed=n)
+    if fault == "pos":
+        s.pos[n - 1, 2] = np.nan
+    elif fault == "vel":
+        s.vel[5, 0] = np.inf
+    return s, mdx.MD_E_CAPACITY if fault == "lists" else mdx.MD_E_NONFINITE
+
+
+@pytest.mark.parametrize("fault", ["pos", "vel", "lists"])
+@pytest.mark.parametrize("prec", ["ds", "fp64"])
+def test_later_replicas_run_as_alone(prec, fault):
+    good = {2: _lj(1500, 0.5, 1), 0: _lj(1100, 0.5, 2), 1: _lj(1300, 0.5, 3)}
+    bad, status = _faulty(fault, 3000)
+    cfg = mdx.make_config(bad.table, prec, 0.002, bad.skin, 3, 6000, nbr_capacity=CAP)
+    pool = mdx.MdSystem(cfg)
+    pool.attach_system(2, good[2])
+    with pytest.raises(mdx.MdError) as e:
+        pool.attach_system(0, bad)
+    assert e.value.status == status
+    pool.attach_system(0, good[0])  # the same slot, fewer particles
+    pool.attach_system(1, good[1])  # another slot, over the rest of the range
+    pool.step(200)
+    assert all(o["n_rebuilds"] > 4 for o in pool.observables())
+    for k, s in good.items():
+        alone = pool_for([s], prec, dt=0.002, nbr_capacity=CAP)
+        alone.step(200)
+        assert _same(pool.get_state(k), alone.get_state(0)), k
+        alone.close()
+    pool.close()
