@@ -1767,8 +1767,8 @@ md_status md_restore(md_system *s, int32_t slot, const void *blob, int64_t bytes
     Ctl c = make_int4((int)H.step, (int)H.fresh, 1, 0);
     st = upload_slot(s, slot, h, hr, &xr, c, H.nreb, (int)H.status);
     if (st == MD_OK) st = finish_attach(s, slot);
-    if (st != MD_OK) { release_slot_ranges(s, s->slots[slot]); return st; }
-    return MD_OK;
+    if (st != MD_OK) abandon_slot(s, slot);
+    return st;
 }
 
 md_status md_debug_neighbours(md_system *s, int32_t slot, int32_t *counts, int32_t *ids, int32_t cap)

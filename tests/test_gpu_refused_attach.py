@@ -1,6 +1,6 @@
-"""An attach that is refused leaves nothing in the arena: what is attached
-afterwards, to the same slot or over the same range, runs as in a pool of its
-own."""
+"""An attach or a restore that is refused leaves nothing in the arena: what is
+attached afterwards, to the same slot or over the same range, runs as in a pool
+of its own."""
 import numpy as np
 import pytest
 
@@ -48,6 +48,38 @@ def test_later_replicas_run_as_alone(prec, fault):
     for k, s in good.items():
         alone = pool_for([s], prec, dt=0.002, nbr_capacity=CAP)
         alone.step(200)
+        assert _same(pool.get_state(k), alone.get_state(0)), k
+        alone.close()
+    pool.close()
+
+
+@pytest.mark.parametrize("prec", ["ds", "fp64"])
+def test_a_refused_restore_leaves_nothing(prec):
+    """A checkpoint whose lists overflow the pool's capacity: the dead slot is
+    counted neither by the observables' reduction (its chunks of 4096 particles
+    would not fit beside the others') nor by the steps."""
+    n = 60000
+    dense = _lj(n, 1.4, 4)
+    wide = pool_for([dense], prec, dt=0.002)
+    blob = wide.save(0)
+    wide.close()
+    s, t = _lj(n - 5000, 0.5, 5), _lj(1300, 0.5, 6)
+    cfg = mdx.make_config(s.table, prec, 0.002, s.skin, 3, n, nbr_capacity=CAP)
+    pool = mdx.MdSystem(cfg)
+    with pytest.raises(mdx.MdError) as e:
+        pool.restore(0, blob, n, dense.box)
+    assert e.value.status == mdx.MD_E_CAPACITY
+    assert list(pool.poll()[0]) == [-1, -1, -1]
+    pool.attach_system(1, s)
+    pool.attach_system(0, t)
+    pool.step(60)
+    obs = pool.observables()
+    for k, r in ((1, s), (0, t)):
+        alone = pool_for([r], prec, dt=0.002, nbr_capacity=CAP)
+        alone.step(60)
+        o = alone.observables()[0]
+        assert all(np.array_equal(o[q], obs[k][q]) for q in o), k
+        assert o["n_rebuilds"] > 1
         assert _same(pool.get_state(k), alone.get_state(0)), k
         alone.close()
     pool.close()
