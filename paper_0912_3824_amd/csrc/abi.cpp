@@ -522,7 +522,7 @@ static md_status launch_rebuild(md_system *s, int p)
 static md_status launch_build_main(md_system *s, int slot, bool make_cand)
 {
     int *rlist = s->rlist[s->parity ^ 1];
-    HIPCHK(s, launch_enlist(rlist, s->sync[s->parity ^ 1], s->ctl[0], (int)s->lay.slots, slot, s->stream));
+    HIPCHK(s, launch_enlist(rlist, s->sync[s->parity ^ 1], s->ctl[0], s->status, (int)s->lay.slots, slot, s->stream));
     BuildArgs ba;
     memset(&ba, 0, sizeof ba);
     ba.A = arena_of(s);
@@ -1360,7 +1360,7 @@ md_status md_rebuild_neighbours(md_system *s)
     ca.count = s->count[kp];
     ca.corder = s->corder;
     HIPCHK(s, launch_count(s->prec, ca, s->stream));
-    HIPCHK(s, launch_enlist(s->rlist[kp], s->sync[kp], s->ctl[p], (int)s->lay.slots, -1, s->stream));
+    HIPCHK(s, launch_enlist(s->rlist[kp], s->sync[kp], s->ctl[p], s->status, (int)s->lay.slots, -1, s->stream));
     // the rebuild kernels of a step of parity kp read snap[kp ^ 1] == snap[p]
     return launch_rebuild(s, kp);
 }
@@ -1765,7 +1765,8 @@ md_status md_restore(md_system *s, int32_t slot, const void *blob, int64_t bytes
     h.target = H.step;
     s->slots[slot] = h;
     Ctl c = make_int4((int)H.step, (int)H.fresh, 1, 0);
-    st = upload_slot(s, slot, h, hr, &xr, c, H.nreb, (int)H.status);
+    const int status = (int)H.status & ~(ST_BAD_INPUT | ST_BAD_SPECIES); // (those are set during md_attach only)
+    st = upload_slot(s, slot, h, hr, &xr, c, H.nreb, status);
     if (st == MD_OK) st = finish_attach(s, slot);
     if (st != MD_OK) abandon_slot(s, slot);
     return st;

@@ -482,7 +482,17 @@ __device__ __forceinline__ void attach_encode(const AttachArgs &a, int id, State
     meta = make_int4(img[0], img[1], img[2], id);
 }
 
-// Sort key of each particle and its place among the cell's arrivals.
+// The input of a slot being attached was found wrong (k_attach_count): the
+// kernels that follow write nothing.
+__device__ __forceinline__ bool attach_refused(const AttachArgs &a)
+{
+    return (a.status[a.slot] & (ST_BAD_INPUT | ST_BAD_SPECIES)) != 0;
+}
+
+// Check of the input, and of each particle its sort key and its place among
+// the cell's arrivals.  Nothing of the replica is written before every particle
+// has passed: non-finite positions all convert to one cell, and the passes
+// over a cell's members take the square of their number.
 template <int P>
 __global__ void __launch_bounds__(256) k_attach_count(const AttachArgs a)
 {
@@ -494,6 +504,7 @@ __global__ void __launch_bounds__(256) k_attach_count(const AttachArgs a)
         fine = fine && isfinite(a.pos[3 * (size_t)id + d]) && isfinite(a.vel[3 * (size_t)id + d]);
     if (!fine) atomicOr(a.status + a.slot, ST_BAD_INPUT);
     if (a.species && (a.species[id] < 0 || a.species[id] >= a.n_species)) atomicOr(a.status + a.slot, ST_BAD_SPECIES);
+    if (!fine) return;
     State<P> st;
     uint4 sn[2];
     int4 meta;
@@ -553,7 +564,7 @@ __global__ void __launch_bounds__(1024) k_attach_scan(const AttachArgs a)
 __global__ void __launch_bounds__(256) k_attach_scatter(const AttachArgs a)
 {
     const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id < a.n) a.ids[a.cs[a.rep.coff + a.key[id]] - a.off + a.arrival[id]] = id;
+    if (id < a.n && !attach_refused(a)) a.ids[a.cs[a.rep.coff + a.key[id]] - a.off + a.arrival[id]] = id;
 }
 
 // Each particle to its slot: a cell's members in the order of their ids.
@@ -561,7 +572,7 @@ template <int P>
 __global__ void __launch_bounds__(256) k_attach_place(const AttachArgs a)
 {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= a.n) return;
+    if (k >= a.n || attach_refused(a)) return;
     const int id = a.ids[k], key = a.key[id];
     const int q0 = a.cs[a.rep.coff + key] - a.off, q1 = a.cs[a.rep.coff + key + 1] - a.off;
     int rank = 0;

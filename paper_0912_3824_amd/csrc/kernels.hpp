@@ -162,7 +162,8 @@ hipError_t thermo_scratch_init(int dev); // once per device, with that device cu
 double *thermo_scratch(int dev);         // its device address (nullptr before init)
 hipError_t launch_step(int prec, const StepArgs &a, int block, int n_cu, bool obs, hipStream_t s);
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s);
-hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, int slot, hipStream_t s);
+hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, const int *status, int max_slots, int slot,
+                         hipStream_t s);
 hipError_t launch_permute(int prec, bool large, const PermArgs &a, int grid, hipStream_t s);
 hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s);
 hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);

@@ -32,17 +32,19 @@ __global__ void k_count(const CountArgs a)
 }
 
 // ------------------------------------------------------------ k_enlist
-// Rebuild list of a rebuild or list build asked for by the host: `slot`, or
-// every attached slot (slot < 0).
-__global__ void __launch_bounds__(64) k_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots,
-                                               int slot)
+// Rebuild list of a rebuild or list build asked for by the host: `slot`, unless
+// its input was found wrong while it was attached, or every attached slot
+// (slot < 0).
+__global__ void __launch_bounds__(64) k_enlist(int *rlist, int *sync, const Ctl *ctl, const int *status,
+                                               int max_slots, int slot)
 {
     const int lane = threadIdx.x;
     if (lane < SYNC_WORDS / SYNC_STRIDE) sync[lane * SYNC_STRIDE] = 0;
     int cnt = 0;
     for (int base = 0; base < max_slots; base += 64) {
         const int s = base + lane;
-        const bool in = s < max_slots && (slot < 0 ? ctl[s].z != 0 : s == slot);
+        const bool in = s < max_slots && (slot < 0 ? ctl[s].z != 0
+                                               : s == slot && !(status[s] & (ST_BAD_INPUT | ST_BAD_SPECIES)));
         const unsigned long long m = __ballot(in);
         if (in) rlist[1 + cnt + __popcll(m & ((1ull << lane) - 1ull))] = s;
         cnt += __popcll(m);
@@ -1115,9 +1117,10 @@ hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
     LAUNCH_CHECK();
 }
 
-hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, int max_slots, int slot, hipStream_t s)
+hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, const int *status, int max_slots, int slot,
+                         hipStream_t s)
 {
-    hipLaunchKernelGGL(k_enlist, dim3(1), dim3(64), 0, s, rlist, sync, ctl, max_slots, slot);
+    hipLaunchKernelGGL(k_enlist, dim3(1), dim3(64), 0, s, rlist, sync, ctl, status, max_slots, slot);
     LAUNCH_CHECK();
 }
 

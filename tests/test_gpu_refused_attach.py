@@ -1,6 +1,8 @@
 """An attach or a restore that is refused leaves nothing in the arena: what is
 attached afterwards, to the same slot or over the same range, runs as in a pool
 of its own."""
+import time
+
 import numpy as np
 import pytest
 
@@ -83,3 +85,27 @@ def test_a_refused_restore_leaves_nothing(prec):
         assert _same(pool.get_state(k), alone.get_state(0)), k
         alone.close()
     pool.close()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("prec", ["ds", "fp64"])
+def test_input_without_a_finite_position_is_refused_at_once(prec, value):
+    """All non-finite positions convert to one cell; a list build of that cell
+    (20,000 members in one wave) would take seconds."""
+    s = _lj(20000, 0.5, 7)
+    cfg = mdx.make_config(s.table, prec, 0.002, s.skin, 1, s.n, nbr_capacity=CAP)
+    pool = mdx.MdSystem(cfg)
+    pool.attach_system(0, s)
+    pool.detach(0)
+    t0 = time.perf_counter()
+    with pytest.raises(mdx.MdError) as e:
+        pool.attach(0, s.n, s.box, s.species, np.full_like(s.pos, value), s.vel)
+    assert time.perf_counter() - t0 < 0.5
+    assert e.value.status == mdx.MD_E_NONFINITE
+    pool.attach_system(0, s)
+    pool.step(40)
+    alone = pool_for([s], prec, dt=0.002, nbr_capacity=CAP)
+    alone.step(40)
+    assert _same(pool.get_state(0), alone.get_state(0))
+    pool.close()
+    alone.close()
