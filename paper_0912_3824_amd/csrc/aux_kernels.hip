@@ -512,14 +512,7 @@ __global__ void __launch_bounds__(256) k_attach_count(const AttachArgs a)
     attach_encode<P>(a, id, st, sn, meta, species);
     const int nd = a.rep.nd;
     int cell = 0;
-    if (nd > 1) {
-        if constexpr (Traits<P>::NS == 2) {
-            double x, y, z, w;
-            u4_to_dbl2(sn[0], x, y);
-            u4_to_dbl2(sn[1], z, w);
-            cell = dbl_cell(x, y, z, a.rep.L, a.rep.invL, nd);
-        } else cell = fixed_cell(sn[0].x, sn[0].y, sn[0].z, nd);
-    }
+    if (nd > 1) cell = cell_of<P>(a.rep, sn[0], sn[1]);
     const int key = sort_key(cell_rank(cell, a.rep, a.corder), (uint32_t)species << 31, a.rep.planes, nd);
     a.key[id] = key;
     a.arrival[id] = atomicAdd(a.cs_new + a.rep.coff + key, 1);
@@ -590,7 +583,7 @@ __global__ void __launch_bounds__(256) k_attach_place(const AttachArgs a)
         const size_t j = (size_t)w * a.A.P + i;
         a.snap0[j] = a.snap1[j] = a.A.xref_w[j] = sn[w];
     }
-    if (a.rep.bmode == BUILD_CELLS) a.cand[i] = cand_record<P>(a.rep, sn[0], sn[1]);
+    if (a.rep.bmode == BUILD_CELLS) a.cand[i] = cand_record<P>(a.rep, sn[0], sn[1], cell_of<P>(a.rep, sn[0], sn[1]));
 }
 
 template <int P> static void launch_attach_t(const AttachArgs &a, hipStream_t s)

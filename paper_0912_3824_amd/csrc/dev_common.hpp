@@ -142,19 +142,17 @@ __device__ __forceinline__ void wave_sync()
 
 // Position relative to the centre of the particle's own cell, in units of
 // 1 / CELL_UNITS of the cell edge: the fraction of X nd 2^-32 (fixed point),
-// or of the folded double position.  The cell is the one the sort uses.
+// or from the folded double position and the cell that the sort used.
 template <int P>
-__device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, const uint4 &b, float u[3])
+__device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, const uint4 &b, int cell, float u[3])
 {
     if constexpr (P == PREC_FP64) {
         double x[3], w;
         u4_to_dbl2(a, x[0], x[1]);
         u4_to_dbl2(b, x[2], w);
+        const int c[3] = {cell % r.nd, (cell / r.nd) % r.nd, cell / (r.nd * r.nd)};
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double t = (x[d] - r.L * floor(x[d] * r.invL)) * r.invL * (double)r.nd;
-            u[d] = (float)(t - (double)dbl_cell1(x[d], r.L, r.invL, r.nd) - 0.5) * CELL_UNITS;
-        }
+        for (int d = 0; d < 3; ++d) u[d] = (float)dbl_cell_offset1(x[d], c[d], r.L, r.invL, r.nd) * CELL_UNITS;
     } else {
         const uint32_t X[3] = {a.x, a.y, a.z};
 #pragma unroll
@@ -171,15 +169,26 @@ __device__ __forceinline__ unsigned half2_bits(_Float16 a, _Float16 b)
     return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
 }
 template <int P>
-__device__ __forceinline__ uint4 cand_record(const RepDev &r, const uint4 &a, const uint4 &b)
+__device__ __forceinline__ uint4 cand_record(const RepDev &r, const uint4 &a, const uint4 &b, int cell)
 {
     float u[3];
-    cell_units<P>(r, a, b, u);
+    cell_units<P>(r, a, b, cell, u);
     const float s = __builtin_fmaf(u[0], u[0], __builtin_fmaf(u[1], u[1], u[2] * u[2]));
     const _Float16 xh = (_Float16)u[0], yh = (_Float16)u[1], zh = (_Float16)u[2], sh = (_Float16)s;
     const _Float16 xl = (_Float16)(u[0] - (float)xh), yl = (_Float16)(u[1] - (float)yh),
                    zl = (_Float16)(u[2] - (float)zh), sl = (_Float16)(s - (float)sh);
     return make_uint4(half2_bits(xh, yh), half2_bits(zh, xl), half2_bits(yl, zl), half2_bits(sh, sl));
+}
+
+// Cell of a position in the box (its snapshot words).
+template <int P> __device__ __forceinline__ int cell_of(const RepDev &r, const uint4 &a, const uint4 &b)
+{
+    if constexpr (P == PREC_FP64) {
+        double x, y, z, w;
+        u4_to_dbl2(a, x, y);
+        u4_to_dbl2(b, z, w);
+        return dbl_cell(x, y, z, r.L, r.invL, r.nd);
+    } else return fixed_cell(a.x, a.y, a.z, r.nd);
 }
 
 // ------------------------------------------------------- per-precision state

@@ -200,6 +200,18 @@ __host__ __device__ __forceinline__ int dbl_cell1(double x, double L, double inv
     return c;
 }
 
+// FP64 path: offset of a position from the centre of cell c along one axis, in
+// cell edges, c being the cell that the sort took the particle for.  That cell
+// comes from the position before the sort folded it into the box: x = L, or x
+// so little below 0 that x + L rounds to L, counts in the last cell and folds to
+// 0, the lower face of the first.  So c is told, and the offset is the nearest
+// image's.  (For nd >= 3; for any other position |offset| <= 1/2.)
+__host__ __device__ __forceinline__ double dbl_cell_offset1(double x, int c, double L, double invL, int nd)
+{
+    const double t = (x - L * floor(x * invL)) * invL * (double)nd - (double)c - 0.5;
+    return t < -0.5 * (double)nd ? t + (double)nd : t > 0.5 * (double)nd ? t - (double)nd : t;
+}
+
 // Sort key of a particle (its index in the replica's cell arrays): the rank
 // of its cell in the replica's cell order, within the plane of its species.
 // With two planes every species is sorted by cell on its own (all A, then

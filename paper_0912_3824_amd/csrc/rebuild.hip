@@ -103,9 +103,9 @@ __device__ __forceinline__ uint4 f4_as_u4(float4 f)
 }
 
 // Fold the member's position into [0, L) (counting the image shift in its
-// meta word) and store it at scratch slot dst.
+// meta word) and store it at scratch slot dst; `cell` is its new cell.
 template <int P>
-__device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, const Moved<P> &mv, int dst)
+__device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, const Moved<P> &mv, int dst, int cell)
 {
     constexpr int NS = Traits<P>::NS;
     int4 m = mv.meta;
@@ -154,14 +154,14 @@ __device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, 
             const uint4 w0 = dbl2_to_u4(x, y), w1 = dbl2_to_u4(z, ww);
             a.sc_snap[dst] = w0;
             a.sc_snap[(size_t)a.A.P + dst] = w1;
-            if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, w0, w1);
+            if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, w0, w1, cell);
         }
     }
     m.x += ix; m.y += iy; m.z += iz;
     a.sc_meta[dst] = m;
     if constexpr (NS == 1) {
         a.sc_snap[dst] = mv.snap;
-        if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.snap, mv.snap);
+        if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.snap, mv.snap, cell);
     }
 }
 
@@ -231,7 +231,7 @@ __device__ __forceinline__ void permute_cell(const PermArgs &a, const RepDev &rp
             const int2 e = W.lst[k];
             Moved<P> mv;
             move_load<P>(a, e.x, mv);
-            move_store<P>(a, rp, mv, e.y);
+            move_store<P>(a, rp, mv, e.y, c);
         }
         wave_sync();
     };
@@ -340,7 +340,7 @@ __device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp
         if (k < rp.n) {
             Moved<P> mv;
             move_load<P>(a, rp.off + k, mv);
-            move_store<P>(a, rp, mv, rp.off + k);
+            move_store<P>(a, rp, mv, rp.off + k, 0);
         }
         if (k == 0) {
             const int n0 = cnt[0], n1 = two ? cnt[1] : 0;
@@ -646,14 +646,26 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
     const int *cs = a.cs_new + rp.coff;
     const Snap<P> xi = ld_pos<P>(a, i);
     const ListRadii<P> rl(a, rp, snap_species<P>(xi));
-    int cell;
-    if constexpr (Traits<P>::NS == 2) {
-        double x, y, z, w;
-        u4_to_dbl2(xi.a, x, y);
-        u4_to_dbl2(xi.b, z, w);
-        cell = dbl_cell(x, y, z, rp.L, rp.invL, nd);
-    } else cell = fixed_cell(xi.a.x, xi.a.y, xi.a.z, nd);
-    const int cx = cell % nd, cy = (cell / nd) % nd, cz = cell / (nd * nd);
+    const int cell = cell_of<P>(rp, xi.a, xi.b);
+    int cx = cell % nd, cy = (cell / nd) % nd, cz = cell / (nd * nd);
+    if constexpr (P == PREC_FP64) {
+        // a member that the sort took for the last cell of an axis and folded to
+        // the first's lower face (see dbl_cell_offset1): its cell is the one whose
+        // slots hold it
+        auto holds = [&](int x, int y, int z) {
+            const int k = sort_key(cell_rank(x + nd * (y + nd * z), rp, a.corder), (uint32_t)snap_species<P>(xi) << 31,
+                                   rp.planes, nd);
+            return i >= cs[k] && i < cs[k + 1];
+        };
+        if (!holds(cx, cy, cz)) {
+            const int lx = cx, ly = cy, lz = cz;
+            for (int q = 1; q < 8; ++q) {
+                const int x = (q & 1) && lx == 0 ? nd - 1 : lx, y = (q & 2) && ly == 0 ? nd - 1 : ly,
+                          z = (q & 4) && lz == 0 ? nd - 1 : lz;
+                if (holds(x, y, z)) { cx = x; cy = y; cz = z; break; }
+            }
+        }
+    }
     int cnt = 0, pad = -1;
 #pragma unroll 1
     for (int v = 0; v < 27; ++v) {
@@ -741,7 +753,8 @@ __device__ __forceinline__ void fill_visits(VisitLds &V) // by threads of one bl
 
 template <int P>
 __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev &rp, int s, BuildLds &W,
-                                                const VisitLds &V, int ns, const Members &mem, int first, int stride)
+                                                const VisitLds &V, int ns, int cell, const Members &mem, int first,
+                                                int stride)
 {
     const KArena &A = a.A;
     const int lane = __lane_id(), col = lane & 31, h = lane >> 5;
@@ -771,7 +784,7 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
         const int si = snap_species<P>(xi);
         const ListRadii<P> rl(a, rp, si);
         float u[3];
-        cell_units<P>(rp, xi.a, xi.b, u);
+        cell_units<P>(rp, xi.a, xi.b, cell, u);
         half8 mb; // the members' side of the terms that no offset enters
         {
             const float c0 = rp.rlc[0], c1 = rp.rlc[1], c2 = rp.rlc[2], c3 = rp.rlc[3];
@@ -978,7 +991,7 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
         for (int c = 0, k = chunks_upto - chunks; c < chunks; ++c, ++k)
             W.tab[k] = make_int4(gA + 32 * c, gB - nA + 32 * c, nA - 32 * c, (n - 32 * c) | (lane << 16));
         wave_sync();
-        build_cell_mfma<P>(a, rp, s, W, V, ns, mem, 32 * part, 32 * parts);
+        build_cell_mfma<P>(a, rp, s, W, V, ns, cell, mem, 32 * part, 32 * parts);
     } else if (part == 0) { // few members per cell (or a neighbourhood beyond the chunk table)
         if (lane < 27) W.tab[lane] = make_int4(upto - n, gA, gB - nA, nA);
         wave_sync();
@@ -1104,7 +1117,7 @@ __global__ void __launch_bounds__(256) k_cand(const BuildArgs a, uint4 *cand, in
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= rp.n) return;
     const Snap<P> q = ld_pos<P>(a, rp.off + k);
-    cand[rp.off + k] = cand_record<P>(rp, q.a, q.b);
+    cand[rp.off + k] = cand_record<P>(rp, q.a, q.b, cell_of<P>(rp, q.a, q.b));
 }
 // ------------------------------------------------------------ launchers
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
