@@ -932,6 +932,11 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
     }
 }
 
+// The sort lost a particle of slot s: the replica has stopped, and some of its
+// scratch records are not its own (frames and thermostat draws pass through
+// them), so nothing is copied back and it stays as the step left it.
+__device__ __forceinline__ bool sort_lost(const BuildArgs &a, int s) { return (a.status[s] & 4) != 0; }
+
 template <int P>
 __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, const VisitLds &V, int s,
                                            int item)
@@ -1011,7 +1016,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
     fill_visits(visits);
     __syncthreads();
     const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for_items(a.rlist, [&](int sl) { return a.rep[sl].items4; },
+    for_items(a.rlist, [&](int sl) { return a.from_scratch && sort_lost(a, sl) ? 0 : a.rep[sl].items4; },
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
               [&](int s, int item) {
                   const RepDev rp = a.rep[s];
@@ -1095,9 +1100,12 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
                 all = __all(got >= want);
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            if (lane == 0) word = all;
+            if (lane == 0)
+                word = !all ? 0
+                       : __hip_atomic_load(ba.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 4 ? 2 : 1;
         }
         __syncthreads();
+        if (word == 2) return; // (see sort_lost)
         if (word) break;
         if (round == 0) left = G;
         if (++round > SYNC_ROUNDS) {
