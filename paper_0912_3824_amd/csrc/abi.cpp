@@ -74,6 +74,7 @@ struct SlotHost {
     double L = 0;
     int64_t target = 0;
     int failed = 0; // error bits (MD_ST_*) seen at the last synchronising call
+    bool wide = false; // its list build takes the kernel's wide form
 };
 
 struct Layout {
@@ -113,6 +114,7 @@ struct md_system {
     md_launch launch{};
     double rlist_max = 0;
     std::vector<SlotHost> slots;
+    int n_wide = 0; // attached replicas whose list build takes the wide form
     RangeAlloc parena, carena;
     int parity = 0; // parity of the snapshot the next step reads
     int lpp = 1;    // lanes per particle of the force sum
@@ -358,36 +360,56 @@ static md_status size_grids(md_system *s)
     return MD_OK;
 }
 
-// The form of a replica's list build (none changes a list entry).  With 12 or
-// more members per cell a product of the matrix cores (32 members x 32
-// candidates) is full enough to beat one lane per candidate, whose cost per
-// cell grows with the square of its members; both take about 2,500
-// instructions per cell at 14.  Below that, replicas of many cells give each
-// member a lane (64 members share a wave), and smaller ones, which would
-// leave the chip idle that way, give each cell a wave.
-static int build_mode(int n, int nd)
+// How the list build works on a replica (nothing here changes a list entry).
+//
+// Above 100,000 cells of less than 12 members a lane per member is best.  Else
+// an item is a share of a cell's members, which the kernel tests on the matrix
+// cores or a lane per candidate, whichever the cell's own numbers favour, so
+// that replicas of uneven density (a droplet in its vapour) are served too.
+//
+// Shares per cell: a product of the matrix cores takes 32 members, so a cell
+// that holds more at the pool's density is given to several waves, as far as
+// the idle items of emptier cells cost little (8,192 of them 4 us): a droplet of
+// 20,000 with cutoff 4 takes 524 us a rebuild with one share, 250 with three.
+// Cells of 29 members on average get two in any case.
+//
+// A small replica whose chain of products (27 cells x chunks of 32 candidates,
+// and the entries of its longest lists) outlasts all of its tests made a lane per
+// candidate gets finer shares, of one or a few members, while few replicas rebuild
+// in the step.  Us a rebuild with and without: the mixture at 1,100 particles 58
+// and 74, 2,200 60 and 75, 8,000 76 and 81, 12,000 81 and 79; a fluid of 4,000 at
+// cutoff 3 54 and 74, 3.5 89 and 130; of 20,000 at cutoff 5 269 and 392 (lists
+// beyond the kernel's buffer are dear on the matrix cores).  In FP64 a test costs
+// more: 3,200 97 and 85.
+struct BuildShape { int mode, parts, few, few_max; bool wide; };
+static BuildShape build_shape(const md_system *s, int n, double L, int nd)
 {
+    BuildShape b{BUILD_CELLS, 1, 0, 0, false};
     const int64_t nc = (int64_t)nd * nd * nd;
-    if (nd == 1) return BUILD_SINGLE;
-    if (n >= 12 * nc) return BUILD_CELLS;
-    return nc > 100000 ? BUILD_MEMBERS : BUILD_SPARSE;
+    if (nd == 1) b.mode = BUILD_SINGLE;
+    else if (n < 12 * nc && nc > 100000) b.mode = BUILD_MEMBERS;
+    if (b.mode != BUILD_CELLS) return b;
+    const double mean = (double)n / nc, edge = L / nd;
+    const double dense = (s->cfg.max_density > 0 ? s->cfg.max_density : 1.2) * edge * edge * edge;
+    const double groups = std::ceil(std::max(1.1 * mean, dense) / 32);
+    b.parts = (int)std::min(groups, (double)std::max<int64_t>(n > 29 * nc ? 2 : 1, 8192 / nc));
+    b.wide = mean > 80; // some neighbourhoods have more than BUILD_SLOTS chunks
+    const double rl = s->rlist_max / L, list = 4.18879 * rl * rl * rl * n;
+    if (mean > 32 || list > 100) {
+        const double chunks = 27 * std::ceil(mean / 32), tests = n * std::ceil(27 * mean / 64);
+        const int per = chunks > BUILD_SLOTS ? 12000 : list > BUILD_WIN ? 6000 : s->prec == PREC_FP64 ? 1250 : 2200;
+        b.few_max = (int)std::min(64.0, per * chunks / tests);
+        if (b.few_max > 0) b.few = std::max(b.parts, (int)(mean / (1 + n / 4100)));
+    }
+    return b;
 }
 
-// List-build items per cell: two where the mean cell holds more than 29
-// members, so that most cells take more than one product of 32 (at the 27.8
-// of a large mixture about one cell in thirty does, and an item of its own
-// for the rest of every cell would cost more than it spreads).
-static int build_parts(int n, int nd)
+static int items4_of(const BuildShape &b, int n, int nd)
 {
-    return build_mode(n, nd) == BUILD_CELLS && n > 29 * (int64_t)nd * nd * nd ? 2 : 1;
-}
-
-static int items4_of(int n, int nd)
-{
-    switch (build_mode(n, nd)) {
+    switch (b.mode) {
     case BUILD_SINGLE: return (n + SINGLE_MEMBERS - 1) / SINGLE_MEMBERS;
     case BUILD_MEMBERS: return (n + 63) / 64;
-    default: return nd * nd * nd * build_parts(n, nd);
+    default: return nd * nd * nd * b.parts;
     }
 }
 
@@ -465,7 +487,7 @@ static StepArgs step_args(const md_system *s, int p)
 // launch that the others save (1.5 us); for one slot both forms take the same
 // time at 64,000 particles, which rebuild every 25 steps.
 #define ONE_REBUILD_MAX 49152
-static bool one_rebuild(const md_system *s) { return s->lay.slots == 1 && s->lay.P <= ONE_REBUILD_MAX; }
+static bool one_rebuild(const md_system *s) { return s->lay.slots == 1 && s->lay.P <= ONE_REBUILD_MAX && s->n_wide == 0; }
 
 // The rebuild launches that follow a step of parity p: the replicas on its
 // rebuild list are sorted and their lists built.
@@ -512,7 +534,7 @@ static md_status launch_rebuild(md_system *s, int p)
         return MD_OK;
     }
     HIPCHK(s, launch_permute(prec, sort_large(s), pa, s->grid_perm, s->stream));
-    HIPCHK(s, launch_build(prec, ba, s->grid_build, s->stream));
+    HIPCHK(s, launch_build(prec, s->n_wide > 0, ba, s->grid_build, s->stream));
     return MD_OK;
 }
 
@@ -539,9 +561,9 @@ static md_status launch_build_main(md_system *s, int slot, bool make_cand)
     ba.status = s->status;
     ba.pp = s->pp;
     const SlotHost &h = s->slots[slot];
-    if (make_cand && build_mode(h.n, h.nd) == BUILD_CELLS)
+    if (make_cand && build_shape(s, h.n, h.L, h.nd).mode == BUILD_CELLS)
         HIPCHK(s, launch_cand(s->prec, ba, s->cand, slot, h.n, s->stream));
-    HIPCHK(s, launch_build(s->prec, ba, s->grid_build, s->stream));
+    HIPCHK(s, launch_build(s->prec, s->n_wide > 0, ba, s->grid_build, s->stream));
     return MD_OK;
 }
 
@@ -556,7 +578,7 @@ static md_status launch_one_step(md_system *s, int p)
 // `parity`, captured once into a hipGraph and cached by (steps, parity).
 static md_status get_graph(md_system *s, int steps, int parity, hipGraphExec_t *out)
 {
-    const int key = 2 * steps + parity;
+    const int key = 4 * steps + 2 * (s->n_wide > 0) + parity; // (the launches depend on the list build's form)
     auto it = s->graphs.find(key);
     if (it != s->graphs.end()) { *out = it->second; return MD_OK; }
     if (s->graphs.size() >= 64) drop_graphs(s); // callers cycling through many step counts
@@ -736,9 +758,12 @@ static RepDev repdev_of(const md_system *s, const SlotHost &h)
     }
     // the sort works on cells (in every plane), or on the particles of a single cell
     r.items3 = h.nd == 1 ? h.n : h.nd * h.nd * h.nd;
-    r.items4 = items4_of(h.n, h.nd);
-    r.bmode = build_mode(h.n, h.nd);
-    r.bparts = build_parts(h.n, h.nd);
+    const BuildShape b = build_shape(s, h.n, h.L, h.nd);
+    r.items4 = items4_of(b, h.n, h.nd);
+    r.bmode = b.mode;
+    r.bparts = b.parts;
+    r.bfew = b.few;
+    r.bfew_max = b.few_max;
     return r;
 }
 
@@ -827,11 +852,14 @@ static md_status alloc_slot_ranges(md_system *s, int slot, int n, double L, Slot
         return fail(s, MD_E_CAPACITY, "cell arena full (need %lld)", (long long)h.ncell_alloc);
     }
     (void)slot;
+    h.wide = build_shape(s, n, L, h.nd).wide;
+    s->n_wide += h.wide;
     return MD_OK;
 }
 
 static void release_slot_ranges(md_system *s, SlotHost &h)
 {
+    s->n_wide -= h.wide;
     s->parena.release(h.off, h.n);
     s->carena.release(h.coff, h.ncell_alloc);
     h.attached = false;

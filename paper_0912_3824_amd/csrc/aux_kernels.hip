@@ -583,7 +583,7 @@ __global__ void __launch_bounds__(256) k_attach_place(const AttachArgs a)
         const size_t j = (size_t)w * a.A.P + i;
         a.snap0[j] = a.snap1[j] = a.A.xref_w[j] = sn[w];
     }
-    if (a.rep.bmode == BUILD_CELLS) a.cand[i] = cand_record<P>(a.rep, sn[0], sn[1], cell_of<P>(a.rep, sn[0], sn[1]));
+    if (a.rep.bmode == BUILD_CELLS) a.cand[i] = cand_record<P>(a.rep, sn[0], sn[1]);
 }
 
 template <int P> static void launch_attach_t(const AttachArgs &a, hipStream_t s)

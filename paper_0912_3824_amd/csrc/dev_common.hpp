@@ -142,17 +142,16 @@ __device__ __forceinline__ void wave_sync()
 
 // Position relative to the centre of the particle's own cell, in units of
 // 1 / CELL_UNITS of the cell edge: the fraction of X nd 2^-32 (fixed point),
-// or from the folded double position and the cell that the sort used.
+// or of the double position, as the sort counted it (dbl_cell_offset1).
 template <int P>
-__device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, const uint4 &b, int cell, float u[3])
+__device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, const uint4 &b, float u[3])
 {
     if constexpr (P == PREC_FP64) {
         double x[3], w;
         u4_to_dbl2(a, x[0], x[1]);
         u4_to_dbl2(b, x[2], w);
-        const int c[3] = {cell % r.nd, (cell / r.nd) % r.nd, cell / (r.nd * r.nd)};
 #pragma unroll
-        for (int d = 0; d < 3; ++d) u[d] = (float)dbl_cell_offset1(x[d], c[d], r.L, r.invL, r.nd) * CELL_UNITS;
+        for (int d = 0; d < 3; ++d) u[d] = (float)dbl_cell_offset1(x[d], r.L, r.invL, r.nd) * CELL_UNITS;
     } else {
         const uint32_t X[3] = {a.x, a.y, a.z};
 #pragma unroll
@@ -163,16 +162,16 @@ __device__ __forceinline__ void cell_units(const RepDev &r, const uint4 &a, cons
 
 // Candidate record of the list build: position in cell units and its squared
 // length, each as two half-precision words (high words x, y, z, low words x,
-// y, z, then the square's).
+// y, z, then the square's). 
 __device__ __forceinline__ unsigned half2_bits(_Float16 a, _Float16 b)
 {
     return (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
 }
 template <int P>
-__device__ __forceinline__ uint4 cand_record(const RepDev &r, const uint4 &a, const uint4 &b, int cell)
+__device__ __forceinline__ uint4 cand_record(const RepDev &r, const uint4 &a, const uint4 &b)
 {
     float u[3];
-    cell_units<P>(r, a, b, cell, u);
+    cell_units<P>(r, a, b, u);
     const float s = __builtin_fmaf(u[0], u[0], __builtin_fmaf(u[1], u[1], u[2] * u[2]));
     const _Float16 xh = (_Float16)u[0], yh = (_Float16)u[1], zh = (_Float16)u[2], sh = (_Float16)s;
     const _Float16 xl = (_Float16)(u[0] - (float)xh), yl = (_Float16)(u[1] - (float)yh),
@@ -189,6 +188,15 @@ template <int P> __device__ __forceinline__ int cell_of(const RepDev &r, const u
         u4_to_dbl2(b, z, w);
         return dbl_cell(x, y, z, r.L, r.invL, r.nd);
     } else return fixed_cell(a.x, a.y, a.z, r.nd);
+}
+
+// The position in cell units of a record, to 2^-17.
+__device__ __forceinline__ void record_units(const uint4 &c, float u[3])
+{
+    auto half = [](unsigned w) { return (float)__builtin_bit_cast(_Float16, (unsigned short)w); };
+    u[0] = half(c.x) + half(c.y >> 16);
+    u[1] = half(c.x >> 16) + half(c.z);
+    u[2] = half(c.y) + half(c.z >> 16);
 }
 
 // ------------------------------------------------------- per-precision state

@@ -166,7 +166,7 @@ hipError_t launch_enlist(int *rlist, int *sync, const Ctl *ctl, const int *statu
                          hipStream_t s);
 hipError_t launch_permute(int prec, bool large, const PermArgs &a, int grid, hipStream_t s);
 hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s);
-hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s);
+hipError_t launch_build(int prec, bool wide, const BuildArgs &a, int grid, hipStream_t s);
 hipError_t launch_cand(int prec, const BuildArgs &a, uint4 *cand, int slot, int n, hipStream_t s);
 hipError_t occupancy_permute(int prec, bool large, int *per_cu);
 hipError_t occupancy_build(int prec, int *per_cu);

@@ -51,7 +51,8 @@ struct RepDev {
     float L_hi, L_lo; // L as double-single
     int items3, items4; // work items of the sort and list-build kernels
     int bmode;    // how the list build works on the replica (BUILD_CELLS, ...)
-    int bparts;   // list-build work items per cell (BUILD_CELLS: 1 or 2)
+    int bparts;   // list-build work items per cell (BUILD_CELLS)
+    int bfew, bfew_max; // the same while at most bfew_max replicas rebuild
     // pair constants in fixed-point units u = L / 2^32, per species pair
     // [si*2+sj]: rc^2/u^2, sigma^2/u^2, 24 eps/u; smoothing: rc/u, u/(h sigma),
     // 1/(h sigma); and (skin/2)^2/u^2 for the displacement test
@@ -62,8 +63,11 @@ struct RepDev {
     float rlc[4];     // list radius^2 in cell units (cell_units), the matrix-core test's
 };
 
-// Forms of the list build (rebuild.hip), chosen per replica by build_mode().
-enum { BUILD_SINGLE = 0, BUILD_CELLS = 1, BUILD_SPARSE = 2, BUILD_MEMBERS = 3 };
+// Forms of the list build (rebuild.hip), chosen per replica by build_shape().
+enum { BUILD_SINGLE = 0, BUILD_CELLS = 1, BUILD_MEMBERS = 2 };
+#define BUILD_SLOTS 96       // chunks of 32 candidates a neighbourhood may have (BUILD_CELLS) ...
+#define BUILD_SLOTS_WIDE 552 // ... and in the wide form
+#define BUILD_WIN 128        // list entries per member buffered in LDS (a multiple of 16)
 #define SINGLE_MEMBERS 2     // members per list-build work item of a single-cell replica
 #define CELL_UNITS 64.0f     // cell edge in the units of the list build's candidate records
 
@@ -200,16 +204,14 @@ __host__ __device__ __forceinline__ int dbl_cell1(double x, double L, double inv
     return c;
 }
 
-// FP64 path: offset of a position from the centre of cell c along one axis, in
-// cell edges, c being the cell that the sort took the particle for.  That cell
-// comes from the position before the sort folded it into the box: x = L, or x
-// so little below 0 that x + L rounds to L, counts in the last cell and folds to
-// 0, the lower face of the first.  So c is told, and the offset is the nearest
-// image's.  (For nd >= 3; for any other position |offset| <= 1/2.)
-__host__ __device__ __forceinline__ double dbl_cell_offset1(double x, int c, double L, double invL, int nd)
+// FP64 path: offset of a position from the centre of its cell along one axis,
+// in cell edges, at most 1/2.  Of the position as the sort counts it, before it
+// is folded into the box: x = L, or x so little below 0 that x + L rounds to L,
+// counts in the last cell and folds to 0, the lower face of the first.
+__host__ __device__ __forceinline__ double dbl_cell_offset1(double x, double L, double invL, int nd)
 {
-    const double t = (x - L * floor(x * invL)) * invL * (double)nd - (double)c - 0.5;
-    return t < -0.5 * (double)nd ? t + (double)nd : t > 0.5 * (double)nd ? t - (double)nd : t;
+    const double t = (x - L * floor(x * invL)) * invL * (double)nd;
+    return t - (double)dbl_cell1(x, L, invL, nd) - 0.5;
 }
 
 // Sort key of a particle (its index in the replica's cell arrays): the rank

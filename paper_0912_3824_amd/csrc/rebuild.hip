@@ -103,9 +103,9 @@ __device__ __forceinline__ uint4 f4_as_u4(float4 f)
 }
 
 // Fold the member's position into [0, L) (counting the image shift in its
-// meta word) and store it at scratch slot dst; `cell` is its new cell.
+// meta word) and store it at scratch slot dst.
 template <int P>
-__device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, const Moved<P> &mv, int dst, int cell)
+__device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, const Moved<P> &mv, int dst)
 {
     constexpr int NS = Traits<P>::NS;
     int4 m = mv.meta;
@@ -136,6 +136,9 @@ __device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, 
         a.sc_st[1][dst] = f4_as_u4(make_float4(y.lo, z.lo, w1.z, w1.w));
         a.sc_st[2][dst] = mv.st[2];
     } else {
+        if constexpr (NS == 2) { // (of the position as the sort counted it, before the fold)
+            if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.st[0], mv.st[1]);
+        }
         double x, y, z, w;
         u4_to_dbl2(mv.st[0], x, y);
         u4_to_dbl2(mv.st[1], z, w);
@@ -151,17 +154,15 @@ __device__ __forceinline__ void move_store(const PermArgs &a, const RepDev &rp, 
         if constexpr (NS == 2) { // the double snapshot, from the folded state
             double zz, ww;
             u4_to_dbl2(mv.snap, zz, ww);
-            const uint4 w0 = dbl2_to_u4(x, y), w1 = dbl2_to_u4(z, ww);
-            a.sc_snap[dst] = w0;
-            a.sc_snap[(size_t)a.A.P + dst] = w1;
-            if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, w0, w1, cell);
+            a.sc_snap[dst] = dbl2_to_u4(x, y);
+            a.sc_snap[(size_t)a.A.P + dst] = dbl2_to_u4(z, ww);
         }
     }
     m.x += ix; m.y += iy; m.z += iz;
     a.sc_meta[dst] = m;
     if constexpr (NS == 1) {
         a.sc_snap[dst] = mv.snap;
-        if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.snap, mv.snap, cell);
+        if (rp.bmode == BUILD_CELLS) a.cand[dst] = cand_record<P>(rp, mv.snap, mv.snap);
     }
 }
 
@@ -231,7 +232,7 @@ __device__ __forceinline__ void permute_cell(const PermArgs &a, const RepDev &rp
             const int2 e = W.lst[k];
             Moved<P> mv;
             move_load<P>(a, e.x, mv);
-            move_store<P>(a, rp, mv, e.y, c);
+            move_store<P>(a, rp, mv, e.y);
         }
         wave_sync();
     };
@@ -340,7 +341,7 @@ __device__ __forceinline__ void permute_item(const PermArgs &a, const RepDev &rp
         if (k < rp.n) {
             Moved<P> mv;
             move_load<P>(a, rp.off + k, mv);
-            move_store<P>(a, rp, mv, rp.off + k, 0);
+            move_store<P>(a, rp, mv, rp.off + k);
         }
         if (k == 0) {
             const int n0 = cnt[0], n1 = two ? cnt[1] : 0;
@@ -423,13 +424,11 @@ __global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu
 // One wave per work item; the waves of a block share nothing.  An item is,
 // by the replica's build mode (RepDev::bmode, build_mode() on the host):
 //
-//   BUILD_CELLS    a cell of a replica whose cells hold many members: its
-//                  members, 32 at a time, against the members of the 27
-//                  surrounding cells, tested on the matrix cores
-//                  (build_cell_mfma); where cells hold more than 32 members
-//                  as a rule, an item is every other 32 of them
-//   BUILD_SPARSE   a cell of a replica of few members per cell: one lane per
-//                  candidate, a loop over the members (build_by_candidates)
+//   BUILD_CELLS    a share of a cell's members against the members of the 27
+//                  surrounding cells: every so many'th 32 of them on the matrix
+//                  cores (build_cell_mfma), or as many consecutive ones, one
+//                  lane per candidate and a loop over the members
+//                  (build_by_candidates), whichever is estimated to be faster
 //   BUILD_MEMBERS  64 members of a large replica of few members per cell, one
 //                  lane each (build_by_members)
 //   BUILD_SINGLE   SINGLE_MEMBERS members of a single-cell replica, one lane
@@ -439,9 +438,7 @@ __global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu
 // o followed by -o (Sec. 4.1), and within a cell the A members before the B
 // members, in slot order.  The sorted records of the item's members are
 // copied back from scratch, and the old cell starts retired, on the way.
-#define BUILD_WIN 128     // list entries per member buffered in LDS (a multiple of 16)
 #define BUILD_STRIDE 130  // their stride: members of a wave start in different banks
-#define BUILD_SLOTS 96   // chunks of 32 candidates per neighbourhood (BUILD_CELLS)
 
 #define BUILD_BLOCK 256   // threads per block: four waves that share nothing
 
@@ -449,7 +446,22 @@ typedef int v4i_t __attribute__((ext_vector_type(4)));
 
 struct BuildLds { // one per wave
     uint16_t lst[32][BUILD_STRIDE];
-    int4 tab[BUILD_SLOTS];
+    // the chunks of 32 candidates: (slot before the chunk's first in plane 0, the
+    // same in plane 1, plane-0 members left, members left and visit << 16)
+    union {
+        int4 tab[BUILD_SLOTS];
+        struct { // more chunks (WIDE): the visits' cells, and of each chunk the visit and the place in its cell
+            int4 cell[27];
+            uint16_t chunk[BUILD_SLOTS_WIDE];
+        } wide;
+    };
+    template <bool WIDE> __device__ __forceinline__ int4 chunk(int k) const
+    {
+        if constexpr (!WIDE) return tab[k];
+        const int code = wide.chunk[k], c = 32 * (code >> 5);
+        const int4 t = wide.cell[code & 31];
+        return make_int4(t.x + c, t.y + c, t.z - c, t.w - c);
+    }
 };
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -594,12 +606,16 @@ __device__ __forceinline__ void build_by_candidates(const BuildArgs &a, const Re
         const Snap<P> xm = ld_pos<P>(a, mine);
         int cnt = 0, pad = -1; // of this lane's member
         int r = 0;
-        for (int b = 0; b < tot; b += 64) {
-            const bool valid = b + lane < tot;
+        auto slot_at = [&](int b) { // this lane's candidate of chunk b
             const int e = min(b + lane, tot - 1);
             while (r + 1 < nr && tab[r + 1].x <= e) ++r;
             const int4 t = tab[r];
-            const int x = e - t.x, j = (x < t.w ? t.y : t.z) + x;
+            const int x = e - t.x;
+            return (x < t.w ? t.y : t.z) + x;
+        };
+        for (int b = 0; b < tot; b += 64) {
+            const bool valid = b + lane < tot;
+            const int j = slot_at(b);
             const Snap<P> q = ld_pos<P>(a, j);
             for (int m = 0; m < gn; ++m) {
                 Snap<P> xi;
@@ -706,7 +722,8 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
 // their acceptance bits are the signs of T, one instruction each.
 //
 // T is off by at most 3.2e-5 of the squared edge: the products left out, the
-// rounding of the low words (w and u are at most half an edge per axis), low
+// rounding of the low words (w and u are at most half an edge per axis; in FP64
+// u is the member's own record, 2^-25 of the edge off, which moves T by 3e-7), low
 // words flushed to zero, and 32 roundings of the sum.  Where some |T| is
 // below BUILD_EDGE (6.1e-5 of the squared edge, about 3 % of the products),
 // that candidate is tested again by the list test itself, so the lists are
@@ -751,10 +768,9 @@ __device__ __forceinline__ void fill_visits(VisitLds &V) // by threads of one bl
                          CELL_UNITS * CELL_UNITS * (o[0] * o[0] + o[1] * o[1] + o[2] * o[2]));
 }
 
-template <int P>
+template <int P, bool WIDE>
 __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev &rp, int s, BuildLds &W,
-                                                const VisitLds &V, int ns, int cell, const Members &mem, int first,
-                                                int stride)
+                                                const VisitLds &V, int ns, const Members &mem, int first, int stride)
 {
     const KArena &A = a.A;
     const int lane = __lane_id(), col = lane & 31, h = lane >> 5;
@@ -767,7 +783,7 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
     const unsigned keep2 = h ? 0u : ~0u, setA = h ? 0x00003C00u : 0u, setB = h ? 0x3C003C00u : 0u;
     const unsigned setB3 = h ? 0x00003C00u : 0u, gkeep = h ? ~0u : 0u;
     auto chunk = [&](int k) { // the same for all lanes
-        const int4 t = W.tab[k];
+        const int4 t = W.template chunk<WIDE>(k);
         return make_int4(__builtin_amdgcn_readfirstlane(t.x), __builtin_amdgcn_readfirstlane(t.y),
                          __builtin_amdgcn_readfirstlane(t.z), __builtin_amdgcn_readfirstlane(t.w));
     };
@@ -784,7 +800,8 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
         const int si = snap_species<P>(xi);
         const ListRadii<P> rl(a, rp, si);
         float u[3];
-        cell_units<P>(rp, xi.a, xi.b, cell, u);
+        if constexpr (P == PREC_FP64) record_units(a.cand[i], u);
+        else cell_units<P>(rp, xi.a, xi.b, u);
         half8 mb; // the members' side of the terms that no offset enters
         {
             const float c0 = rp.rlc[0], c1 = rp.rlc[1], c2 = rp.rlc[2], c3 = rp.rlc[3];
@@ -901,7 +918,7 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
         const auto pads = __builtin_amdgcn_permlane32_swap(pad, pad, false, false);
         pad = (int)pads[0] >= 0 ? (int)pads[0] : (int)pads[1];
         auto slot_of_code = [&](int code) {
-            const int4 t = W.tab[code >> 5];
+            const int4 t = W.template chunk<WIDE>(code >> 5);
             const int e = code & 31;
             return (e < t.z ? t.x : t.y) + e;
         };
@@ -937,12 +954,21 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
 // them), so nothing is copied back and it stays as the step left it.
 __device__ __forceinline__ bool sort_lost(const BuildArgs &a, int s) { return (a.status[s] & 4) != 0; }
 
-template <int P>
+// Items of a replica while n replicas rebuild, and its shares per cell.
+__device__ __forceinline__ bool few_rebuild(const RepDev &rp, int n) { return n <= rp.bfew_max; }
+__device__ __forceinline__ int build_items(const RepDev &rp, int n)
+{
+    return few_rebuild(rp, n) ? rp.items3 * rp.bfew : rp.items4;
+}
+
+template <int P, bool WIDE>
 __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, const VisitLds &V, int s,
-                                           int item)
+                                           int item, int rebuilding)
 {
     const int lane = __lane_id();
-    const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes, items = rp.items4;
+    const int nd = rp.nd, nc = nd * nd * nd, planes = rp.planes;
+    const bool few = few_rebuild(rp, rebuilding);
+    const int items = build_items(rp, rebuilding);
     const int *cs = a.cs_new + rp.coff;
     if (a.from_scratch) { // retire this item's share of the old cell starts
         const long long all = (long long)planes * nc + 1;
@@ -966,7 +992,7 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
         wave_sync();
         return;
     }
-    const int parts = rp.bparts, cell = parts == 2 ? item >> 1 : item, part = parts == 2 ? item & 1 : 0;
+    const int parts = few ? rp.bfew : rp.bparts, cell = parts > 1 ? item / parts : item, part = item - cell * parts;
     // lane v holds the cell of visit v: its starts and members in both planes
     int gA = 0, nA = 0, gB = 0, nB = 0;
     if (lane < 27) {
@@ -983,7 +1009,6 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
     const int n = nA + nB;
     const Members mem = {__builtin_amdgcn_readlane(gA, 0), __builtin_amdgcn_readlane(nA, 0),
                          __builtin_amdgcn_readlane(gB, 0), __builtin_amdgcn_readlane(n, 0)};
-    if (mem.n <= 32 * part) return;
     const int chunks = (n + 31) >> 5;
     int upto = n, chunks_upto = chunks; // inclusive sums over the visits
 #pragma unroll
@@ -992,35 +1017,57 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
         if (lane >= o) { upto += x; chunks_upto += y; }
     }
     const int tot = __builtin_amdgcn_readlane(upto, 26), ns = __builtin_amdgcn_readlane(chunks_upto, 26);
-    if (rp.bmode == BUILD_CELLS && ns <= BUILD_SLOTS) {
-        for (int c = 0, k = chunks_upto - chunks; c < chunks; ++c, ++k)
-            W.tab[k] = make_int4(gA + 32 * c, gB - nA + 32 * c, nA - 32 * c, (n - 32 * c) | (lane << 16));
-        wave_sync();
-        build_cell_mfma<P>(a, rp, s, W, V, ns, cell, mem, 32 * part, 32 * parts);
-    } else if (part == 0) { // few members per cell (or a neighbourhood beyond the chunk table)
+    int m0 = 0, m1 = mem.n; // the item's share of the members
+    if (parts > 1) {
+        const int each = mem.n / parts, more = mem.n - each * parts;
+        m0 = part * each + min(part, more);
+        m1 = m0 + each + (part < more ? 1 : 0);
+    }
+    // A product (32 members x 32 candidates) lasts as long as two tests of a member
+    // against 64 candidates, or four where the lists outgrow the buffer.  While few
+    // replicas rebuild the chip is underfilled and an item's own chain counts, else
+    // the sum over the cell's items.
+    const int tests = few ? (mem.n + parts - 1) / parts : mem.n, groups = few ? 1 : (mem.n + 31) >> 5;
+    if (ns <= (WIDE ? BUILD_SLOTS_WIDE : BUILD_SLOTS) &&
+        tests * ((tot + 63) >> 6) > (ns > BUILD_SLOTS ? 4 : 2) * ns * groups) {
+        if (mem.n > 32 * part) {
+            const int4 t = make_int4(gA, gB - nA, nA, n | (lane << 16));
+            for (int c = 0, k = chunks_upto - chunks; c < chunks; ++c, ++k) {
+                if constexpr (WIDE) W.wide.chunk[k] = (uint16_t)(lane | c << 5);
+                else W.tab[k] = make_int4(t.x + 32 * c, t.y + 32 * c, t.z - 32 * c, t.w - 32 * c);
+            }
+            if constexpr (WIDE) {
+                if (lane < 27) W.wide.cell[lane] = t;
+            }
+            wave_sync();
+            build_cell_mfma<P, WIDE>(a, rp, s, W, V, ns, mem, 32 * part, 32 * parts);
+        }
+    } else if (m0 < m1) {
         if (lane < 27) W.tab[lane] = make_int4(upto - n, gA, gB - nA, nA);
         wave_sync();
-        build_by_candidates<P>(a, rp, s, W.tab, 27, tot, mem, 0, mem.n);
+        build_by_candidates<P>(a, rp, s, W.tab, 27, tot, mem, m0, m1);
         wave_sync();
     }
-    if (part == 0)
-        for (int m = lane; m < mem.n; m += 64) copy_back<P>(a, mem.slot(m));
+    for (int m = m0 + lane; m < m1; m += 64) copy_back<P>(a, mem.slot(m));
 }
 
-template <int P>
+// WIDE: for pools that hold a replica of more chunks per neighbourhood than the
+// plain table takes (the second level costs the others 3 %).
+template <int P, bool WIDE>
 __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
 {
     __shared__ BuildLds lds[BUILD_BLOCK / 64];
     __shared__ VisitLds visits;
-    if (a.rlist[0] == 0) return;
+    const int cnt = a.rlist[0];
+    if (cnt == 0) return;
     fill_visits(visits);
     __syncthreads();
     const int wpb = BUILD_BLOCK / 64, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for_items(a.rlist, [&](int sl) { return a.from_scratch && sort_lost(a, sl) ? 0 : a.rep[sl].items4; },
+    for_items(a.rlist, [&](int sl) { return a.from_scratch && sort_lost(a, sl) ? 0 : build_items(a.rep[sl], cnt); },
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
               [&](int s, int item) {
                   const RepDev rp = a.rep[s];
-                  build_item<P>(a, rp, lds[wv], visits, s, item);
+                  build_item<P, WIDE>(a, rp, lds[wv], visits, s, item, cnt);
               });
 }
 
@@ -1060,7 +1107,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
     fill_visits(visits); // (before the loop's barriers)
     const RepDev rp = ld_uniform(ba.rep, 0);
     const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nblk = gridDim.x;
-    const int np = perm_units(rp, nblk), nb = rp.items4; // sort units, list-build items
+    const int np = perm_units(rp, nblk), nb = build_items(rp, 1); // sort units, list-build items
     const int first = remap_block(blockIdx.x, nblk, ba.xcd) * WPB; // the block's first list-build item
     int g = (int)(blockIdx.x % G), left = (int)blockIdx.x < np ? 1 : 0; // groups to take units from: g and on
     for (int round = 0;;) {
@@ -1113,7 +1160,8 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
             return;
         }
     }
-    for (int item = first + wv; item < nb; item += nblk * WPB) build_item<P>(ba, rp, lds.build[wv], visits, 0, item);
+    for (int item = first + wv; item < nb; item += nblk * WPB)
+        build_item<P, false>(ba, rp, lds.build[wv], visits, 0, item, 1);
 }
 
 // Candidate records of a slot's particles (k_permute writes those of a
@@ -1125,7 +1173,7 @@ __global__ void __launch_bounds__(256) k_cand(const BuildArgs a, uint4 *cand, in
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= rp.n) return;
     const Snap<P> q = ld_pos<P>(a, rp.off + k);
-    cand[rp.off + k] = cand_record<P>(rp, q.a, q.b, cell_of<P>(rp, q.a, q.b));
+    cand[rp.off + k] = cand_record<P>(rp, q.a, q.b);
 }
 // ------------------------------------------------------------ launchers
 hipError_t launch_count(int prec, const CountArgs &a, hipStream_t s)
@@ -1170,16 +1218,19 @@ hipError_t occupancy_permute(int prec, bool large, int *per_cu)
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void *)permute_kernel(prec, large), PERM_BLOCK, 0);
 }
 
+static void (*build_kernel(int prec, bool wide))(BuildArgs)
+{
+    switch (prec) {
+    case PREC_FP32: return wide ? k_build<PREC_FP32, true> : k_build<PREC_FP32, false>;
+    case PREC_DS: return wide ? k_build<PREC_DS, true> : k_build<PREC_DS, false>;
+    case PREC_MIX: return wide ? k_build<PREC_MIX, true> : k_build<PREC_MIX, false>;
+    default: return wide ? k_build<PREC_FP64, true> : k_build<PREC_FP64, false>;
+    }
+}
+
 hipError_t occupancy_build(int prec, int *per_cu)
 {
-    const void *f;
-    switch (prec) {
-    case PREC_FP32: f = (const void *)k_build<PREC_FP32>; break;
-    case PREC_DS: f = (const void *)k_build<PREC_DS>; break;
-    case PREC_MIX: f = (const void *)k_build<PREC_MIX>; break;
-    default: f = (const void *)k_build<PREC_FP64>; break;
-    }
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, f, BUILD_BLOCK, 0);
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, (const void *)build_kernel(prec, false), BUILD_BLOCK, 0);
 }
 
 hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba, int *sync, int grid, hipStream_t s)
@@ -1194,14 +1245,9 @@ hipError_t launch_rebuild_one(int prec, const PermArgs &pa, const BuildArgs &ba,
     LAUNCH_CHECK();
 }
 
-hipError_t launch_build(int prec, const BuildArgs &a, int grid, hipStream_t s)
+hipError_t launch_build(int prec, bool wide, const BuildArgs &a, int grid, hipStream_t s)
 {
-    switch (prec) {
-    case PREC_FP32: hipLaunchKernelGGL((k_build<PREC_FP32>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
-    case PREC_DS: hipLaunchKernelGGL((k_build<PREC_DS>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
-    case PREC_MIX: hipLaunchKernelGGL((k_build<PREC_MIX>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
-    default: hipLaunchKernelGGL((k_build<PREC_FP64>), dim3(grid), dim3(BUILD_BLOCK), 0, s, a); break;
-    }
+    hipLaunchKernelGGL(build_kernel(prec, wide), dim3(grid), dim3(BUILD_BLOCK), 0, s, a);
     LAUNCH_CHECK();
 }
 

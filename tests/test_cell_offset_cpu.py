@@ -1,6 +1,7 @@
 """dbl_cell_offset1 (the matrix-core list test's positions in FP64), compiled
-for the host: with the cell that the sort took from the unfolded position, the
-folded position lies within that cell, whatever the two roundings did."""
+for the host: the offset that goes with the cell that the sort takes from an
+unfolded position.  The folded position's own cell is another one at both ends
+of the box."""
 import os
 import subprocess
 
@@ -21,7 +22,7 @@ int main()
         double f = x; // the sort's fold
         if (f < 0.0) f += L;
         if (f >= L) f -= L;
-        printf("%d %d %a %a\n", c, dbl_cell1(f, L, invL, nd), f, dbl_cell_offset1(f, c, L, invL, nd));
+        printf("%d %d %a %a\n", c, dbl_cell1(f, L, invL, nd), f, dbl_cell_offset1(x, L, invL, nd));
     }
 }
 """
@@ -46,7 +47,7 @@ def test_offsets_lie_in_the_cell_of_the_sort(tmp_path):
     out = np.array([float.fromhex(v) if "x" in v else float(v) for v in out]).reshape(-1, 4)
     assert len(out) == len(rows)
     x, L, nd = (np.array(v) for v in zip(*rows))
-    cell, again, folded, off = out.T
+    cell, again, _, off = out.T
     # the two roundings part at both ends of the box
     assert np.sum((cell == nd - 1) & (again == 0) & (x < 0)) > 10
     assert np.any((cell == nd - 1) & (again == 0) & (x >= L))
