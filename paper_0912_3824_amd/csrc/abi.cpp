@@ -481,13 +481,32 @@ static StepArgs step_args(const md_system *s, int p)
     return a;
 }
 
-// One rebuild launch instead of two (k_rebuild) for pools of one slot up to
-// this size.  With several slots some replica rebuilds every few steps, and the
-// barrier in the kernel costs those steps more (5 to 30 us) than the idle
-// launch that the others save (1.5 us); for one slot both forms take the same
-// time at 64,000 particles, which rebuild every 25 steps.
-#define ONE_REBUILD_MAX 49152
-static bool one_rebuild(const md_system *s) { return s->lay.slots == 1 && s->lay.P <= ONE_REBUILD_MAX && s->n_wide == 0; }
+// One rebuild launch instead of two (k_rebuild), for pools of one slot: every
+// step saves an idle launch, 1.45 us, and a step that rebuilds pays for the
+// barrier in the kernel, about 2 us and 1 us for 80 cells (each sort unit of four
+// cells writes its XCD's L2 back; there are at most 1,024 units).  So it is a
+// matter of how often the replica rebuilds: when its fastest particle, at about
+// 4.7 sqrt(T / m), has gone half a skin, taken here at T = eps.  (With several
+// slots some replica rebuilds every few steps.)
+//
+// Us a step with one launch and with two (over 105 such pairs the rule's choice is
+// the lower one or within 2 % of it, 5 % once): mixture, time step 0.001, skin 0.3 (a rebuild every 26
+// to 42 steps): 600 particles 8.4 and 9.9, 8,000 9.9 and 11.4, 37,000 13.2 and
+// 14.2, 48,000 15.4 and 16.3; 0.002 (every 13 to 16): 24,000 15.0 and 15.6,
+// 48,000 20.4 and 20.3; 0.004, skin 0.25 (every 5): 8,000 20.2 and 20.8, 24,000
+// 24.1 and 23.0, 48,000 31.0 and 27.7.  A fluid of 20,000 at density 0.3 (2,744
+// cells), 0.001: 8.6 and 9.4, 0.002: 12.2 and 11.5, 0.004: 21.6 and 16.2; one of
+// 8,000 with the cutoff at the minimum (3,375 cells), 0.003: 12.8 and 10.7.
+#define ONE_REBUILD_MAX 49152 // particles: beyond, steps are long and rebuilds fill the chip
+static bool one_rebuild(const md_system *s)
+{
+    if (s->lay.slots != 1 || s->lay.P > ONE_REBUILD_MAX || s->n_wide > 0) return false;
+    const md_config &c = s->cfg;
+    double every = c.skin / (9.4 * c.dt * std::sqrt(c.eps[0] / c.mass));
+    if (c.rebuild_every > 0) every = std::max((double)c.rebuild_every, c.rebuild_early * every);
+    const int nd = s->slots[0].nd;
+    return std::min(2 + nd * nd * nd / 80.0, 36.0) <= 1.45 * every;
+}
 
 // The rebuild launches that follow a step of parity p: the replicas on its
 // rebuild list are sorted and their lists built.
@@ -578,7 +597,7 @@ static md_status launch_one_step(md_system *s, int p)
 // `parity`, captured once into a hipGraph and cached by (steps, parity).
 static md_status get_graph(md_system *s, int steps, int parity, hipGraphExec_t *out)
 {
-    const int key = 4 * steps + 2 * (s->n_wide > 0) + parity; // (the launches depend on the list build's form)
+    const int key = 8 * steps + 4 * one_rebuild(s) + 2 * (s->n_wide > 0) + parity; // (steps of up to 256 a graph)
     auto it = s->graphs.find(key);
     if (it != s->graphs.end()) { *out = it->second; return MD_OK; }
     if (s->graphs.size() >= 64) drop_graphs(s); // callers cycling through many step counts
