@@ -889,9 +889,14 @@ __global__ void __launch_bounds__(H > 1 ? 256 : 1024) k_step(const StepArgs a)
 template <int P, int KIND, int LPP>
 static void launch_step_k(const StepArgs &a, int grid, int block, int h, bool obs, hipStream_t s)
 {
-    if (obs && h > 1) hipLaunchKernelGGL((k_step<P, true, KIND, LPP, true, QUAD>), dim3(grid), dim3(block), 0, s, a);
-    else if (obs) hipLaunchKernelGGL((k_step<P, true, KIND, LPP, false, 1>), dim3(grid), dim3(block), 0, s, a);
-    else if (h > 1) hipLaunchKernelGGL((k_step<P, false, KIND, LPP, true, QUAD>), dim3(grid), dim3(block), 0, s, a);
+    if constexpr (LPP <= 2) { // (lists of four lanes take no quads, see launch_step)
+        if (h > 1) {
+            if (obs) hipLaunchKernelGGL((k_step<P, true, KIND, LPP, true, QUAD>), dim3(grid), dim3(block), 0, s, a);
+            else hipLaunchKernelGGL((k_step<P, false, KIND, LPP, true, QUAD>), dim3(grid), dim3(block), 0, s, a);
+            return;
+        }
+    }
+    if (obs) hipLaunchKernelGGL((k_step<P, true, KIND, LPP, false, 1>), dim3(grid), dim3(block), 0, s, a);
     else if (a.max_slots == 1) hipLaunchKernelGGL((k_step<P, false, KIND, LPP, true, 1>), dim3(grid), dim3(block), 0, s, a);
     else hipLaunchKernelGGL((k_step<P, false, KIND, LPP, false, 1>), dim3(grid), dim3(block), 0, s, a);
 }
