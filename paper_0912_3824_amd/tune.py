@@ -29,6 +29,10 @@ SPACE = {
 # present list build; kept for callers that read the space).
 ALIGNED_SPACE = {"build_bulk": [0, 32]}
 
+# Fields without effect on the present kernels: shapes that differ in them alone
+# are timed once.
+INERT = ("build_width", "build_block", "build_lanes", "build_split", "build_bulk")
+
 
 def bucket(n_total: int) -> int:
     return int(round(math.log2(max(n_total, 1)) * 2))
@@ -86,9 +90,14 @@ def tune(pool, steps: int = 200, space: Optional[Dict[str, List[int]]] = None,
             pool.restore(s, blobs[s], sizes[s], boxes[s])
 
     results = []
+    seen = set()
     names = list(space)
     for combo in itertools.product(*(space[k] for k in names)):
         shape = dict(zip(names, combo))
+        live = tuple(v for k, v in shape.items() if k not in INERT)
+        if live in seen:
+            continue
+        seen.add(live)
         restore_all()
         pool.set_launch(**shape)
         pool.step(2)          # graph capture / warm caches
