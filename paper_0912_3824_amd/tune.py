@@ -30,7 +30,7 @@ SPACE = {
 ALIGNED_SPACE = {"build_bulk": [0, 32]}
 
 # Fields without effect on the present kernels: shapes that differ in them alone
-# are timed once.
+# are timed once and share the time.
 INERT = ("build_width", "build_block", "build_lanes", "build_split", "build_bulk")
 
 
@@ -90,22 +90,20 @@ def tune(pool, steps: int = 200, space: Optional[Dict[str, List[int]]] = None,
             pool.restore(s, blobs[s], sizes[s], boxes[s])
 
     results = []
-    seen = set()
+    timed = {}
     names = list(space)
     for combo in itertools.product(*(space[k] for k in names)):
         shape = dict(zip(names, combo))
         live = tuple(v for k, v in shape.items() if k not in INERT)
-        if live in seen:
-            continue
-        seen.add(live)
-        restore_all()
-        pool.set_launch(**shape)
-        pool.step(2)          # graph capture / warm caches
-        restore_all()
-        dt = _time_steps(pool, steps)
-        results.append((dt, shape))
-        if verbose:
-            print(f"[tune] {shape} -> {dt * 1e6:.1f} us/step", flush=True)
+        if live not in timed:
+            restore_all()
+            pool.set_launch(**shape)
+            pool.step(2)          # graph capture / warm caches
+            restore_all()
+            timed[live] = _time_steps(pool, steps)
+            if verbose:
+                print(f"[tune] {shape} -> {timed[live] * 1e6:.1f} us/step", flush=True)
+        results.append((timed[live], shape))
     results.sort(key=lambda r: r[0])
     best = results[0][1]
     restore_all()
