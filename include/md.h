@@ -99,8 +99,8 @@ typedef enum {
 #define MD_ST_LIST_OVERFLOW 1 /* a particle had more neighbours than nbr_capacity */
 #define MD_ST_NONFINITE 2     /* a position became NaN/Inf */
 #define MD_ST_LOST 4          /* cell counting lost particles (follows NONFINITE) */
-#define MD_ST_NO_PAD 8        /* a list could not be padded: every particle of the
-                                 replica lies within the list radius of another */
+#define MD_ST_NO_PAD 8        /* a list could not be padded: every other particle of
+                                 the replica is in it */
 #define MD_ST_AT_FULL_STEP 256 /* not an error: velocities are at a full step
                                   (reported by md_poll only) */
 

@@ -555,6 +555,26 @@ __device__ __forceinline__ void pad_list(const KArena &A, int i, int cnt, int k0
     for (int k = max(cnt, k0); k < ((cnt + gm) & ~gm) && k < A.cap; ++k) put_entry(A, i, k, pad < 0 ? i : pad);
 }
 
+// A particle to pad the list of slot i with where every other particle of its 27
+// cells is in it (a dilute gas, a small cluster): cnt are within its list
+// radius, so of any cnt + 1 others one is not.  -1 where the replica has no such
+// particle, or the list needs no padding.
+template <int P>
+__device__ __forceinline__ int far_particle(const BuildArgs &a, const RepDev &rp, int i, int cnt)
+{
+    if (!(cnt & ((4 << a.A.lg) - 1))) return -1;
+    const Snap<P> xi = ld_pos<P>(a, i);
+    const ListRadii<P> rl(a, rp, snap_species<P>(xi));
+    int j = i + rp.n / 2; // (half the replica's slots away: the first one will do)
+    for (int k = min(cnt + 1, rp.n - 1); k > 0; --k, ++j) {
+        j -= j >= rp.off + rp.n ? rp.n : 0;
+        if (j == i) ++j;
+        j -= j >= rp.off + rp.n ? rp.n : 0;
+        if (!in_list<P>(rp, xi, rl, ld_pos<P>(a, j))) return j;
+    }
+    return -1;
+}
+
 // List length of slot i, and the status bits of a list that overflowed or
 // that needed padding and found none.
 __device__ __forceinline__ void finish_list(const BuildArgs &a, int s, int i, int cnt, bool padded)
@@ -647,6 +667,7 @@ __device__ __forceinline__ void build_by_candidates(const BuildArgs &a, const Re
             }
         }
         if (lane < gn) {
+            if (pad < 0) pad = far_particle<P>(a, rp, mine, cnt);
             pad_list(A, mine, cnt, 0, pad);
             finish_list(a, s, mine, cnt, pad >= 0);
         }
@@ -700,6 +721,7 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
         }
     }
     if (live) {
+        if (pad < 0) pad = far_particle<P>(a, rp, i, cnt);
         pad_list(A, i, cnt, 0, pad);
         finish_list(a, s, i, cnt, pad >= 0);
     }
@@ -937,12 +959,13 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
                 for (int c = 0; c < 4; ++c) row[c] = list_entry(slot_of_code(lp[c << lg]));
                 dst[(size_t)q * LIST_TILE] = row;
             }
-            if (pad < 0) // nothing to pad with: the list is not stepped on (the replica stops)
+            const int far = pad >= 0 ? i : far_particle<P>(a, rp, i, cnt);
+            if (pad < 0) // (where there is no such particle, the replica stops)
                 for (int k = buffered; k < filled; ++k)
-                    if ((list_entry_row(k, lg) & 1) == h) put_entry(A, i, k, i);
+                    if ((list_entry_row(k, lg) & 1) == h) put_entry(A, i, k, far < 0 ? i : far);
             if (h == 0) {
-                if (used > BUILD_WIN) pad_list(A, i, used, BUILD_WIN, pad >= 0 ? slot_of_code(pad) : -1);
-                finish_list(a, s, i, cnt, pad >= 0);
+                if (used > BUILD_WIN) pad_list(A, i, used, BUILD_WIN, pad >= 0 ? slot_of_code(pad) : far);
+                finish_list(a, s, i, cnt, far >= 0);
             }
         }
         wave_sync();
