@@ -407,7 +407,7 @@ static BuildShape build_shape(const md_system *s, int n, double L, int nd)
 static int items4_of(const BuildShape &b, int n, int nd)
 {
     switch (b.mode) {
-    case BUILD_SINGLE: return (n + SINGLE_MEMBERS - 1) / SINGLE_MEMBERS;
+    case BUILD_SINGLE: return 0; // (by how many replicas rebuild: single_members)
     case BUILD_MEMBERS: return (n + 63) / 64;
     default: return nd * nd * nd * b.parts;
     }

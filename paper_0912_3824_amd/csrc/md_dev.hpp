@@ -68,7 +68,6 @@ enum { BUILD_SINGLE = 0, BUILD_CELLS = 1, BUILD_MEMBERS = 2 };
 #define BUILD_SLOTS 96       // chunks of 32 candidates a neighbourhood may have (BUILD_CELLS) ...
 #define BUILD_SLOTS_WIDE 552 // ... and in the wide form
 #define BUILD_WIN 128        // list entries per member buffered in LDS (a multiple of 16)
-#define SINGLE_MEMBERS 2     // members per list-build work item of a single-cell replica
 #define CELL_UNITS 64.0f     // cell edge in the units of the list build's candidate records
 
 // Control word of a slot: x = completed steps, y = 1 if velocities are at a

@@ -422,7 +422,7 @@ __global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu
 
 // ------------------------------------------------------------ k_build
 // One wave per work item; the waves of a block share nothing.  An item is,
-// by the replica's build mode (RepDev::bmode, build_mode() on the host):
+// by the replica's build mode (RepDev::bmode, build_shape() on the host):
 //
 //   BUILD_CELLS    a share of a cell's members against the members of the 27
 //                  surrounding cells: every so many'th 32 of them on the matrix
@@ -431,8 +431,8 @@ __global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu
 //                  (build_by_candidates), whichever is estimated to be faster
 //   BUILD_MEMBERS  64 members of a large replica of few members per cell, one
 //                  lane each (build_by_members)
-//   BUILD_SINGLE   SINGLE_MEMBERS members of a single-cell replica, one lane
-//                  per candidate
+//   BUILD_SINGLE   members of a single-cell replica: two or eight, one lane per
+//                  candidate, or 64, one lane each (single_members)
 //
 // Every form writes the same list: the own cell, then each half-space offset
 // o followed by -o (Sec. 4.1), and within a cell the A members before the B
@@ -727,6 +727,65 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
     }
 }
 
+// 64 members of a single-cell replica, one lane each, against all of its
+// particles, which are the same for all lanes and come by scalar loads (only
+// where the sort ran in a launch of its own), a few at a time so that they are
+// in flight together.  Slots are taken 32 at a time from a multiple of 32 on,
+// so that no load leaves the arena.  A test of 64 members takes 14 instructions,
+// against 50 for a member and 64 candidates above, where the ballot and the
+// entry's place cost as much as the test; what bounds an item is its chain, 56 us
+// at 700 particles (82 with each batch waited for before the next is asked for).
+template <int P>
+__device__ __forceinline__ void build_single_members(const BuildArgs &a, const RepDev &rp, int s, int m)
+{
+    constexpr int NS = Traits<P>::NS, U = 8 / NS;
+    struct Records { uint4 r[U]; };
+    const KArena &A = a.A;
+    const int end = rp.off + rp.n, lg = A.lg;
+    const bool live = m < rp.n;
+    const int i = rp.off + min(m, rp.n - 1);
+    const Snap<P> xi = ld_pos<P>(a, i);
+    const ListRadii<P> rl(a, rp, snap_species<P>(xi));
+    int *list = A.nbr_w + 4 * list_row_index(i, 0, A.cap);
+    int cnt = 0, pad = -1;
+    auto load = [&](const uint4 *src, int j) { return ld_uniform((const Records *)(src + j), 0); };
+    Records na = load(a.src_x, rp.off & ~31), nb = na;
+    if constexpr (NS == 2) nb = load(a.src_x + A.P, rp.off & ~31);
+    const int last = ((end + 31) & ~31) - U;
+#pragma unroll 1
+    for (int b = rp.off & ~31; b < end; b += 32) {
+        unsigned hit = 0;
+#pragma unroll 1
+        for (int c = 0; c < 32; c += U) {
+            const Records ra = na, rb = nb;
+            // (the wait for these, then the next: scalar loads return in any order)
+            asm volatile("" ::"s"(ra.r[U - 1].w), "s"(rb.r[U - 1].w));
+            __builtin_amdgcn_sched_barrier(0);
+            na = load(a.src_x, min(b + c + U, last));
+            if constexpr (NS == 2) nb = load(a.src_x + A.P, min(b + c + U, last));
+            __builtin_amdgcn_sched_barrier(0);
+            unsigned h = 0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                h |= in_list<P>(rp, xi, rl, Snap<P>{ra.r[u], NS == 2 ? rb.r[u] : ra.r[u]}) ? 1u << u : 0u;
+            hit |= h << c;
+        }
+        unsigned valid = end - b >= 32 ? ~0u : (1u << (end - b)) - 1u;
+        if (b < rp.off) valid &= ~0u << (rp.off - b);
+        if ((unsigned)(i - b) < 32u) valid &= ~(1u << (i - b));
+        const unsigned miss = valid & ~hit;
+        if (miss) pad = b + __ffs(miss) - 1;
+        hit = live ? hit & valid : 0u;
+        for (; hit; hit &= hit - 1, ++cnt)
+            if (cnt < A.cap)
+                list[4 * LIST_TILE * list_entry_row(cnt, lg) + list_entry_col(cnt, lg)] = list_entry(b + __ffs(hit) - 1);
+    }
+    if (live) {
+        pad_list(A, i, cnt, 0, pad);
+        finish_list(a, s, i, cnt, pad >= 0);
+    }
+}
+
 // A cell's members against its 27-cell neighbourhood on the matrix cores.
 //
 // Positions are taken in units of 1/CELL_UNITS of the cell edge from the
@@ -977,14 +1036,24 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
 // them), so nothing is copied back and it stays as the step left it.
 __device__ __forceinline__ bool sort_lost(const BuildArgs &a, int s) { return (a.status[s] & 4) != 0; }
 
+// Members per item of a single-cell replica while n replicas rebuild.  The fewer,
+// the shorter the item's chain and the more work in all: the chain of 64 members
+// a wave is 56 us at 700 particles.  Us a forced rebuild of 64 and 256 replicas
+// of 700 with 2 members an item 187 and 510, with 8 173 and 436, with 64 174 and
+// 320; of 250 82 and 206, 79 and 191, 90 and 162; 16 of 700 99, 106 and 138;
+// 1,024 of 700 1,777, 1,508 and 892.
+__device__ __forceinline__ int single_members(int n) { return n <= 32 ? 2 : n <= 96 ? 8 : 64; }
+
 // Items of a replica while n replicas rebuild, and its shares per cell.
 __device__ __forceinline__ bool few_rebuild(const RepDev &rp, int n) { return n <= rp.bfew_max; }
 __device__ __forceinline__ int build_items(const RepDev &rp, int n)
 {
+    if (rp.bmode == BUILD_SINGLE) return (rp.n + single_members(n) - 1) / single_members(n);
     return few_rebuild(rp, n) ? rp.items3 * rp.bfew : rp.items4;
 }
 
-template <int P, bool WIDE>
+// ONE: in one launch with the sort, one replica.
+template <int P, bool WIDE, bool ONE>
 __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp, BuildLds &W, const VisitLds &V, int s,
                                            int item, int rebuilding)
 {
@@ -1006,8 +1075,15 @@ __device__ __forceinline__ void build_item(const BuildArgs &a, const RepDev &rp,
         return;
     }
     if (rp.bmode == BUILD_SINGLE) { // the replica's slots are one range in canonical order
+        const int per = ONE ? 2 : single_members(rebuilding);
+        if (!ONE && per == 64) {
+            const int m = item * 64 + lane;
+            build_single_members<P>(a, rp, s, m);
+            if (m < rp.n) copy_back<P>(a, rp.off + m);
+            return;
+        }
         const Members mem = {rp.off, rp.n, 0, rp.n};
-        const int m0 = item * SINGLE_MEMBERS, m1 = min(m0 + SINGLE_MEMBERS, rp.n);
+        const int m0 = item * per, m1 = min(m0 + per, rp.n);
         if (lane == 0) W.tab[0] = make_int4(0, rp.off, 0, rp.n);
         wave_sync();
         build_by_candidates<P>(a, rp, s, W.tab, 1, rp.n, mem, m0, m1);
@@ -1090,7 +1166,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_build(const BuildArgs a)
               remap_block(blockIdx.x, gridDim.x, a.xcd) * wpb + wv, gridDim.x * wpb,
               [&](int s, int item) {
                   const RepDev rp = a.rep[s];
-                  build_item<P, WIDE>(a, rp, lds[wv], visits, s, item, cnt);
+                  build_item<P, WIDE, false>(a, rp, lds[wv], visits, s, item, cnt);
               });
 }
 
@@ -1184,7 +1260,7 @@ __global__ void __launch_bounds__(BUILD_BLOCK, 4) k_rebuild(const PermArgs pa, c
         }
     }
     for (int item = first + wv; item < nb; item += nblk * WPB)
-        build_item<P, false>(ba, rp, lds.build[wv], visits, 0, item, 1);
+        build_item<P, false, true>(ba, rp, lds.build[wv], visits, 0, item, 1);
 }
 
 // Candidate records of a slot's particles (k_permute writes those of a

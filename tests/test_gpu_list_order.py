@@ -83,6 +83,36 @@ def test_entries_are_in_order(form, prec):
     pool.close()
 
 
+@pytest.mark.parametrize("prec", ["ds", "fp64"])
+@pytest.mark.parametrize("count", [32, 33, 96, 97])
+def test_many_single_cell_replicas(count, prec):
+    """How many members share an item goes by how many replicas rebuild together;
+    sizes of one member, of less and of more than a wave, at odd places."""
+    sizes = [601, 1, 31, 64, 65, 2, 187]
+    box = 8.0  # two cells of 2.8 an edge
+    reps = []
+    for k, n in enumerate(sizes):
+        rng = np.random.default_rng(k)
+        pos = I.fcc_positions(n, box, rng, 0.05)
+        reps.append(I.System(n, box, pos, rng.normal(size=(n, 3)), I.species_80_20(n, rng), I.ka_table(), 0.7))
+    cfg = mdx.make_config(reps[0].table, prec, 0.001, 0.3, count, 601 * count)
+    pool = mdx.MdSystem(cfg)
+    for k in range(count):
+        pool.attach_system(k, reps[k % len(reps)])
+    pool.rebuild_neighbours()
+    for k in list(range(7)) + [count - 1]:
+        s = reps[k % len(reps)]
+        pos, _, _ = pool.get_state(k)
+        slots = slots_of(pool, k, s.n)
+        ref = ordered_lists(pos, box, s.species, s.table, 0.3, None, 1, slots, np.arange(s.n))
+        near = near_cutoff(pos, box, s.species, s.table, lambda a, b: s.table.rcut[a, b] + 0.3)
+        cnt, ids = pool.neighbours(k, cap=200)
+        bad = [i for i in range(s.n) if not near[i] and not np.array_equal(ids[i, :cnt[i]], ref[i])]
+        say(f"{count} single cells {prec}, replica of {s.n}: lists of {cnt.min()} to {cnt.max()}, {len(bad)} differ")
+        assert not bad
+    pool.close()
+
+
 def test_a_replica_of_heavy_cells_comes_and_goes():
     """The list build's form follows the replicas attached, also in captured
     graphs, and changes no bit of the others' trajectories."""
