@@ -28,9 +28,9 @@
  *     workspace of md_workspace_bytes() bytes and a hipStream_t (as void*);
  *     the library never allocates or frees device memory.  The library owns
  *     only the host handle (freed by md_destroy), its host-side mirrors and,
- *     from the first call that reads data back, about 1 MiB of pinned host
- *     memory for small transfers (96 bytes a slot where that is more; freed by
- *     md_destroy too).
+ *     from the first md_attach or the first call that reads data back, up to
+ *     1 MiB of pinned host memory for small transfers either way (60 bytes a
+ *     particle; 96 bytes a slot where that is more; freed by md_destroy too).
  *   - Host arrays passed in are read before the call returns; host arrays
  *     passed out are written before the call returns.
  *   - Asynchrony: calls that only launch work (md_step, md_advance,
@@ -178,8 +178,8 @@ typedef struct {
 } md_obs;
 
 /* Launch shapes (the autotuner's knobs).  None changes any result bit.  The
- * list build takes one wave per cell whatever the build_* fields say: they
- * are checked and kept, and have no effect. */
+ * list build takes its shape from the replicas whatever the build_* fields say:
+ * they are checked and kept, and have no effect. */
 typedef struct {
     int32_t step_block;    /* threads per block of the fused step kernel: 64..1024, multiple of 64 */
     int32_t build_width;   /* 1..16; no effect */

@@ -107,7 +107,7 @@ struct md_system {
     SlotWords *words = nullptr;     // [slots], where there is no `pin`
     int *bad = nullptr;             // set by a read-back that met a corrupt particle id: the first word of `stage`
     // host state
-    void *pin = nullptr;            // pinned host memory of pin_bytes(), made by the first read-back
+    void *pin = nullptr;            // pinned host memory, made by the first attach or read-back (pinned())
     bool no_pin = false;            // it could not be had
     PairDev pp{};
     IntegDev ig{};
@@ -233,8 +233,9 @@ struct Carver {
 };
 
 // Read-backs of up to STAGE_BYTES go through device memory of the workspace
-// to pinned host memory in two launches and one synchronisation; each of the
-// pageable copies they replace costs 10 us and more before its first byte.
+// to pinned host memory in two launches and one synchronisation, and the input
+// of an attached replica the other way; each of the pageable copies they replace
+// costs 10 us and more before its first byte.
 constexpr int64_t STAGE_BYTES = 1 << 20;
 constexpr int64_t FRAME_BYTES = 60; // a particle's position, velocity and images
 static int64_t stage_words(int64_t P) { return std::min(STAGE_BYTES, align_up(P * FRAME_BYTES, 64)) / 16 + 1; }
@@ -978,7 +979,8 @@ static md_status finish_attach(md_system *s, int slot)
     return MD_OK;
 }
 
-// The pool's pinned buffer: a small read-back or every slot's words and sums.
+// The pool's pinned buffer: a small read-back, every slot's words and sums, or
+// the input of a small replica.
 // Null where it cannot be had; callers then copy from device memory.
 static void *pinned(md_system *s)
 {

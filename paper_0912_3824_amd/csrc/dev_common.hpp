@@ -6,7 +6,7 @@
 //
 // One MD step (Sec. 2.2, velocity Verlet with Verlet lists) is one fused
 // launch of k_step plus two rebuild kernels (one, k_rebuild, in small pools of
-// one slot) that exit at once unless the
+// one slot that do not rebuild too often) that exit at once unless the
 // replica's maximum displacement since its last list build exceeded skin/2:
 //
 //   k_step<P>    per particle: force over its Verlet list (FP32 pair term,
@@ -25,10 +25,10 @@
 //                over them in old slot order gives each its new slot.  The
 //                whole particle record is gathered into the scratch arena,
 //                positions folded back into the box.
-//   k_build<P>   per cell (one wave): its members' lists over the own cell and
-//                then the 13 opposite cell pairs (Sec. 4.1), the distance
-//                tests on the matrix cores; the sorted records are copied
-//                back from scratch.
+//   k_build<P>   per share of a cell's members (one wave): their lists over the
+//                own cell and then the 13 opposite cell pairs (Sec. 4.1), the
+//                distance tests on the matrix cores; the sorted records are
+//                copied back from scratch.
 //
 // Bitwise determinism: lists are in a canonical order (own cell, then +o/-o
 // pairs; inside a cell the A members, then the B members, in slot order), the sort is stable, each particle sums

@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(PERM_BLOCK) __attribute__((amdgpu_waves_per_eu
 // o followed by -o (Sec. 4.1), and within a cell the A members before the B
 // members, in slot order.  The sorted records of the item's members are
 // copied back from scratch, and the old cell starts retired, on the way.
-#define BUILD_STRIDE 130  // their stride: members of a wave start in different banks
+#define BUILD_STRIDE 130  // stride of the members' entries buffered in LDS: members of a wave start in different banks
 
 #define BUILD_BLOCK 256   // threads per block: four waves that share nothing
 
