@@ -738,7 +738,7 @@ __device__ __forceinline__ void build_by_members(const BuildArgs &a, const RepDe
 template <int P>
 __device__ __forceinline__ void build_single_members(const BuildArgs &a, const RepDev &rp, int s, int m)
 {
-    constexpr int NS = Traits<P>::NS, U = 8 / NS;
+    constexpr int NS = Traits<P>::NS, U = NS == 2 ? 2 : 8; // (more cost scalar registers: FP64 spilled)
     struct Records { uint4 r[U]; };
     const KArena &A = a.A;
     const int end = rp.off + rp.n, lg = A.lg;
@@ -1018,16 +1018,18 @@ __device__ __forceinline__ void build_cell_mfma(const BuildArgs &a, const RepDev
                 for (int c = 0; c < 4; ++c) row[c] = list_entry(slot_of_code(lp[c << lg]));
                 dst[(size_t)q * LIST_TILE] = row;
             }
-            const int far = pad >= 0 ? i : far_particle<P>(a, rp, i, cnt);
-            if (pad < 0) // (where there is no such particle, the replica stops)
-                for (int k = buffered; k < filled; ++k)
-                    if ((list_entry_row(k, lg) & 1) == h) put_entry(A, i, k, far < 0 ? i : far);
             if (h == 0) {
-                if (used > BUILD_WIN) pad_list(A, i, used, BUILD_WIN, pad >= 0 ? slot_of_code(pad) : far);
-                finish_list(a, s, i, cnt, far >= 0);
+                if (used > BUILD_WIN && pad >= 0) pad_list(A, i, used, BUILD_WIN, slot_of_code(pad));
+                finish_list(a, s, i, cnt, true);
             }
         }
         wave_sync();
+        if (live && pad < 0 && (cnt & gm)) { // (apart from the rest, whose registers are free here)
+            const int far = far_particle<P>(a, rp, i, cnt);
+            for (int k = used; k < ((cnt + gm) & ~gm) && k < cap; ++k)
+                if ((list_entry_row(k, lg) & 1) == h) put_entry(A, i, k, far < 0 ? i : far); // (the half that wrote the row)
+            if (far < 0) atomicOr(a.status + s, 8);
+        }
     }
 }
 
